@@ -19,6 +19,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <string>
+#include <thread>
 #include <unordered_set>
 #include <vector>
 
@@ -29,6 +30,7 @@
 #include "batch_plan.hpp"
 #include "internal.hpp"
 #include "modap.h"
+#include "readback.hpp"
 
 using namespace modap;
 using namespace modap_host;
@@ -98,7 +100,6 @@ struct modap_batch {
     int grid = 0;
 
     int32_t *queue = nullptr;
-    int *d_count = nullptr;
     // shared by the systems (their calls are ordered on the batch's stream)
     int *claim = nullptr;                  // row claims of a device-side replacement (zero between calls)
     size_t claim_cap = 0;
@@ -112,13 +113,12 @@ struct modap_batch {
     double *cert_dmax = nullptr, *cert_binf = nullptr, *cert_drift = nullptr;
     Totals *cert_tot = nullptr;
     size_t cert_m = 0, cert_part_cap = 0, cert_n = 0;
-    int *h_count = nullptr;               // pinned [2]
+    modap_host::Readback rb;              // results read back by the host (see readback.hpp)
     unsigned long long *bad = nullptr;
     int *flag = nullptr;
     void *stage = nullptr;
     size_t stage_bytes = 0;
     std::vector<hipEvent_t> events;
-    hipEvent_t sync_ev[2] = {nullptr, nullptr};
 };
 
 namespace {
@@ -384,8 +384,8 @@ modap_status enqueue_begin(modap_batch *c, int64_t max_steps) {
     return launch(c, prime_fn(c->dt), nsys, 256, a, nullptr, nullptr);
 }
 
-modap_status enqueue_iteration(modap_batch *c, const modap_params *p, int track, int64_t i, size_t *ev_used,
-                               double *bytes) {
+modap_status enqueue_iteration(modap_batch *c, const modap_params *p, int track, int64_t i, uint64_t *progress,
+                               size_t *ev_used, double *bytes) {
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
     if (p->profile > 0 && i % p->profile == 0) {
         for (int k = 0; k < 4; ++k) {
@@ -400,7 +400,9 @@ modap_status enqueue_iteration(modap_batch *c, const modap_params *p, int track,
     a.dp = decide_of(p, track);
     modap_status st;
     if ((st = launch(c, sweep_fn(c->dt), c->grid, 256, a, ev[0], ev[1]))) return st;
-    if ((st = launch(c, reduce_fn(c->dt), (int)c->h_cols.size(), 256, a, ev[2], ev[3], c->d_cols, 0, true)))
+    a.progress = progress;
+    if ((st = launch(c, reduce_fn(c->dt), (int)c->h_cols.size() + (progress ? 1 : 0), 256, a, ev[2], ev[3], c->d_cols, 0,
+                     true)))
         return st;
     c->jn += 1;
     *bytes += c->bytes_per_iter;
@@ -431,15 +433,30 @@ modap_status profile_totals(modap_batch *c, size_t ev_used, modap_batch_stats *o
     return MODAP_OK;
 }
 
-modap_status count_running_now(modap_batch *c, int slot_index, int *out) {
-    BatchArgs a = batch_args(c);
-    hipLaunchKernelGGL(count_running, dim3(1), dim3(256), 0, c->stream, a, slot_index, c->d_count);
-    LAUNCH_TRY(c, "count_running launch");
-    HIP_TRY(c, hipMemcpyAsync(out, c->d_count, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+// As for a single system (host.hip).
+modap_status poll_pause(modap_batch *c, uint32_t turn) {
+    _mm_pause();
+    if ((turn & 0x3fff) == 0) {
+        const hipError_t e = hipStreamQuery(c->stream);
+        if (e != hipSuccess && e != hipErrorNotReady) return hip_fail(c, e, "hipStreamQuery");
+        (void)hipGetLastError();
+        std::this_thread::yield();
+    }
     return MODAP_OK;
 }
 
 int last_slot(const modap_batch *c) { return (int)((c->jn - 1) & 1); }
+
+// Wait for everything queued and count the systems that still run.
+modap_status count_running_now(modap_batch *c, int64_t *out) {
+    const uint32_t seq = ++c->rb.seq;
+    hipLaunchKernelGGL(publish_running, dim3(1), dim3(256), 0, c->stream, batch_args(c), last_slot(c), c->rb.dev,
+                       c->rb.arrived, seq);
+    LAUNCH_TRY(c, "publish_running launch");
+    HIP_TRY(c, c->rb.wait(c->stream));
+    *out = c->rb.view->running;
+    return MODAP_OK;
+}
 
 // Scratch of the FP64 certificate for a system of m rows and padded length
 // ldA (row bands of at least 256 rows, at most 128 bands).
@@ -583,11 +600,9 @@ modap_status modap_batch_create(int device, void *hip_stream, modap_dtype storag
     hipDeviceProp_t prop;
     bool ok = hipGetDeviceProperties(&prop, device) == hipSuccess;
     if (ok) c->cu_count = prop.multiProcessorCount;
-    ok = ok && hipMalloc(&c->queue, sizeof(int32_t)) == hipSuccess && hipMalloc(&c->d_count, sizeof(int)) == hipSuccess &&
+    ok = ok && hipMalloc(&c->queue, sizeof(int32_t)) == hipSuccess &&
          hipMalloc(&c->bad, sizeof(unsigned long long)) == hipSuccess && hipMalloc(&c->flag, sizeof(int)) == hipSuccess &&
-         hipHostMalloc(&c->h_count, 2 * sizeof(int)) == hipSuccess &&
-         hipEventCreateWithFlags(&c->sync_ev[0], hipEventDisableTiming) == hipSuccess &&
-         hipEventCreateWithFlags(&c->sync_ev[1], hipEventDisableTiming) == hipSuccess;
+         c->rb.create() == hipSuccess;
     if (!ok) {
         modap_batch_destroy(c);
         return MODAP_E_DEVICE;
@@ -610,7 +625,6 @@ void modap_batch_destroy(modap_batch *c) {
     free_dev(c->dmax_part);
     free_dev(c->binf_part);
     free_dev(c->queue);
-    free_dev(c->d_count);
     free_dev(c->claim);
     free_dev(c->rhs);
     free_dev(c->d_states);
@@ -626,10 +640,8 @@ void modap_batch_destroy(modap_batch *c) {
     free_dev(c->bad);
     free_dev(c->flag);
     free_dev(c->stage);
-    if (c->h_count) (void)hipHostFree(c->h_count);
+    c->rb.destroy();
     for (hipEvent_t e : c->events) (void)hipEventDestroy(e);
-    for (hipEvent_t e : c->sync_ev)
-        if (e) (void)hipEventDestroy(e);
     delete c;
 }
 
@@ -844,15 +856,16 @@ modap_status modap_batch_iterate(modap_batch *c, const modap_params *p, int64_t 
     size_t ev = 0;
     double bytes = 0.0;
     for (int64_t i = 0; i < k; ++i)
-        if ((st = enqueue_iteration(c, p, track, i, &ev, &bytes))) return st;
+        if ((st = enqueue_iteration(c, p, track, i, nullptr, &ev, &bytes))) return st;
     if (k > 0 && (st = enqueue_settle(c, p, track))) return st;
     if (!out) return MODAP_OK;
     if (k > 0 && p->certify && (st = certify_stopped(c, p, nullptr))) return st;
-    if ((st = count_running_now(c, last_slot(c), &c->h_count[0]))) return st;
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    int64_t running = 0;
+    if ((st = count_running_now(c, &running))) return st;
+    if (p->profile) HIP_TRY(c, hipStreamSynchronize(c->stream));   // the events too
     *out = modap_batch_stats{};
     out->iters = k;
-    out->running = c->h_count[0];
+    out->running = running;
     out->systems = (int64_t)c->h_sys.size();
     out->seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     out->hbm_bytes = bytes;
@@ -879,25 +892,31 @@ modap_status modap_batch_solve(modap_batch *c, const modap_params *p, modap_batc
     // Passes of queued iterations until no system runs; stops that the FP64
     // certificate does not confirm have taken a step instead, and the next
     // pass goes on from there (the step limits are the devices').
+    const int64_t ahead = 10.0 + c->bytes_per_iter / 6e6 > 100.0 ? 2 : 4;   // as for a single system's solve
+    int64_t running = 0;
     for (;;) {
-        int64_t queued = 0, chunk = 1;
-        int slot = 0, pending = -1;
-        bool done = false;
-        while (queued < total && !done) {
-            const int64_t cnt = std::min(chunk, total - queued);
-            for (int64_t i = 0; i < cnt; ++i)
-                if ((st = enqueue_iteration(c, p, 0, queued + i, &ev, &bytes))) return st;
-            queued += cnt;
-            // the newest settled states: the checks before the last queued sweep
-            if ((st = count_running_now(c, (int)((c->jn - 2) & 1), &c->h_count[slot]))) return st;
-            HIP_TRY(c, hipEventRecord(c->sync_ev[slot], c->stream));
-            if (pending >= 0) {
-                HIP_TRY(c, hipEventSynchronize(c->sync_ev[pending]));
-                if (c->h_count[pending] == 0) done = true;
+        // Each reduction tells the host how many systems run on after the
+        // previous check; the host keeps a few iterations queued beyond that.
+        const int64_t first = c->jn;
+        int64_t queued = 0, settled = 0;
+        uint32_t idle = 0;
+        volatile uint64_t *word = &c->rb.view->progress;
+        *word = 0;   // (nothing that writes it is queued)
+        while (queued < total) {
+            const uint64_t w = *word;
+            if (w != 0 && (int64_t)((uint32_t)(w >> 32) - (uint32_t)(first + 1)) > 0) {
+                // check j - 1 of this pass is settled (the first reduction's word speaks of the one before it)
+                if ((uint32_t)w == 0) break;
+                const int64_t now_settled = (int64_t)((uint32_t)(w >> 32) - (uint32_t)(first + 1));
+                if (now_settled != settled) idle = 0;
+                settled = now_settled;
             }
-            pending = slot;
-            slot ^= 1;
-            chunk = std::min<int64_t>(chunk * 2, 64);
+            if (queued - settled >= ahead) {
+                if ((st = poll_pause(c, ++idle))) return st;
+                continue;
+            }
+            if ((st = enqueue_iteration(c, p, 0, queued, &c->rb.dev->progress, &ev, &bytes))) return st;
+            ++queued;
         }
         queued_all += queued;
         if ((st = enqueue_settle(c, p, 0))) return st;
@@ -905,16 +924,15 @@ modap_status modap_batch_solve(modap_batch *c, const modap_params *p, modap_batc
         int certified = 0;
         if ((st = certify_stopped(c, p, &certified))) return st;
         if (certified == 0) break;
-        if ((st = count_running_now(c, last_slot(c), &c->h_count[0]))) return st;
-        HIP_TRY(c, hipStreamSynchronize(c->stream));
-        if (c->h_count[0] == 0) break;
+        if ((st = count_running_now(c, &running))) return st;
+        if (running == 0) break;
     }
-    if ((st = count_running_now(c, last_slot(c), &c->h_count[0]))) return st;
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    if ((st = count_running_now(c, &running))) return st;
+    if (p->profile) HIP_TRY(c, hipStreamSynchronize(c->stream));   // the events too
     if (out) {
         *out = modap_batch_stats{};
         out->iters = queued_all;
-        out->running = c->h_count[0];
+        out->running = running;
         out->systems = (int64_t)c->h_sys.size();
         out->seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
         out->hbm_bytes = bytes;
@@ -931,17 +949,38 @@ modap_status modap_batch_query(modap_batch *c, int64_t id, double *x, double *b,
     DeviceGuard g(c->device);
     modap_status st;
     const int sl = last_slot(c);
-    if (x && (st = b_from_device(c, x, s->x, sizeof(double) * s->n, on_dev))) return st;
+    // the right-hand side is the data as the caller sees them, in FP64; nothing is committed
+    double *rhs = b;
     if (b) {
-        // the data as the caller sees them, in FP64, without committing anything
-        if ((st = ensure_buf(c, c->rhs, c->rhs_cap, (size_t)s->m))) return st;
+        if (!on_dev) {
+            if ((st = ensure_buf(c, c->rhs, c->rhs_cap, (size_t)s->m))) return st;
+            rhs = c->rhs;
+        }
         HIP_TRY(c, aux_rhs_exact(c->dt, s->A, s->ldA, s->m, s->n, s->ctl, sl, s->bref, s->wsum, s->vpend,
-                                 s->T > 0 ? s->V : nullptr, s->ldA, c->rhs, c->stream));
-        if ((st = b_from_device(c, b, c->rhs, sizeof(double) * s->m, on_dev))) return st;
+                                 s->T > 0 ? s->V : nullptr, s->ldA, rhs, c->stream));
     }
-    State k;
-    HIP_TRY(c, hipMemcpyAsync(&k, &s->ctl->st[sl], sizeof(State), hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    PublishArgs pa{};
+    pa.st = &s->ctl->st[sl];
+    const int64_t nx = x ? s->n : 0, nb = b ? s->m : 0;
+    const bool staged = !on_dev && nx + nb <= Readback::kMaxStaged;
+    if (staged) {
+        HIP_TRY(c, c->rb.reserve(nx + nb));
+        pa.src[0] = s->x;
+        pa.src[1] = rhs;
+        pa.dst[0] = c->rb.buf_dev;
+        pa.dst[1] = c->rb.buf_dev + nx;
+        pa.count[0] = nx;
+        pa.count[1] = nb;
+    } else {
+        if (x && (st = b_from_device(c, x, s->x, sizeof(double) * s->n, on_dev))) return st;
+        if (b && !on_dev && (st = b_from_device(c, b, rhs, sizeof(double) * s->m, 0))) return st;
+    }
+    HIP_TRY(c, c->rb.run(pa, c->stream));
+    if (staged) {
+        if (x) std::memcpy(x, c->rb.buf, sizeof(double) * (size_t)nx);
+        if (b) std::memcpy(b, c->rb.buf + nx, sizeof(double) * (size_t)nb);
+    }
+    const State k = c->rb.view->st;
     if (out) {
         *out = modap_stats{};
         out->iters = k.steps;

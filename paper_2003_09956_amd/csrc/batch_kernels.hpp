@@ -27,6 +27,7 @@
 #pragma once
 
 #include "modap_device.hpp"
+#include "readback.hpp"
 #include "sweep_wide.hpp"
 
 namespace modap {
@@ -77,6 +78,7 @@ struct BatchArgs {
     Decide dp;
     int32_t check_status;     // skip systems whose state is not ST_RUNNING
     int32_t write_b;          // store the translated b (0: a stateless sweep, e.g. for timing)
+    uint64_t *progress;       // host memory or null: the reduction tells (j << 32) | systems that still run
 };
 
 constexpr int kBatchWaves = 4;  // wavefronts per workgroup of sweep_batch
@@ -258,7 +260,7 @@ __device__ void batch_item(const BatchArgs &a, const BatchSys &Sref, int64_t k,
     load_row(bufA, bA, nA, 0);
     load_row(bufB, bB, nB, 1);
 
-    Pending pd{S.ctl, a.j, S.tot, S.ynp, S.R, a.decide, a.dp};
+    Pending pd{S.ctl, a.j, S.tot, S.ynp, S.R, a.decide, a.dp, nullptr};
     const State st = sweep_state(pd, lane, band == 0 && tid == 0);
     if (a.check_status && st.status != ST_RUNNING) return;
     const bool apply_v = st.vpend_valid || st.v_idx >= 0;
@@ -405,7 +407,7 @@ __device__ void batch_item_short(const BatchArgs &a, const BatchSys &Sref, int64
     load_rows(bufA, bA, nA, 0);
     load_rows(bufB, bB, nB, 1);
 
-    Pending pd{S.ctl, a.j, S.tot, S.ynp, S.R, a.decide, a.dp};
+    Pending pd{S.ctl, a.j, S.tot, S.ynp, S.R, a.decide, a.dp, nullptr};
     const State st = sweep_state(pd, lane, band == 0 && tid == 0);
     if (a.check_status && st.status != ST_RUNNING) return;
     const bool apply_v = st.vpend_valid || st.v_idx >= 0;
@@ -559,6 +561,18 @@ __global__ __launch_bounds__(256) void sweep_batch(const BatchArgs a) {
     }
 }
 
+// Number of systems whose state in slot sl is ST_RUNNING (a whole workgroup of
+// 256; thread 0 holds the result).
+__device__ __forceinline__ int running_systems(const BatchArgs &a, int sl) {
+    int cnt = 0;
+    for (int i = threadIdx.x; i < a.nsys; i += 256) cnt += a.sys[i].ctl->st[sl].status == ST_RUNNING;
+    cnt = wave_sum(cnt);
+    __shared__ int w[4];
+    if ((threadIdx.x & 63) == 0) w[threadIdx.x >> 6] = cnt;
+    __syncthreads();
+    return w[0] + w[1] + w[2] + w[3];
+}
+
 // Column sums of a system's item partials (item order, FP64), the previous
 // step made permanent in x, and the next sweep's working vectors.  One
 // workgroup per 64-column block; block 0 of a system also forms its totals.
@@ -571,6 +585,16 @@ __global__ __launch_bounds__(256) void sweep_batch(const BatchArgs a) {
 template <typename Acc>
 __global__ __launch_bounds__(256) void reduce_batch(const BatchArgs a, const BatchCol *cols) {
     if (blockIdx.x == 0 && threadIdx.x == 0) *a.queue = 0;
+    // A solve launches one workgroup more: it tells the host, which polls the
+    // word, how many systems run on after check j - 1 (settled by this
+    // iteration's sweep), so no counting kernel or copy follows.
+    if (a.progress && blockIdx.x == gridDim.x - 1) {
+        const int cnt = running_systems(a, slot_of(a.j - 1));
+        if (threadIdx.x == 0)
+            __hip_atomic_store(a.progress, ((uint64_t)(a.j + 1) << 32) | (uint32_t)cnt, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
+        return;
+    }
     const BatchCol cb = cols[blockIdx.x];
     const BatchSys S = a.sys[cb.sys];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -709,15 +733,13 @@ __global__ void gather_states(const BatchArgs a, int sl, int2 *out) {
     out[i] = make_int2(s.status, s.certified);
 }
 
-// Number of systems whose state in slot sl is ST_RUNNING (one workgroup).
-__global__ __launch_bounds__(256) void count_running(const BatchArgs a, int sl, int *out) {
-    int cnt = 0;
-    for (int i = threadIdx.x; i < a.nsys; i += 256) cnt += a.sys[i].ctl->st[sl].status == ST_RUNNING;
-    cnt = wave_sum(cnt);
-    __shared__ int w[4];
-    if ((threadIdx.x & 63) == 0) w[threadIdx.x >> 6] = cnt;
-    __syncthreads();
-    if (threadIdx.x == 0) *out = w[0] + w[1] + w[2] + w[3];
+// Number of systems whose state in slot sl is ST_RUNNING, to the host (one
+// workgroup).
+__global__ __launch_bounds__(256) void publish_running(const BatchArgs a, int sl, HostView *view, uint32_t *arrived,
+                                                       uint32_t seq) {
+    const int cnt = running_systems(a, sl);
+    if (threadIdx.x == 0) view->running = (uint32_t)cnt;
+    announce(view, arrived, seq, 1);
 }
 
 }  // namespace modap

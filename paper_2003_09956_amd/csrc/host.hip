@@ -21,6 +21,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <string>
+#include <thread>
 #include <unordered_set>
 #include <vector>
 
@@ -31,12 +32,14 @@
 #include "trace.hpp"
 #include "internal.hpp"
 #include "modap.h"
+#include "readback.hpp"
 #include "resident.hpp"
 #include "sweep_split.hpp"
 #include "modap_device.hpp"
 #include "sweep_table.hpp"
 
 using namespace modap;
+using modap_host::Readback;
 
 struct modap_ctx {
     int device = 0;
@@ -86,7 +89,7 @@ struct modap_ctx {
     void *work_eval = nullptr;
 
     Ctrl *ctl = nullptr;
-    State *hst = nullptr;        // pinned [2]
+    Readback rb;                 // results read back by the host (see readback.hpp)
     double *x_eval = nullptr, *y_eval = nullptr, *r_eval = nullptr;
     unsigned long long *bad = nullptr;
     int *flag = nullptr;
@@ -113,7 +116,6 @@ struct modap_ctx {
     int64_t cert_rows_per_band = 0;
 
     std::vector<hipEvent_t> events;
-    hipEvent_t sync_ev[2] = {nullptr, nullptr};
 };
 
 namespace {
@@ -528,8 +530,8 @@ modap_status enqueue_prime(modap_ctx *c, void *work, const double *x) {
 // check, except in the first iteration of a call) at the current x on the
 // current data, then the reduction of y (which makes the previous step
 // permanent in x and writes the next sweep's working vectors).
-modap_status enqueue_iteration(modap_ctx *c, const modap_params *p, int track, int64_t i, size_t *ev_used,
-                               double *bytes) {
+modap_status enqueue_iteration(modap_ctx *c, const modap_params *p, int track, int64_t i, uint64_t *progress,
+                               size_t *ev_used, double *bytes) {
     const bool hv = translation_possible(c);
     const int64_t j = c->jn;
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -542,6 +544,7 @@ modap_status enqueue_iteration(modap_ctx *c, const modap_params *p, int track, i
     a.pd.j = j;
     a.pd.decide = i > 0;   // the first sweep of a call runs under the committed state
     a.pd.dp = decide_params(p, track);
+    a.pd.progress = progress;
     a.check_status = 1;
     modap_status st;
     if ((st = launch_sweep(c, a, hv, ev[0], ev[1]))) return st;
@@ -572,12 +575,36 @@ modap_status enqueue_settle(modap_ctx *c, const modap_params *p, int track) {
     return MODAP_OK;
 }
 
-modap_status read_state(modap_ctx *c, State *out) {
-    uint32_t bf[2] = {0, 0};
-    HIP_TRY(c, hipMemcpyAsync(out, &c->ctl->st[last_slot(c)], sizeof(State), hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(bf, &c->ctl->barrier, sizeof bf, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    if (bf[1])
+// Wait for everything queued and read the committed state (and, for a query,
+// up to two vectors of doubles to host memory).
+modap_status read_back(modap_ctx *c, State *out, const double *src0 = nullptr, double *dst0 = nullptr, int64_t n0 = 0,
+                       const double *src1 = nullptr, double *dst1 = nullptr, int64_t n1 = 0) {
+    PublishArgs p{};
+    p.st = &c->ctl->st[last_slot(c)];
+    p.fault = &c->ctl->fault;
+    const double *src[2] = {src0, src1};
+    double *dst[2] = {dst0, dst1};
+    const int64_t cnt[2] = {n0, n1};
+    const bool staged = n0 + n1 <= Readback::kMaxStaged;
+    if (staged) {
+        HIP_TRY(c, c->rb.reserve(n0 + n1));
+        p.src[0] = src0;
+        p.src[1] = src1;
+        p.dst[0] = c->rb.buf_dev;
+        p.dst[1] = c->rb.buf_dev + n0;
+        p.count[0] = n0;
+        p.count[1] = n1;
+    } else {
+        for (int k = 0; k < 2; ++k)
+            if (cnt[k]) HIP_TRY(c, hipMemcpyAsync(dst[k], src[k], sizeof(double) * (size_t)cnt[k], hipMemcpyDeviceToHost, c->stream));
+    }
+    HIP_TRY(c, c->rb.run(p, c->stream));
+    if (staged) {
+        if (n0) std::memcpy(dst0, c->rb.buf, sizeof(double) * (size_t)n0);
+        if (n1) std::memcpy(dst1, c->rb.buf + n0, sizeof(double) * (size_t)n1);
+    }
+    *out = c->rb.view->st;
+    if (c->rb.view->fault)
         return fail(c, MODAP_E_DEVICE,
                     "a resident launch gave up waiting at a grid barrier; the context's data are void until set_system");
     return MODAP_OK;
@@ -730,7 +757,8 @@ bool use_resident(const modap_ctx *c, const modap_params *p) {
 
 // Queue K resident iterations from the committed state (the launch settles
 // every check it makes, so no stage kernel follows).
-modap_status launch_resident(modap_ctx *c, const modap_params *p, int track, int64_t K, double *bytes) {
+modap_status launch_resident(modap_ctx *c, const modap_params *p, int track, int64_t K, uint64_t *progress,
+                             double *bytes) {
     const bool hv = translation_possible(c);
     // (the arrival counters were cleared by the last workgroup of the previous
     // launch, or by set_system; the fault flag stays raised)
@@ -758,11 +786,36 @@ modap_status launch_resident(modap_ctx *c, const modap_params *p, int track, int
     r.h_part = c->res_h;
     r.dmax_part = c->res_dmax;
     r.binf_part = c->res_binf;
+    r.progress = progress;
     r.timeout_ticks = kResidentTimeoutTicks;
     if (const char *e = std::getenv("MODAP_RESIDENT_TIMEOUT_TICKS")) r.timeout_ticks = std::atoll(e);   // tests
     HIP_TRY(c, aux_resident_launch(c->dt, r, c->res_grid, c->res_lds, c->stream));
     c->jn += K;
     *bytes += (double)K * sweep_bytes(c, hv);
+    return MODAP_OK;
+}
+
+// Iterations a solve keeps queued beyond the last decision the host has seen:
+// enough to cover the decision's way to the host and the next launch's to the
+// device (about 10 us; an iteration takes about 10 us plus its bytes at 6
+// TB/s), few enough that a stop leaves little queued in vain.  Queued in
+// doubling chunks instead, a solve of 16 steps on a 128 MB system launched 126
+// iterations and took 2.4 ms.
+int64_t solve_ahead(const modap_ctx *c) {
+    const double us = 10.0 + sweep_bytes(c, true) / 6e6;
+    return us > 100.0 ? 2 : 4;
+}
+
+// One turn of a host loop that polls: a pause, and now and then a look at the
+// stream for an error, and a yield once the wait has become long.
+modap_status poll_pause(modap_ctx *c, uint32_t turn) {
+    _mm_pause();
+    if ((turn & 0x3fff) == 0) {
+        const hipError_t e = hipStreamQuery(c->stream);
+        if (e != hipSuccess && e != hipErrorNotReady) return hip_fail(c, e, "hipStreamQuery");
+        (void)hipGetLastError();
+        std::this_thread::yield();
+    }
     return MODAP_OK;
 }
 
@@ -909,9 +962,7 @@ modap_status modap_create(int device, void *hip_stream, modap_ctx **out) {
     bool ok = hipMalloc(&c->ctl, sizeof(Ctrl)) == hipSuccess && hipMalloc(&c->tot, sizeof(Totals)) == hipSuccess &&
               hipMalloc(&c->bad, sizeof(unsigned long long)) == hipSuccess &&
               hipMalloc(&c->flag, sizeof(int)) == hipSuccess &&
-              hipHostMalloc(&c->hst, 2 * sizeof(State), hipHostMallocDefault) == hipSuccess &&
-              hipEventCreateWithFlags(&c->sync_ev[0], hipEventDisableTiming) == hipSuccess &&
-              hipEventCreateWithFlags(&c->sync_ev[1], hipEventDisableTiming) == hipSuccess;
+              c->rb.create() == hipSuccess;
     if (!ok) {
         modap_destroy(c);
         return MODAP_E_NOMEM;
@@ -942,10 +993,8 @@ void modap_destroy(modap_ctx *c) {
     free_dev(c->bad);
     free_dev(c->flag);
     free_dev(c->stage);
-    if (c->hst) (void)hipHostFree(c->hst);
+    c->rb.destroy();
     for (hipEvent_t e : c->events) (void)hipEventDestroy(e);
-    for (hipEvent_t e : c->sync_ev)
-        if (e) (void)hipEventDestroy(e);
     delete c;
 }
 
@@ -1187,20 +1236,26 @@ modap_status modap_iterate(modap_ctx *c, const modap_params *p, int64_t k, modap
         // one launch of many iterations (each launch settles its own checks)
         for (int64_t done = 0; done < k;) {
             const int64_t K = std::min<int64_t>(k - done, int64_t(1) << 20);
-            if ((st = launch_resident(c, p, track, K, &bytes))) return st;
+            if ((st = launch_resident(c, p, track, K, nullptr, &bytes))) return st;
             done += K;
         }
     } else {
         if ((st = enqueue_prime(c, c->work, c->x))) return st;
         if ((st = reserve_events(c, k, p->profile))) return st;
         for (int64_t i = 0; i < k; ++i)
-            if ((st = enqueue_iteration(c, p, track, i, &ev, &bytes))) return st;
+            if ((st = enqueue_iteration(c, p, track, i, nullptr, &ev, &bytes))) return st;
         if (k > 0 && (st = enqueue_settle(c, p, track))) return st;
     }
-    if (k > 0 && p->certify && (st = enqueue_certify(c, p))) return st;
-    if (!out) return MODAP_OK;
+    // (a tracked iteration never stops: there is nothing to certify)
+    const bool certify = k > 0 && p->certify && !track;
+    if (!out) return certify ? enqueue_certify(c, p) : MODAP_OK;
     State kc;
-    if ((st = read_state(c, &kc))) return st;
+    if ((st = read_back(c, &kc))) return st;
+    if (certify && kc.status == ST_CONVERGED && !kc.certified) {
+        if ((st = enqueue_certify(c, p))) return st;
+        if ((st = read_back(c, &kc))) return st;
+    }
+    if (p->profile) HIP_TRY(c, hipStreamSynchronize(c->stream));   // the events too
     *out = modap_stats{};
     fill_stats(out, kc);
     out->seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
@@ -1231,46 +1286,54 @@ modap_status modap_solve(modap_ctx *c, const modap_params *p, modap_stats *out) 
     // Passes of queued iterations until the device stops; a stop at
     // eps-feasibility that the FP64 certificate does not confirm has taken a
     // step instead, and the next pass goes on from there.  The step limit is
-    // the device's, so a pass may queue more iterations than remain.  The host
-    // reads the state of the chunk before the newest one, so the device never
-    // waits for it.
+    // the device's, so a pass may queue more iterations than remain.
+    const int64_t ahead = resident ? 0 : solve_ahead(c);
     for (;;) {
-        int64_t queued = 0, chunk = resident ? 16 : 1;
-        int slot = 0, pending = -1;
-        bool done = false;
-        while (queued < total && !done) {
-            TraceRange trace_chunk("modap_solve chunk");
-            const int64_t cnt = std::min(chunk, total - queued);
+        // Each sweep tells the host the decision it takes on the previous
+        // check (a resident launch its last one).  The host keeps a few
+        // iterations (two launches) queued beyond the last decision it has
+        // seen, so the device never waits for it and few are queued in vain.
+        const int64_t first = c->jn;
+        int64_t queued = 0, chunk = 16, settled = 0;
+        int64_t prev_end = first - 1, last_end = first - 1;   // last checks of the two newest resident launches
+        uint32_t idle = 0;
+        *static_cast<volatile uint64_t *>(&c->rb.view->progress) = 0;   // (nothing that writes it is queued)
+        while (queued < total) {
+            const uint64_t w = *static_cast<volatile uint64_t *>(&c->rb.view->progress);
+            if (w != 0) {
+                if ((w & 0xff) != ST_RUNNING) break;
+                const int64_t now_settled = (int64_t)(w >> 8) - first;
+                if (now_settled != settled) idle = 0;
+                settled = now_settled;
+            }
+            const bool room = resident ? first - 1 + settled >= prev_end : queued - settled < ahead;
+            if (!room) {
+                if ((st = poll_pause(c, ++idle))) return st;
+                continue;
+            }
             if (resident) {
-                if ((st = launch_resident(c, p, 0, cnt, &bytes))) return st;
+                const int64_t cnt = std::min(chunk, total - queued);
+                if ((st = launch_resident(c, p, 0, cnt, &c->rb.dev->progress, &bytes))) return st;
+                queued += cnt;
+                prev_end = last_end;
+                last_end = c->jn - 1;
+                chunk = std::min<int64_t>(chunk * 2, 1024);
             } else {
-                for (int64_t i = 0; i < cnt; ++i)
-                    if ((st = enqueue_iteration(c, p, 0, queued + i, &ev, &bytes))) return st;
+                if ((st = enqueue_iteration(c, p, 0, queued, &c->rb.dev->progress, &ev, &bytes))) return st;
+                ++queued;
             }
-            queued += cnt;
-            // the newest settled state: the check before the last queued sweep
-            // (two-kernel path), or the last check of the launch (resident path)
-            HIP_TRY(c, hipMemcpyAsync(&c->hst[slot], &c->ctl->st[slot_of(c->jn - (resident ? 1 : 2))], sizeof(State),
-                                      hipMemcpyDeviceToHost, c->stream));
-            HIP_TRY(c, hipEventRecord(c->sync_ev[slot], c->stream));
-            if (pending >= 0) {
-                HIP_TRY(c, hipEventSynchronize(c->sync_ev[pending]));
-                if (c->hst[pending].status != ST_RUNNING) done = true;
-            }
-            pending = slot;
-            slot ^= 1;
-            chunk = std::min<int64_t>(chunk * 2, resident ? 1024 : 64);
         }
         if (!resident && (st = enqueue_settle(c, p, 0))) return st;
-        if ((st = read_state(c, &kc))) return st;
+        if ((st = read_back(c, &kc))) return st;
         observed = std::chrono::steady_clock::now();
         if (!(p->certify && kc.status == ST_CONVERGED && !kc.certified)) break;
         if ((st = enqueue_certify(c, p))) return st;
-        if ((st = read_state(c, &kc))) return st;
+        if ((st = read_back(c, &kc))) return st;
         bytes += sweep_bytes(c, false);
         observed = std::chrono::steady_clock::now();
         if (kc.status != ST_RUNNING) break;
     }
+    if (p->profile) HIP_TRY(c, hipStreamSynchronize(c->stream));   // the events too
     if (out) {
         *out = modap_stats{};
         fill_stats(out, kc);
@@ -1291,25 +1354,48 @@ modap_status modap_eval_sweep(modap_ctx *c, const double *x, double *r, double *
     if (st) return st;
     if (!x || !y) return fail(c, MODAP_E_INVAL, "x and y are required");
     DeviceGuard g(c->device);
-    if ((st = to_device(c, c->x_eval, x, sizeof(double) * c->n, on_dev))) return st;
-    if ((st = enqueue_prime(c, c->work_eval, c->x_eval))) return st;
+    // The point is read, and device results are written, where the caller
+    // holds them; host ones pass through the staging memory.
+    const int64_t nr = r ? c->m : 0;
+    const bool staged = !on_dev && c->n + nr <= Readback::kMaxStaged;
+    if (on_dev) {
+        if ((st = enqueue_prime(c, c->work_eval, x))) return st;
+    } else {
+        if ((st = to_device(c, c->x_eval, x, sizeof(double) * c->n, 0))) return st;
+        if ((st = enqueue_prime(c, c->work_eval, c->x_eval))) return st;
+    }
     const bool hv = translation_possible(c);
     SweepArgs a = sweep_args(c);
     a.b_out = nullptr;
     a.work = c->work_eval;
     a.check_status = 0;
-    a.r_out = r ? c->r_eval : nullptr;
+    a.r_out = !r ? nullptr : on_dev ? r : c->r_eval;
     if ((st = launch_sweep(c, a, hv, nullptr, nullptr))) return st;
     ReduceArgs ra = reduce_args(c);
-    ra.y = c->y_eval;
+    ra.y = on_dev ? y : c->y_eval;
     ra.ctl = nullptr;
     ra.iterate = 0;
     if ((st = launch_reduce(c, ra))) return st;
-    Totals to;
-    HIP_TRY(c, hipMemcpyAsync(&to, c->tot, sizeof to, hipMemcpyDeviceToHost, c->stream));
-    if ((st = from_device(c, y, c->y_eval, sizeof(double) * c->n, on_dev))) return st;
-    if (r && (st = from_device(c, r, c->r_eval, sizeof(double) * c->m, on_dev))) return st;
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    PublishArgs pa{};
+    pa.tot = c->tot;
+    if (staged) {
+        HIP_TRY(c, c->rb.reserve(c->n + nr));
+        pa.src[0] = c->y_eval;
+        pa.src[1] = c->r_eval;
+        pa.dst[0] = c->rb.buf_dev;
+        pa.dst[1] = c->rb.buf_dev + c->n;
+        pa.count[0] = c->n;
+        pa.count[1] = nr;
+    } else if (!on_dev) {
+        if ((st = from_device(c, y, c->y_eval, sizeof(double) * c->n, 0))) return st;
+        if (r && (st = from_device(c, r, c->r_eval, sizeof(double) * c->m, 0))) return st;
+    }
+    HIP_TRY(c, c->rb.run(pa, c->stream));
+    if (staged) {
+        std::memcpy(y, c->rb.buf, sizeof(double) * (size_t)c->n);
+        if (r) std::memcpy(r, c->rb.buf + c->n, sizeof(double) * (size_t)c->m);
+    }
+    const Totals to = c->rb.view->tot;
     if (h) *h = to.h;
     if (max_viol) *max_viol = to.dmax;
     return MODAP_OK;
@@ -1320,16 +1406,20 @@ modap_status modap_query(modap_ctx *c, double *x, double *b, modap_stats *out, i
     modap_status st = check_ctx(c, true);
     if (st) return st;
     DeviceGuard g(c->device);
-    if (x && (st = from_device(c, x, c->x, sizeof(double) * c->n, on_dev))) return st;
-    if (b) {
-        // the data as the caller sees them, every translation applied, in FP64;
-        // nothing is committed, so reading b does not change the iteration
+    // the right-hand side is the data as the caller sees them, every
+    // translation applied, in FP64; nothing is committed, so reading b does
+    // not change the iteration
+    if (b)
         HIP_TRY(c, aux_rhs_exact(c->dt, c->A, c->ldA, c->m, c->n, c->ctl, last_slot(c), c->bref, c->wsum, c->vpend,
-                                 c->V, c->ldA, c->r_eval, c->stream));
-        if ((st = from_device(c, b, c->r_eval, sizeof(double) * c->m, on_dev))) return st;
-    }
+                                 c->V, c->ldA, on_dev ? b : c->r_eval, c->stream));
     State kc;
-    if ((st = read_state(c, &kc))) return st;
+    if (on_dev) {
+        if (x && (st = from_device(c, x, c->x, sizeof(double) * c->n, 1))) return st;
+        st = read_back(c, &kc);
+    } else {
+        st = read_back(c, &kc, c->x, x, x ? c->n : 0, c->r_eval, b, b ? c->m : 0);
+    }
+    if (st) return st;
     if (out) {
         *out = modap_stats{};
         fill_stats(out, kc);

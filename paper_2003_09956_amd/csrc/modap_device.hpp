@@ -14,6 +14,7 @@ enum : int32_t {
     ST_NUMERIC = 3,
     ST_LIMIT = 4,
     ST_BAD_ROW = 5,
+    ST_FAULT = 0xff,      // told to the host only: a resident launch gave up at a grid barrier
     ST_UNCERTIFIED = 6,   // the FP64 certificate cannot confirm eps: eps_abs lies below its rounding bound
 };
 
@@ -103,6 +104,7 @@ struct Pending {
     int32_t R;              // norm parts
     int32_t decide;         // 0: slot (j-1)&1 already holds the state this sweep runs under
     Decide dp;
+    uint64_t *progress;     // host memory or null: told each decision as (check + 1) << 8 | status
 };
 
 struct SweepArgs {
@@ -399,6 +401,11 @@ __device__ __forceinline__ State decide(const State &p, const Totals &t, double 
     return s;
 }
 
+// Tell the host, which polls the word, how far the iteration has come.
+__device__ __forceinline__ void post_progress(uint64_t *p, int64_t check, int32_t status) {
+    __hip_atomic_store(p, ((uint64_t)(check + 1) << 8) | (uint64_t)status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // The state that sweep pd.j runs under (see Pending).  Called by whole
 // wavefronts (the norm of y is summed across the wavefront); `writer` commits
 // a fresh decision.
@@ -411,7 +418,10 @@ __device__ __forceinline__ State sweep_state(const Pending &pd, int lane, bool w
     const int64_t len = load_global(&pd.ctl->sched_len);
     const double yn = ynorm_of(pd.ynp, pd.R, lane);
     const State s = decide(p, t, yn, pd.dp, limit, len);
-    if (writer) store_global(&pd.ctl->st[slot_of(pd.j - 1)], s);
+    if (writer) {
+        store_global(&pd.ctl->st[slot_of(pd.j - 1)], s);
+        if (pd.progress) post_progress(pd.progress, pd.j - 1, s.status);
+    }
     return s;
 }
 

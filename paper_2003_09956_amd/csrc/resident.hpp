@@ -58,6 +58,7 @@ struct ResidentArgs {
     int64_t *h_part;        // [2 x G]
     double *dmax_part;      // [2 x G]
     double *binf_part;      // [2 x G]
+    uint64_t *progress;     // host memory or null: told the last check and its status when the launch ends
     int64_t timeout_ticks;  // constant-clock (100 MHz) ticks a workgroup waits at the barrier
 };
 
@@ -407,7 +408,10 @@ __global__ __launch_bounds__(kResidentThreads) void resident_iterate(const Resid
             __hip_atomic_store(&a.ctl->exits, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
-    if (failed) return;
+    if (failed) {
+        if (g == 0 && tid == 0 && a.progress) post_progress(a.progress, a.j0 + a.K - 1, ST_FAULT);
+        return;
+    }
 
     // write back: the band's b; workgroup 0 the vectors and the state
     for (int i = tid; i < nr; i += NT) a.b[r0 + i] = bs[i];
@@ -426,6 +430,7 @@ __global__ __launch_bounds__(kResidentThreads) void resident_iterate(const Resid
     if (tid == 0) {
         store_global(&a.ctl->st[0], p);
         store_global(&a.ctl->st[1], p);
+        if (a.progress) post_progress(a.progress, a.j0 + a.K - 1, p.status);
     }
 }
 
