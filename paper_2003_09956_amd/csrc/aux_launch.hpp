@@ -42,7 +42,20 @@ struct ResidentArgs;
 hipError_t aux_resident_launch(int dt, const ResidentArgs &a, int grid, size_t lds, hipStream_t s);
 // Dynamic LDS of a resident workgroup holding `rows` rows of ldR elements.
 size_t resident_lds_bytes(int dt, int rows, int ldR);
-// Queue the FP64 certificate of the stop in slot a.sl (see certify.hpp); R and Gs are filled in.
-hipError_t aux_certify(int dt, CertArgs a, hipStream_t s);
+// How the FP64 certificate of one system is cut (see certify.hpp), and the
+// scratch it works in: filled into `a` by place(), whose base is 256-aligned.
+struct CertPlan {
+    int Gs, bands, tiles, R;
+    int64_t rows_per_band;
+    size_t bytes;
+    void place(CertArgs *a, void *base) const;
+};
+// `workgroups`: what the pass over A spreads over (at most one per 16 rows).
+CertPlan cert_plan(int dt, int64_t m, int64_t n, int64_t ldA, int64_t workgroups);
+// Queue the FP64 certificate of the stop in slot a.sl, or of `count` systems
+// at once (list and jobs in device memory: dot, axpy and reduce jobs in turn).
+hipError_t aux_certify(int dt, const CertArgs &a, const CertPlan &plan, hipStream_t s);
+hipError_t aux_certify_list(int dt, const CertArgs *list, int count, const CertJob *jobs, int ndot, int naxpy,
+                            int nreduce, hipStream_t s);
 
 }  // namespace modap

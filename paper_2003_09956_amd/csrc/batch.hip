@@ -105,14 +105,10 @@ struct modap_batch {
     size_t claim_cap = 0;
     double *rhs = nullptr;                 // exact right-hand side read by modap_batch_query
     size_t rhs_cap = 0;
-    int2 *d_states = nullptr;              // statuses gathered for the certificate
-    size_t states_cap = 0;
-    // FP64 certificate scratch, sized for the largest system certified so far
-    double *cert_wt = nullptr, *cert_part = nullptr, *cert_y = nullptr, *cert_ynp = nullptr;
-    int64_t *cert_h = nullptr;
-    double *cert_dmax = nullptr, *cert_binf = nullptr, *cert_drift = nullptr;
-    Totals *cert_tot = nullptr;
-    size_t cert_m = 0, cert_part_cap = 0, cert_n = 0;
+    // FP64 certificates: scratch of the systems certified together, and the
+    // list of systems and jobs
+    unsigned char *cert = nullptr, *cert_list = nullptr;
+    size_t cert_cap = 0, cert_list_cap = 0;
     modap_host::Readback rb;              // results read back by the host (see readback.hpp)
     unsigned long long *bad = nullptr;
     int *flag = nullptr;
@@ -192,6 +188,21 @@ modap_status ensure_buf(modap_batch *c, P *&p, size_t &cap, size_t count) {
     const size_t want = std::max(count, cap * 2);
     HIP_TRY(c, hipMalloc(&p, sizeof(P) * want));
     cap = want;
+    return MODAP_OK;
+}
+
+// As ensure_buf for bytes, without room to grow into; nothing is kept on failure.
+modap_status ensure_bytes(modap_batch *c, unsigned char *&p, size_t &cap, size_t bytes) {
+    if (bytes <= cap) return MODAP_OK;
+    free_dev(p);
+    cap = 0;
+    const hipError_t e = hipMalloc(&p, bytes);
+    if (e != hipSuccess) {
+        p = nullptr;
+        (void)hipGetLastError();
+        return hip_fail(c, e, "hipMalloc");
+    }
+    cap = bytes;
     return MODAP_OK;
 }
 
@@ -447,121 +458,126 @@ modap_status poll_pause(modap_batch *c, uint32_t turn) {
 
 int last_slot(const modap_batch *c) { return (int)((c->jn - 1) & 1); }
 
-// Wait for everything queued and count the systems that still run.
-modap_status count_running_now(modap_batch *c, int64_t *out) {
-    const uint32_t seq = ++c->rb.seq;
-    hipLaunchKernelGGL(publish_running, dim3(1), dim3(256), 0, c->stream, batch_args(c), last_slot(c), c->rb.dev,
-                       c->rb.arrived, seq);
-    LAUNCH_TRY(c, "publish_running launch");
-    HIP_TRY(c, c->rb.wait(c->stream));
-    *out = c->rb.view->running;
-    return MODAP_OK;
-}
-
-// Scratch of the FP64 certificate for a system of m rows and padded length
-// ldA (row bands of at least 256 rows, at most 128 bands).
-modap_status ensure_cert(modap_batch *c, int64_t m, int64_t ldA, int64_t *rpb, int *bands) {
-    *rpb = std::max<int64_t>(256, (m + 127) / 128);
-    *bands = (int)((m + *rpb - 1) / *rpb);
-    const size_t gs = (size_t)((m + 3) / 4);
-    if ((size_t)m > c->cert_m) {
-        HIP_TRY(c, hipStreamSynchronize(c->stream));
-        free_dev(c->cert_wt);
-        free_dev(c->cert_h);
-        free_dev(c->cert_dmax);
-        free_dev(c->cert_binf);
-        free_dev(c->cert_drift);
-        c->cert_m = 0;
-        HIP_TRY(c, hipMalloc(&c->cert_wt, sizeof(double) * (size_t)m));
-        HIP_TRY(c, hipMalloc(&c->cert_h, sizeof(int64_t) * gs));
-        HIP_TRY(c, hipMalloc(&c->cert_dmax, sizeof(double) * gs));
-        HIP_TRY(c, hipMalloc(&c->cert_binf, sizeof(double) * gs));
-        HIP_TRY(c, hipMalloc(&c->cert_drift, sizeof(double) * gs));
-        c->cert_m = (size_t)m;
-    }
-    if ((size_t)ldA > c->cert_n) {
-        HIP_TRY(c, hipStreamSynchronize(c->stream));
-        free_dev(c->cert_y);
-        free_dev(c->cert_ynp);
-        c->cert_n = 0;
-        HIP_TRY(c, hipMalloc(&c->cert_y, sizeof(double) * (size_t)ldA));
-        HIP_TRY(c, hipMalloc(&c->cert_ynp, sizeof(double) * (size_t)((ldA + 63) / 64)));
-        c->cert_n = (size_t)ldA;
-    }
-    const size_t pc = (size_t)*bands * (size_t)ldA;
-    if (pc > c->cert_part_cap) {
-        HIP_TRY(c, hipStreamSynchronize(c->stream));
-        free_dev(c->cert_part);
-        c->cert_part_cap = 0;
-        HIP_TRY(c, hipMalloc(&c->cert_part, sizeof(double) * pc));
-        c->cert_part_cap = pc;
-    }
-    if (!c->cert_tot) HIP_TRY(c, hipMalloc(&c->cert_tot, sizeof(Totals)));
-    return MODAP_OK;
-}
-
-// Queue the FP64 certificate of system s (a no-op on the device unless its
-// committed state is an uncertified stop).
-modap_status certify_sys(modap_batch *c, BSys &s, const modap_params *p) {
-    int64_t rpb = 0;
-    int bands = 0;
-    modap_status st;
-    if ((st = ensure_cert(c, s.m, s.ldA, &rpb, &bands))) return st;
-    CertArgs v{};
-    v.A = s.A;
-    v.ldA = s.ldA;
-    v.m = s.m;
-    v.n = s.n;
-    v.b = s.b;
-    v.bref = s.bref;
-    v.nu = s.nu;
-    v.x = s.x;
-    v.wsum = s.wsum;
-    v.V = s.T > 0 ? s.V : nullptr;
-    v.ldV = s.ldA;
-    v.work = s.work;
-    v.ctl = s.ctl;
-    v.sl = last_slot(c);
-    v.wt = c->cert_wt;
-    v.h_part = c->cert_h;
-    v.dmax_part = c->cert_dmax;
-    v.binf_part = c->cert_binf;
-    v.drift_part = c->cert_drift;
-    v.bands = bands;
-    v.rows_per_band = rpb;
-    v.part = c->cert_part;
-    v.y = c->cert_y;
-    v.ynp = c->cert_ynp;
-    v.tot = c->cert_tot;
-    v.dp = decide_of(p, 0);
-    HIP_TRY(c, aux_certify(c->dt, v, c->stream));
-    return MODAP_OK;
-}
-
-// The certificate of every system whose committed state is an uncertified
-// stop (the states are read first, so only those systems are queued).
-// Synchronises.  *count (may be NULL) receives the number certified.
-modap_status certify_stopped(modap_batch *c, const modap_params *p, int *count) {
-    if (count) *count = 0;
+// Wait for everything queued and read the state of every system (in table
+// order; valid until the next result is read back).
+modap_status read_states(modap_batch *c, const State **out) {
     const int nsys = (int)c->h_sys.size();
-    if (nsys == 0) return MODAP_OK;
-    modap_status st;
-    if ((st = ensure_buf(c, c->d_states, c->states_cap, (size_t)nsys))) return st;
-    BatchArgs a = batch_args(c);
-    hipLaunchKernelGGL(gather_states, dim3((nsys + 255) / 256), dim3(256), 0, c->stream, a, last_slot(c), c->d_states);
-    LAUNCH_TRY(c, "gather_states launch");
-    std::vector<int2> hs((size_t)nsys);
-    HIP_TRY(c, hipMemcpyAsync(hs.data(), c->d_states, sizeof(int2) * (size_t)nsys, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    int cnt = 0;
-    for (int i = 0; i < nsys; ++i) {
-        if (hs[(size_t)i].x != ST_CONVERGED || hs[(size_t)i].y != 0) continue;
-        if ((st = certify_sys(c, c->sys[(size_t)c->order[(size_t)i]], p))) return st;
-        ++cnt;
-    }
-    if (cnt) HIP_TRY(c, hipStreamSynchronize(c->stream));
-    if (count) *count = cnt;
+    constexpr int kWords = sizeof(State) / 8;
+    HIP_TRY(c, c->rb.reserve((int64_t)nsys * kWords));
+    const uint32_t seq = ++c->rb.seq;
+    hipLaunchKernelGGL(publish_states, dim3((nsys + 15) / 16), dim3(256), 0, c->stream, batch_args(c),
+                       last_slot(c), reinterpret_cast<State *>(c->rb.buf_dev), c->rb.dev, c->rb.arrived, seq);
+    LAUNCH_TRY(c, "publish_states launch");
+    HIP_TRY(c, c->rb.wait(c->stream));
+    *out = reinterpret_cast<const State *>(c->rb.buf);
     return MODAP_OK;
+}
+
+int64_t count_running(const modap_batch *c, const State *s) {
+    return std::count_if(s, s + c->h_sys.size(), [](const State &k) { return k.status == ST_RUNNING; });
+}
+
+// Queue the FP64 certificates of the given systems (each a no-op on the device
+// unless its committed state is an uncertified stop), as many together as
+// kCertScratch bytes hold.  The list and the jobs pass through the staging
+// memory; the caller waits before it is used again.
+constexpr size_t kCertScratch = size_t(256) << 20;
+
+modap_status certify_systems(modap_batch *c, const std::vector<int64_t> &ids, const modap_params *p) {
+    if (ids.empty()) return MODAP_OK;
+    // the pass over A: about eight workgroups per CU in all, shared out by size
+    double bytes = 0.0;
+    auto size_of = [&](const BSys &s) { return (double)s.m * (double)s.ldA; };
+    for (int64_t id : ids) bytes += size_of(c->sys[(size_t)id]);
+    std::vector<CertPlan> plans;
+    size_t scratch = 0, list_bytes = 0, largest = 0;
+    auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
+    for (int64_t id : ids) {
+        const BSys &s = c->sys[(size_t)id];
+        const double share = 8.0 * c->cu_count * size_of(s) / bytes;
+        plans.push_back(cert_plan(c->dt, s.m, s.n, s.ldA, std::max<int64_t>(4, (int64_t)share)));
+        const CertPlan &q = plans.back();
+        scratch += q.bytes;
+        largest = std::max(largest, q.bytes);
+        list_bytes += sizeof(CertArgs) + sizeof(CertJob) * (size_t)(q.Gs + q.bands * q.tiles + q.R);
+    }
+    const size_t want = std::min(scratch, std::max(kCertScratch, largest));
+    modap_status st;
+    if (want > c->cert_cap) {
+        HIP_TRY(c, hipStreamSynchronize(c->stream));
+        st = ensure_bytes(c, c->cert, c->cert_cap, want);
+        if (st == MODAP_E_NOMEM && want > largest) st = ensure_bytes(c, c->cert, c->cert_cap, largest);   // one at a time
+        if (st) return st;
+    }
+    // any two neighbouring groups together exceed the scratch; each group's list and jobs are aligned
+    list_bytes += 512 * (2 + 2 * scratch / std::max<size_t>(1, std::min(c->cert_cap, want)));
+    if (list_bytes > c->cert_list_cap) HIP_TRY(c, hipStreamSynchronize(c->stream));
+    if ((st = ensure_buf(c, c->cert_list, c->cert_list_cap, list_bytes))) return st;
+    HIP_TRY(c, c->rb.reserve((int64_t)(list_bytes / sizeof(double) + 1)));
+    unsigned char *host = reinterpret_cast<unsigned char *>(c->rb.buf);
+    size_t list_at = 0;
+    for (size_t first = 0; first < ids.size();) {
+        size_t end = first, used = 0;
+        std::vector<CertArgs> list;
+        std::vector<CertJob> dot, axpy, red;
+        for (; end < ids.size() && (end == first || used + plans[end].bytes <= c->cert_cap); ++end) {
+            const BSys &s = c->sys[(size_t)ids[end]];
+            const CertPlan &q = plans[end];
+            CertArgs v{};
+            v.A = s.A;
+            v.ldA = s.ldA;
+            v.m = s.m;
+            v.n = s.n;
+            v.b = s.b;
+            v.bref = s.bref;
+            v.nu = s.nu;
+            v.x = s.x;
+            v.wsum = s.wsum;
+            v.V = s.T > 0 ? s.V : nullptr;
+            v.ldV = s.ldA;
+            v.work = s.work;
+            v.ctl = s.ctl;
+            v.sl = last_slot(c);
+            v.dp = decide_of(p, 0);
+            q.place(&v, c->cert + used);
+            used += q.bytes;
+            const int32_t k = (int32_t)list.size();
+            list.push_back(v);
+            for (int g = 0; g < q.Gs; ++g) dot.push_back(CertJob{k, g, q.Gs, 0});
+            for (int b = 0; b < q.bands; ++b)
+                for (int t = 0; t < q.tiles; ++t) axpy.push_back(CertJob{k, b, t, 0});
+            for (int r = 0; r < q.R; ++r) red.push_back(CertJob{k, r, 0, 0});
+        }
+        const size_t jobs_at = list_at + up(sizeof(CertArgs) * list.size());
+        size_t at = jobs_at;
+        std::memcpy(host + list_at, list.data(), sizeof(CertArgs) * list.size());
+        for (const std::vector<CertJob> *v : {&dot, &axpy, &red}) {
+            std::memcpy(host + at, v->data(), sizeof(CertJob) * v->size());
+            at += sizeof(CertJob) * v->size();
+        }
+        HIP_TRY(c, hipMemcpyAsync(c->cert_list + list_at, host + list_at, at - list_at, hipMemcpyHostToDevice, c->stream));
+        HIP_TRY(c, aux_certify_list(c->dt, reinterpret_cast<const CertArgs *>(c->cert_list + list_at), (int)list.size(),
+                                    reinterpret_cast<const CertJob *>(c->cert_list + jobs_at), (int)dot.size(),
+                                    (int)axpy.size(), (int)red.size(), c->stream));
+        list_at = up(at);
+        first = end;
+    }
+    return MODAP_OK;
+}
+
+// The states after the certificates of every system whose committed state is
+// an uncertified stop.  Synchronises.
+modap_status certify_stopped(modap_batch *c, const modap_params *p, int *count, const State **states) {
+    *count = 0;
+    modap_status st;
+    if ((st = read_states(c, states))) return st;
+    std::vector<int64_t> ids;
+    for (size_t i = 0; i < c->h_sys.size(); ++i)
+        if ((*states)[i].status == ST_CONVERGED && !(*states)[i].certified) ids.push_back(c->order[i]);
+    if (ids.empty()) return MODAP_OK;
+    *count = (int)ids.size();
+    if ((st = certify_systems(c, ids, p))) return st;
+    return read_states(c, states);
 }
 
 }  // namespace
@@ -572,12 +588,9 @@ modap_status modap_batch_certify_ids(modap_batch *c, const modap_params *p, cons
     TraceRange trace_("modap_batch_certify_ids");
     if (!c) return MODAP_E_INVAL;
     DeviceGuard g(c->device);
-    modap_status st;
-    for (int64_t q = 0; q < count; ++q) {
-        BSys *s = find_sys(c, ids[q]);
-        if (!s) return fail(c, MODAP_E_INVAL, "unknown system id");
-        if ((st = certify_sys(c, *s, p))) return st;
-    }
+    for (int64_t q = 0; q < count; ++q)
+        if (!find_sys(c, ids[q])) return fail(c, MODAP_E_INVAL, "unknown system id");
+    if (modap_status st = certify_systems(c, std::vector<int64_t>(ids, ids + count), p)) return st;
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     return MODAP_OK;
 }
@@ -627,16 +640,8 @@ void modap_batch_destroy(modap_batch *c) {
     free_dev(c->queue);
     free_dev(c->claim);
     free_dev(c->rhs);
-    free_dev(c->d_states);
-    free_dev(c->cert_wt);
-    free_dev(c->cert_part);
-    free_dev(c->cert_y);
-    free_dev(c->cert_ynp);
-    free_dev(c->cert_h);
-    free_dev(c->cert_dmax);
-    free_dev(c->cert_binf);
-    free_dev(c->cert_drift);
-    free_dev(c->cert_tot);
+    free_dev(c->cert);
+    free_dev(c->cert_list);
     free_dev(c->bad);
     free_dev(c->flag);
     free_dev(c->stage);
@@ -859,9 +864,14 @@ modap_status modap_batch_iterate(modap_batch *c, const modap_params *p, int64_t 
         if ((st = enqueue_iteration(c, p, track, i, nullptr, &ev, &bytes))) return st;
     if (k > 0 && (st = enqueue_settle(c, p, track))) return st;
     if (!out) return MODAP_OK;
-    if (k > 0 && p->certify && (st = certify_stopped(c, p, nullptr))) return st;
-    int64_t running = 0;
-    if ((st = count_running_now(c, &running))) return st;
+    const State *states = nullptr;
+    int certified = 0;
+    if (k > 0 && p->certify) {
+        if ((st = certify_stopped(c, p, &certified, &states))) return st;
+    } else if ((st = read_states(c, &states))) {
+        return st;
+    }
+    const int64_t running = count_running(c, states);
     if (p->profile) HIP_TRY(c, hipStreamSynchronize(c->stream));   // the events too
     *out = modap_batch_stats{};
     out->iters = k;
@@ -920,14 +930,16 @@ modap_status modap_batch_solve(modap_batch *c, const modap_params *p, modap_batc
         }
         queued_all += queued;
         if ((st = enqueue_settle(c, p, 0))) return st;
-        if (!p->certify) break;
+        const State *states = nullptr;
         int certified = 0;
-        if ((st = certify_stopped(c, p, &certified))) return st;
-        if (certified == 0) break;
-        if ((st = count_running_now(c, &running))) return st;
-        if (running == 0) break;
+        if (p->certify) {
+            if ((st = certify_stopped(c, p, &certified, &states))) return st;
+        } else if ((st = read_states(c, &states))) {
+            return st;
+        }
+        running = count_running(c, states);
+        if (certified == 0 || running == 0) break;
     }
-    if ((st = count_running_now(c, &running))) return st;
     if (p->profile) HIP_TRY(c, hipStreamSynchronize(c->stream));   // the events too
     if (out) {
         *out = modap_batch_stats{};

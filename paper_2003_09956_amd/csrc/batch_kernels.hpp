@@ -725,21 +725,14 @@ __global__ __launch_bounds__(256) void settle_batch(const BatchArgs a) {
     for (int64_t col = threadIdx.x; col < S.n; col += blockDim.x) S.x[col] = step_point(S.x[col], s, S.y[col]);
 }
 
-// Status and certificate flag of every system in slot sl (one thread each).
-__global__ void gather_states(const BatchArgs a, int sl, int2 *out) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= a.nsys) return;
-    const State &s = a.sys[i].ctl->st[sl];
-    out[i] = make_int2(s.status, s.certified);
-}
-
-// Number of systems whose state in slot sl is ST_RUNNING, to the host (one
-// workgroup).
-__global__ __launch_bounds__(256) void publish_running(const BatchArgs a, int sl, HostView *view, uint32_t *arrived,
-                                                       uint32_t seq) {
-    const int cnt = running_systems(a, sl);
-    if (threadIdx.x == 0) view->running = (uint32_t)cnt;
-    announce(view, arrived, seq, 1);
+// The state in slot sl of every system, to host memory (16 threads a system).
+__global__ __launch_bounds__(256) void publish_states(const BatchArgs a, int sl, State *out, HostView *view,
+                                                      uint32_t *arrived, uint32_t seq) {
+    static_assert(sizeof(State) / 8 <= 16, "16 threads a state");
+    const int i = (int)(blockIdx.x * 16 + threadIdx.x / 16), w = threadIdx.x % 16;
+    if (i < a.nsys && w < (int)(sizeof(State) / 8))
+        reinterpret_cast<uint64_t *>(out + i)[w] = reinterpret_cast<const uint64_t *>(&a.sys[i].ctl->st[sl])[w];
+    announce(view, arrived, seq, gridDim.x);
 }
 
 }  // namespace modap

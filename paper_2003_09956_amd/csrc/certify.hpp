@@ -32,10 +32,14 @@
 //
 // Four kernels, each a no-op unless the committed state is an uncertified
 // stop (so they may be queued without knowing whether one is due):
-//   cert_dot     one wavefront per row: r_i, d_i, the step weight, the rebase
+//   cert_dot     rows in groups of 16: r_i, d_i, the step weight, the rebase
 //   cert_axpy    (row band, column tile): y partial over the band's violated rows
 //   cert_reduce  64 columns per workgroup: y and ||y||^2 parts; totals
 //   cert_decide  one workgroup: the decision, the step, the working vectors
+// They certify one system, or every stopped system of a batch in the same four
+// launches: a workgroup then finds its system and its part in a list of jobs.
+// (Four launches for each of 64 systems had taken 1.3 ms of kernels and as
+// much again of gaps between them.)
 #pragma once
 
 #include "aux_kernels.hpp"
@@ -56,42 +60,90 @@ __device__ __forceinline__ double gamma_of(int64_t k) {
     return ku / (1.0 - ku);
 }
 
+// The system and the part of this workgroup: job blockIdx.x of a list, or
+// (jobs null) the one system given by value and the part `own`.
+struct CertWork {
+    CertArgs a;
+    int first, second;
+};
+__device__ __forceinline__ CertWork cert_work(const CertArgs &one, const CertArgs *list, const CertJob *jobs, int own_a,
+                                              int own_b) {
+    if (!jobs) return CertWork{one, own_a, own_b};
+    const CertJob j = jobs[blockIdx.x];
+    return CertWork{list[j.sys], j.a, j.b};
+}
+
+// Rows of a system in groups of 16, four to a wavefront (kRows64); workgroup
+// `first` of the system takes groups first, first + stride, ...  Bound by the
+// read of A (8 flops an FP64 element pair, far below the FP64 vector rate).
+constexpr int kCertGroup = 4 * kRows64;
 template <int DT>
-__global__ __launch_bounds__(256) void cert_dot(const CertArgs a) {
+__global__ __launch_bounds__(256) void cert_dot(const CertArgs one, const CertArgs *list, const CertJob *jobs) {
+    const CertWork wk = cert_work(one, list, jobs, (int)blockIdx.x, (int)gridDim.x);
+    const CertArgs &a = wk.a;
     if (!cert_due(a.ctl, a.sl)) return;
+    constexpr int VEC = Store<DT>::VEC, R = kRows64;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t row = (int64_t)blockIdx.x * 4 + wave;
+    const double gm = gamma_of(a.n + 4);
     int64_t h = 0;
     double dup = 0.0, binf = 0.0, drift = 0.0;
-    if (row < a.m) {
-        double dx = 0.0, dw = 0.0, sc = 0.0;
-        for (int64_t j = lane; j < a.n; j += 64) {
-            const double e = load_elem<DT>(a.A, row * a.ldA + j);
-            const double xj = a.x[j], wj = a.wsum[j];
-            dx = __fma_rn(e, xj, dx);
-            dw = __fma_rn(e, wj, dw);
-            sc = __fma_rn(fabs(e), fabs(xj) + fabs(wj), sc);
+    const int64_t groups = (a.m + kCertGroup - 1) / kCertGroup;
+    for (int64_t g = wk.first; g < groups; g += wk.second) {
+        const int64_t row0 = g * kCertGroup + wave * R;
+        if (row0 >= a.m) continue;
+        // x and wsum are padded with zeros to ldA, as the rows are
+        double dx[R] = {}, dw[R] = {}, sc[R] = {};
+#pragma unroll 2
+        for (int64_t j = (int64_t)lane * VEC; j < a.ldA; j += 64 * VEC) {
+            double e[R][VEC], xj[VEC], wj[VEC];
+#pragma unroll
+            for (int r = 0; r < R; ++r) load_vec64<DT>(a.A, min(row0 + r, a.m - 1) * a.ldA + j, e[r]);
+            load_f64(a.x + j, xj);
+            load_f64(a.wsum + j, wj);
+#pragma unroll
+            for (int k = 0; k < VEC; ++k) {
+                const double aj = fabs(xj[k]) + fabs(wj[k]);
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    dx[r] = __fma_rn(e[r][k], xj[k], dx[r]);
+                    dw[r] = __fma_rn(e[r][k], wj[k], dw[r]);
+                    sc[r] = __fma_rn(fabs(e[r][k]), aj, sc[r]);
+                }
+            }
         }
-        dx = wave_sum(dx);
-        dw = wave_sum(dw);
-        sc = wave_sum(sc);
-        const double br = a.bref[row];
-        const double bi = br + dw;
-        const double r = dx - bi;
-        const double nu = a.nu[row];
-        const double gm = gamma_of(a.n + 4);
-        const double g = 4.0 * gm * (sc + fabs(br));
-        const double d = ((r + g) / sqrt(nu)) * (1.0 + 2.0 * gm);
-        drift = fabs(a.b[row] - bi);
-        if (lane == 0) {
+        // the wavefront sums, then lane r settles row row0 + r
+        double dxl = 0.0, dwl = 0.0, scl = 0.0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const double tx = wave_total(dx[r]), tw = wave_total(dw[r]), ts = wave_total(sc[r]);
+            if (lane == r) {
+                dxl = tx;
+                dwl = tw;
+                scl = ts;
+            }
+        }
+        const int64_t row = row0 + lane;
+        if (lane < R && row < a.m) {
+            const double br = a.bref[row];
+            const double bi = br + dwl;
+            const double r = dxl - bi;
+            const double nu = a.nu[row];
+            const double gb = 4.0 * gm * (scl + fabs(br));
+            const double d = ((r + gb) / sqrt(nu)) * (1.0 + 2.0 * gm);
+            drift = max_nan(drift, fabs(a.b[row] - bi));
             a.b[row] = bi;
             a.bref[row] = bi;
             a.wt[row] = r > 0.0 ? r / nu : 0.0;
+            h += r > 0.0 ? 1 : 0;
+            dup = max_nan(dup, d > 0.0 ? d : (d != d ? d : 0.0));
+            binf = max_nan(binf, fabs(bi));
         }
-        h = r > 0.0 ? 1 : 0;
-        dup = d > 0.0 ? d : (d != d ? d : 0.0);
-        binf = fabs(bi);
     }
+    // (the lanes that settled no row hold zeros)
+    h = (int64_t)wave_total((double)h);   // an integer below 2^53: exact
+    dup = wave_max_nan(dup);
+    binf = wave_max_nan(binf);
+    drift = wave_max_nan(drift);
     __shared__ int64_t hs[4];
     __shared__ double ds[4], bs[4], fs[4];
     if (lane == 0) {
@@ -102,31 +154,34 @@ __global__ __launch_bounds__(256) void cert_dot(const CertArgs a) {
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        a.h_part[blockIdx.x] = ((hs[0] + hs[1]) + hs[2]) + hs[3];
-        a.dmax_part[blockIdx.x] = max_nan(max_nan(ds[0], ds[1]), max_nan(ds[2], ds[3]));
-        a.binf_part[blockIdx.x] = max_nan(max_nan(bs[0], bs[1]), max_nan(bs[2], bs[3]));
-        a.drift_part[blockIdx.x] = max_nan(max_nan(fs[0], fs[1]), max_nan(fs[2], fs[3]));
+        a.h_part[wk.first] = ((hs[0] + hs[1]) + hs[2]) + hs[3];
+        a.dmax_part[wk.first] = max_nan(max_nan(ds[0], ds[1]), max_nan(ds[2], ds[3]));
+        a.binf_part[wk.first] = max_nan(max_nan(bs[0], bs[1]), max_nan(bs[2], bs[3]));
+        a.drift_part[wk.first] = max_nan(max_nan(fs[0], fs[1]), max_nan(fs[2], fs[3]));
     }
 }
 
 // Partial y of one row band over one column tile of 256 VEC-element vectors
 // (VEC = 16 bytes of the storage type): the band's violated rows are listed
 // in row order, 256 at a time (a ballot per wavefront, wavefronts in order),
-// and each is added in FP64, four rows in flight, in row order.
+// and each is added in FP64, four rows in flight, in row order.  A band
+// without violated rows, the usual case at a stop, writes no partial.
 template <int DT>
-__global__ __launch_bounds__(256) void cert_axpy(const CertArgs a) {
+__global__ __launch_bounds__(256) void cert_axpy(const CertArgs one, const CertArgs *list, const CertJob *jobs) {
+    const CertWork wk = cert_work(one, list, jobs, (int)blockIdx.x, (int)blockIdx.y);
+    const CertArgs &a = wk.a;
     if (!cert_due(a.ctl, a.sl)) return;
     using T = typename Store<DT>::T;
     constexpr int VEC = Store<DT>::VEC;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t col = (int64_t)blockIdx.y * (256 * VEC) + (int64_t)tid * VEC;
+    const int64_t col = (int64_t)wk.second * (256 * VEC) + (int64_t)tid * VEC;
     const bool in = col < a.ldA;
-    const int64_t r0 = (int64_t)blockIdx.x * a.rows_per_band;
+    const int64_t r0 = (int64_t)wk.first * a.rows_per_band;
     const int64_t r1 = min(a.m, r0 + a.rows_per_band);
     double acc[VEC];
 #pragma unroll
     for (int e = 0; e < VEC; ++e) acc[e] = 0.0;
-    __shared__ int64_t list[256];
+    __shared__ int64_t vrows[256];
     __shared__ double wl[256];
     __shared__ int wcount[4];
     const T *A = reinterpret_cast<const T *>(a.A);
@@ -154,6 +209,7 @@ __global__ __launch_bounds__(256) void cert_axpy(const CertArgs a) {
 #pragma unroll
         for (int e = 0; e < VEC; ++e) acc[e] = __fma_rn(w, av[e], acc[e]);
     };
+    int violated = 0;
     for (int64_t base = r0; base < r1; base += 256) {
         const int64_t r = base + tid;
         const double w = r < r1 ? a.wt[r] : 0.0;
@@ -166,25 +222,27 @@ __global__ __launch_bounds__(256) void cert_axpy(const CertArgs a) {
             if (q < wave) off += wcount[q];
             total += wcount[q];
         }
+        violated += total;
         if (f) {
             const int at = off + __popcll(bal & ((1ull << lane) - 1ull));
-            list[at] = r;
+            vrows[at] = r;
             wl[at] = w;
         }
         __syncthreads();
         int k = 0;
         for (; k + 4 <= total; k += 4) {
-            const uint4 u0 = fetch(list[k]), u1 = fetch(list[k + 1]), u2 = fetch(list[k + 2]), u3 = fetch(list[k + 3]);
+            const uint4 u0 = fetch(vrows[k]), u1 = fetch(vrows[k + 1]), u2 = fetch(vrows[k + 2]), u3 = fetch(vrows[k + 3]);
             add_row(u0, wl[k]);
             add_row(u1, wl[k + 1]);
             add_row(u2, wl[k + 2]);
             add_row(u3, wl[k + 3]);
         }
-        for (; k < total; ++k) add_row(fetch(list[k]), wl[k]);
+        for (; k < total; ++k) add_row(fetch(vrows[k]), wl[k]);
         __syncthreads();   // the list is rewritten by the next chunk
     }
-    if (in) {
-        double *p = a.part + (int64_t)blockIdx.x * a.ldA + col;
+    if (tid == 0 && wk.second == 0) a.band_rows[wk.first] = violated;
+    if (in && violated > 0) {
+        double *p = a.part + (int64_t)wk.first * a.ldA + col;
 #pragma unroll
         for (int e = 0; e < VEC; ++e) p[e] = acc[e];
     }
@@ -192,18 +250,21 @@ __global__ __launch_bounds__(256) void cert_axpy(const CertArgs a) {
 
 // y as the sum of the band partials in band order, the parts of ||y||^2, and
 // (workgroup 0) the totals of the dot workgroups' scalars.
-__global__ __launch_bounds__(256) void cert_reduce(const CertArgs a) {
+__global__ __launch_bounds__(256) void cert_reduce(const CertArgs one, const CertArgs *list, const CertJob *jobs) {
+    const CertWork wk = cert_work(one, list, jobs, (int)blockIdx.x, 0);
+    const CertArgs &a = wk.a;
     if (!cert_due(a.ctl, a.sl)) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t col = (int64_t)blockIdx.x * 64 + lane;
+    const int64_t col = (int64_t)wk.first * 64 + lane;
     double s = 0.0;
     if (col < a.n)
-        for (int q = wave; q < a.bands; q += 4) s += a.part[(int64_t)q * a.ldA + col];
+        for (int q = wave; q < a.bands; q += 4)
+            if (a.band_rows[q] > 0) s += a.part[(int64_t)q * a.ldA + col];
     __shared__ double sh[4][64];
     sh[wave][lane] = s;
     int64_t h = 0;
     double dm = 0.0, bm = 0.0, fm = 0.0;
-    if (blockIdx.x == 0) {
+    if (wk.first == 0) {
         for (int g = tid; g < a.Gs; g += 256) {
             h += a.h_part[g];
             dm = max_nan(dm, a.dmax_part[g]);
@@ -235,8 +296,8 @@ __global__ __launch_bounds__(256) void cert_reduce(const CertArgs a) {
         sq = yv * yv;
     }
     sq = wave_sum(sq);
-    if (lane == 0) a.ynp[blockIdx.x] = sq;
-    if (blockIdx.x == 0 && lane == 0) {
+    if (lane == 0) a.ynp[wk.first] = sq;
+    if (wk.first == 0 && lane == 0) {
         Totals t{};
         for (int q = 0; q < 4; ++q) {
             t.h += hw[q];
@@ -257,7 +318,8 @@ __global__ __launch_bounds__(256) void cert_reduce(const CertArgs a) {
 // failure with no row violated in FP64 means eps_abs lies below the rounding
 // bound: ST_UNCERTIFIED.  wsum is cleared (b and bref hold the exact data).
 template <typename Acc>
-__global__ __launch_bounds__(1024) void cert_decide(const CertArgs a) {
+__global__ __launch_bounds__(1024) void cert_decide(const CertArgs one, const CertArgs *list) {
+    const CertArgs a = list ? list[blockIdx.x] : one;
     const State p = load_global(&a.ctl->st[a.sl]);
     if (!(p.status == ST_CONVERGED && p.certified == 0)) return;
     __shared__ State sst;

@@ -107,13 +107,9 @@ struct modap_ctx {
     int64_t *res_h = nullptr;
     double *res_dmax = nullptr, *res_binf = nullptr;
 
-    // FP64 certificate scratch (allocated at the first certificate of a system)
-    double *cert_wt = nullptr, *cert_part = nullptr, *cert_y = nullptr, *cert_ynp = nullptr;
-    int64_t *cert_h = nullptr;
-    double *cert_dmax = nullptr, *cert_binf = nullptr, *cert_drift = nullptr;
-    Totals *cert_tot = nullptr;
-    int cert_bands = 0;
-    int64_t cert_rows_per_band = 0;
+    // FP64 certificate (scratch allocated at the first certificate of a system)
+    void *cert = nullptr;
+    CertPlan cert_cut{};
 
     std::vector<hipEvent_t> events;
 };
@@ -656,19 +652,6 @@ modap_status status_of(modap_ctx *c, const State &k, bool solve) {
     }
 }
 
-void release_cert(modap_ctx *c) {
-    free_dev(c->cert_wt);
-    free_dev(c->cert_part);
-    free_dev(c->cert_y);
-    free_dev(c->cert_ynp);
-    free_dev(c->cert_h);
-    free_dev(c->cert_dmax);
-    free_dev(c->cert_binf);
-    free_dev(c->cert_drift);
-    free_dev(c->cert_tot);
-    c->cert_bands = 0;
-}
-
 void release_resident(modap_ctx *c) {
     free_dev(c->res_part);
     free_dev(c->res_h);
@@ -678,7 +661,7 @@ void release_resident(modap_ctx *c) {
 }
 
 void release_system(modap_ctx *c) {
-    release_cert(c);
+    free_dev(c->cert);
     release_resident(c);
     free_dev(c->bref);
     free_dev(c->wsum);
@@ -819,32 +802,14 @@ modap_status poll_pause(modap_ctx *c, uint32_t turn) {
     return MODAP_OK;
 }
 
-// Scratch of the FP64 certificate: row bands of at least 256 rows, at most
-// 128 bands (the band partials of y are FP64 rows of ldA).
-modap_status ensure_cert(modap_ctx *c) {
-    if (c->cert_bands > 0) return MODAP_OK;
-    const int64_t rpb = std::max<int64_t>(256, (c->m + 127) / 128);
-    const int bands = (int)((c->m + rpb - 1) / rpb);
-    const int64_t gs = (c->m + 3) / 4;
-    HIP_TRY(c, hipMalloc(&c->cert_wt, sizeof(double) * (size_t)c->m));
-    HIP_TRY(c, hipMalloc(&c->cert_part, sizeof(double) * (size_t)bands * (size_t)c->ldA));
-    HIP_TRY(c, hipMalloc(&c->cert_y, sizeof(double) * (size_t)c->ldA));
-    HIP_TRY(c, hipMalloc(&c->cert_ynp, sizeof(double) * (size_t)reduce_grid(c)));
-    HIP_TRY(c, hipMalloc(&c->cert_h, sizeof(int64_t) * (size_t)gs));
-    HIP_TRY(c, hipMalloc(&c->cert_dmax, sizeof(double) * (size_t)gs));
-    HIP_TRY(c, hipMalloc(&c->cert_binf, sizeof(double) * (size_t)gs));
-    HIP_TRY(c, hipMalloc(&c->cert_drift, sizeof(double) * (size_t)gs));
-    HIP_TRY(c, hipMalloc(&c->cert_tot, sizeof(Totals)));
-    c->cert_rows_per_band = rpb;
-    c->cert_bands = bands;
-    return MODAP_OK;
-}
-
 // Queue the FP64 certificate of the committed state (a no-op on the device
 // unless that state is an uncertified stop).
 modap_status enqueue_certify(modap_ctx *c, const modap_params *p) {
-    modap_status st;
-    if ((st = ensure_cert(c))) return st;
+    if (!c->cert) {
+        // eight workgroups per CU keep the pass over A at the HBM rate
+        c->cert_cut = cert_plan(c->dt, c->m, c->n, c->ldA, 8 * (int64_t)c->cu_count);
+        HIP_TRY(c, hipMalloc(&c->cert, c->cert_cut.bytes));
+    }
     CertArgs v{};
     v.A = c->A;
     v.ldA = c->ldA;
@@ -860,19 +825,9 @@ modap_status enqueue_certify(modap_ctx *c, const modap_params *p) {
     v.work = c->work;
     v.ctl = c->ctl;
     v.sl = last_slot(c);
-    v.wt = c->cert_wt;
-    v.h_part = c->cert_h;
-    v.dmax_part = c->cert_dmax;
-    v.binf_part = c->cert_binf;
-    v.drift_part = c->cert_drift;
-    v.bands = c->cert_bands;
-    v.rows_per_band = c->cert_rows_per_band;
-    v.part = c->cert_part;
-    v.y = c->cert_y;
-    v.ynp = c->cert_ynp;
-    v.tot = c->cert_tot;
+    c->cert_cut.place(&v, c->cert);
     v.dp = decide_params(p, 0);
-    HIP_TRY(c, aux_certify(c->dt, v, c->stream));
+    HIP_TRY(c, aux_certify(c->dt, v, c->cert_cut, c->stream));
     return MODAP_OK;
 }
 
@@ -1604,7 +1559,7 @@ hipError_t aux_ctl_set_drift(Ctrl *c, int sl, int64_t T, hipStream_t s) {
 hipError_t aux_rhs_exact(int dt, const void *A, int64_t ldA, int64_t m, int64_t n, const Ctrl *ctl, int sl,
                          const double *bref, const double *wsum, const double *vpend, const double *V, int64_t ldV,
                          double *out, hipStream_t s) {
-    const int nb = (int)((m + 3) / 4);
+    const int nb = (int)((m + 4 * kRows64 - 1) / (4 * kRows64));
     switch (dt) {
         case 0: hipLaunchKernelGGL(rhs_exact<0>, dim3(nb), dim3(256), 0, s, A, ldA, m, n, ctl, sl, bref, wsum, vpend, V, ldV, out); break;
         case 1: hipLaunchKernelGGL(rhs_exact<1>, dim3(nb), dim3(256), 0, s, A, ldA, m, n, ctl, sl, bref, wsum, vpend, V, ldV, out); break;
@@ -1690,24 +1645,79 @@ hipError_t static_sweep_launch(int dt, const StaticPlan &plan, const SweepScratc
     return hipPeekAtLastError();
 }
 
-template <int DT>
-static void launch_cert(CertArgs a, hipStream_t s) {
-    using Acc = typename Store<DT>::Acc;
-    constexpr int VEC = Store<DT>::VEC;
-    const int tiles = (int)((a.ldA + 256 * VEC - 1) / (256 * VEC));
-    hipLaunchKernelGGL(cert_dot<DT>, dim3(a.Gs), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(cert_axpy<DT>, dim3(a.bands, tiles), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(cert_reduce, dim3(a.R), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(cert_decide<Acc>, dim3(1), dim3(1024), 0, s, a);
+CertPlan cert_plan(int dt, int64_t m, int64_t n, int64_t ldA, int64_t workgroups) {
+    CertPlan p{};
+    const int64_t groups = (m + kCertGroup - 1) / kCertGroup, tile = 256 * (int64_t)vec_elems(dt);
+    p.Gs = (int)std::max<int64_t>(1, std::min(groups, workgroups));
+    p.rows_per_band = std::max<int64_t>(256, (m + 127) / 128);   // at most 128 bands: their partials are FP64 rows
+    p.bands = (int)((m + p.rows_per_band - 1) / p.rows_per_band);
+    p.tiles = (int)((ldA + tile - 1) / tile);
+    p.R = (int)((n + 63) / 64);
+    auto up = [](size_t v) { return (v + 255) & ~(size_t)255; };
+    p.bytes = up(8 * (size_t)m) + up(8 * (size_t)p.bands * (size_t)ldA) + up(8 * (size_t)ldA) + up(8 * (size_t)p.R) +
+              4 * up(8 * (size_t)p.Gs) + up(4 * (size_t)p.bands) + up(sizeof(Totals));
+    return p;
 }
 
-hipError_t aux_certify(int dt, CertArgs a, hipStream_t s) {
-    a.R = (int32_t)((a.n + 63) / 64);
-    a.Gs = (int32_t)((a.m + 3) / 4);
+void CertPlan::place(CertArgs *a, void *base) const {
+    unsigned char *at = static_cast<unsigned char *>(base);
+    auto take = [&](size_t bytes) {
+        unsigned char *q = at;
+        at += (bytes + 255) & ~(size_t)255;
+        return q;
+    };
+    a->wt = reinterpret_cast<double *>(take(8 * (size_t)a->m));
+    a->part = reinterpret_cast<double *>(take(8 * (size_t)bands * (size_t)a->ldA));
+    a->y = reinterpret_cast<double *>(take(8 * (size_t)a->ldA));
+    a->ynp = reinterpret_cast<double *>(take(8 * (size_t)R));
+    a->h_part = reinterpret_cast<int64_t *>(take(8 * (size_t)Gs));
+    a->dmax_part = reinterpret_cast<double *>(take(8 * (size_t)Gs));
+    a->binf_part = reinterpret_cast<double *>(take(8 * (size_t)Gs));
+    a->drift_part = reinterpret_cast<double *>(take(8 * (size_t)Gs));
+    a->band_rows = reinterpret_cast<int32_t *>(take(4 * (size_t)bands));
+    a->tot = reinterpret_cast<Totals *>(take(sizeof(Totals)));
+    a->R = R;
+    a->Gs = Gs;
+    a->bands = bands;
+    a->rows_per_band = rows_per_band;
+}
+
+template <int DT>
+static void launch_cert(const CertArgs &a, const CertPlan &p, hipStream_t s) {
+    using Acc = typename Store<DT>::Acc;
+    const CertArgs *nl = nullptr;
+    const CertJob *nj = nullptr;
+    hipLaunchKernelGGL(cert_dot<DT>, dim3(p.Gs), dim3(256), 0, s, a, nl, nj);
+    hipLaunchKernelGGL(cert_axpy<DT>, dim3(p.bands, p.tiles), dim3(256), 0, s, a, nl, nj);
+    hipLaunchKernelGGL(cert_reduce, dim3(p.R), dim3(256), 0, s, a, nl, nj);
+    hipLaunchKernelGGL(cert_decide<Acc>, dim3(1), dim3(1024), 0, s, a, nl);
+}
+
+template <int DT>
+static void launch_cert_list(const CertArgs *list, int count, const CertJob *jobs, int nd, int na, int nr, hipStream_t s) {
+    using Acc = typename Store<DT>::Acc;
+    const CertArgs none{};
+    hipLaunchKernelGGL(cert_dot<DT>, dim3(nd), dim3(256), 0, s, none, list, jobs);
+    hipLaunchKernelGGL(cert_axpy<DT>, dim3(na), dim3(256), 0, s, none, list, jobs + nd);
+    hipLaunchKernelGGL(cert_reduce, dim3(nr), dim3(256), 0, s, none, list, jobs + nd + na);
+    hipLaunchKernelGGL(cert_decide<Acc>, dim3(count), dim3(1024), 0, s, none, list);
+}
+
+hipError_t aux_certify(int dt, const CertArgs &a, const CertPlan &p, hipStream_t s) {
     switch (dt) {
-        case 0: launch_cert<0>(a, s); break;
-        case 1: launch_cert<1>(a, s); break;
-        default: launch_cert<2>(a, s); break;
+        case 0: launch_cert<0>(a, p, s); break;
+        case 1: launch_cert<1>(a, p, s); break;
+        default: launch_cert<2>(a, p, s); break;
+    }
+    return hipPeekAtLastError();
+}
+
+hipError_t aux_certify_list(int dt, const CertArgs *list, int count, const CertJob *jobs, int ndot, int naxpy,
+                            int nreduce, hipStream_t s) {
+    switch (dt) {
+        case 0: launch_cert_list<0>(list, count, jobs, ndot, naxpy, nreduce, s); break;
+        case 1: launch_cert_list<1>(list, count, jobs, ndot, naxpy, nreduce, s); break;
+        default: launch_cert_list<2>(list, count, jobs, ndot, naxpy, nreduce, s); break;
     }
     return hipPeekAtLastError();
 }

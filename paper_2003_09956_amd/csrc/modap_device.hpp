@@ -197,14 +197,24 @@ struct CertArgs {
     double *dmax_part;      // [dot workgroups]
     double *binf_part;      // [dot workgroups]
     double *drift_part;     // [dot workgroups]
-    int32_t Gs;             // dot workgroups: ceil(m / 4)
+    int32_t Gs;             // dot workgroups
     int32_t bands;          // row bands of cert_axpy
     int64_t rows_per_band;
-    double *part;           // [bands x ldA] FP64 partial y
+    int32_t *band_rows;     // [bands] violated rows of each band
+    double *part;           // [bands x ldA] FP64 partial y (of the bands that have any)
     double *y;              // [ldA] FP64 y of the certificate
     double *ynp;            // [R]
     Totals *tot;
     Decide dp;
+};
+
+// What one workgroup of a certificate kernel does when several systems share
+// the launch: system `sys` of the list, and its part there.
+struct CertJob {
+    int32_t sys;
+    int32_t a;              // first row group / row band / 64-column block
+    int32_t b;              // row groups between two of its own / column tile
+    int32_t pad;
 };
 
 __host__ __device__ __forceinline__ int slot_of(int64_t j) { return (int)(j & 1); }
