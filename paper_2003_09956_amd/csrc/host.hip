@@ -20,6 +20,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <iterator>
 #include <string>
 #include <thread>
 #include <unordered_set>
@@ -150,50 +151,77 @@ const SplitKernels *split_for(int dt) {
 
 constexpr int64_t kMaxBandRows = 4096;  // rows per band of the split-row form (its row list)
 
-// Built-in choice of the fused sweep's shape (what measured fastest on the
-// headline systems): the smallest row coverage that holds a padded row; among
-// equal coverage, about 32 elements (128 bytes of FP32) per lane per row, then
-// the smaller workgroup, one row per step and the shallowest prefetch.
-bool choose_shape(int dt, int64_t ldA, modap_tile *out) {
-    int cnt = 0;
-    const SweepKernel *t = kernels_for(dt, &cnt);
-    const SweepKernel *best = nullptr;
-    int64_t best_cov = 0;
-    int best_score = INT_MAX;
-    for (int i = 0; i < cnt; ++i) {
-        if (!t[i].has_v) continue;
-        const int64_t cov = coverage(dt, t[i].lpr, t[i].chunks);
-        if (cov < ldA) continue;
-        const int epl = t[i].chunks * vec_elems(dt);
-        const int score = std::abs(epl - 32) * 16 + (t[i].block == 256 ? 0 : t[i].block == 512 ? 4 : 8) +
-                          (t[i].rs == 1 ? 0 : 2) + 4 * (t[i].pd - 2) + (t[i].lpr == t[i].block ? 0 : 1);
-        if (!best || cov < best_cov || (cov == best_cov && score < best_score)) {
-            best = &t[i];
-            best_cov = cov;
-            best_score = score;
-        }
-    }
-    if (!best) {
+// Built-in choice of the fused sweep's shape, by storage type and padded row
+// length: the first entry that holds a row.  The line between two entries is
+// the coverage of the first (lanes x chunks x 16 bytes); why this shape at a
+// length:
+//  - rows of up to 256 bytes: 16 lanes a row, four rows to a wavefront;
+//  - up to 8 KiB: a wavefront a row with all its chunks in registers.  No
+//    barrier per row, and every wavefront keeps two or three rows in flight.
+//    A row shared by 256 lanes pays a barrier and an exchange per row, which a
+//    row of 8 KiB does not cover: BF16 4096 x 16384 took 46.8 us an iteration
+//    at 256 lanes and 33.2 at 64, FP64 1000 x 4000 18.4 and 15.2, FP32
+//    2000 x 6000 19.2 and 16.9; three or four rows of 16 lanes with four
+//    chunks lose the same way (FP32 250 x 16384 14.4 and 13.0, BF16
+//    500 x 32768 22.0 and 18.5);
+//  - longer rows: the workgroup shares the row, in the fewest chunks that hold
+//    it (BF16 12000 x 30000: 119.7 us with three chunks, 122.7 with four).
+//    12-chunk wavefronts still beat 256 lanes on BF16 rows of 8 to 12 KiB
+//    (6000 x 18000: 51.6 against 60.2).
+// Rows longer than the last entry take the split-row form.
+struct ShapeFor {
+    int32_t row;    // longest padded row
+    int32_t block, lpr, chunks, rs, pd;
+};
+constexpr ShapeFor kShapesF64[] = {
+    {32, 256, 16, 1, 1, 2},    {64, 256, 16, 2, 1, 2},    {128, 256, 16, 4, 1, 2},   {256, 256, 64, 2, 2, 2},
+    {384, 256, 64, 3, 2, 2},   {512, 256, 64, 4, 1, 2},   {768, 256, 64, 6, 1, 3},   {1024, 256, 64, 8, 1, 2},
+    {1536, 256, 64, 12, 1, 2}, {2048, 256, 256, 4, 1, 4}, {3072, 256, 256, 6, 1, 2}, {4096, 256, 256, 8, 1, 2},
+    {6144, 512, 512, 6, 1, 2}, {8192, 512, 512, 8, 1, 2}};
+constexpr ShapeFor kShapesF32[] = {
+    {64, 256, 16, 1, 1, 2},    {128, 256, 16, 2, 1, 2},   {256, 512, 64, 1, 1, 4},   {512, 512, 64, 2, 2, 2},
+    {768, 256, 64, 3, 1, 3},   {1024, 256, 64, 4, 1, 2},  {1536, 256, 64, 6, 1, 3},  {2048, 256, 64, 8, 1, 2},
+    {4096, 512, 256, 4, 1, 2}, {6144, 256, 256, 6, 1, 2}, {8192, 256, 256, 8, 1, 2}, {12288, 512, 512, 6, 1, 2},
+    {16384, 512, 512, 8, 1, 2}};
+constexpr ShapeFor kShapesBF16[] = {
+    {128, 256, 16, 1, 1, 2},   {256, 256, 16, 2, 1, 2},   {512, 256, 64, 1, 2, 2},   {1024, 256, 64, 2, 1, 2},
+    {1536, 256, 64, 3, 1, 3},  {2048, 256, 64, 4, 1, 2},  {3072, 256, 64, 6, 1, 2},  {4096, 256, 64, 8, 1, 3},
+    {6144, 256, 64, 12, 1, 2}, {8192, 512, 512, 2, 2, 2}, {12288, 512, 512, 3, 1, 2}, {16384, 512, 512, 4, 1, 2}};
+
+// Two exceptions by the number of rows.  FP64 rows of 65 to 128 elements: four
+// rows to a wavefront leave compute units idle on short systems (120 x 480:
+// 9.8 us against 8.4 with a wavefront a row, 120 x 4096 12.3 and 11.5, but
+// 120 x 16384 14.9 and 16.1).  And 16-lane rows of long systems take two
+// workgroups per CU, whose partials are short (BF16 100 x 131072: 21.0 us
+// against 25.2; FP32 120 x 65536 17.2 and 18.3, 120 x 16384 13.6 and 12.2).
+constexpr int64_t kFewRowsF64 = 8192;
+constexpr int64_t kManyRows = 65536;
+
+void choose_shape(int dt, int64_t ldA, int64_t m, int cu_count, modap_tile *out) {
+    const ShapeFor *t = dt == 0 ? kShapesF64 : dt == 1 ? kShapesF32 : kShapesBF16;
+    const ShapeFor *end = dt == 0 ? std::end(kShapesF64) : dt == 1 ? std::end(kShapesF32) : std::end(kShapesBF16);
+    while (t != end && t->row < ldA) ++t;
+    *out = modap_tile{};
+    if (t == end) {
         const SplitKernels *sk = split_for(dt);
         out->kind = 1;
         out->block = sk->block;
         out->lanes_per_row = sk->block;
         out->chunks = sk->chunks;
-        out->grid = 0;
         out->rows_per_step = 1;
-        out->depth = 0;
-        out->interleave = 0;
-        return true;
+        return;
     }
-    out->kind = 0;
-    out->block = best->block;
-    out->lanes_per_row = best->lpr;
-    out->chunks = best->chunks;
-    out->grid = 0;
-    out->rows_per_step = best->rs;
-    out->depth = best->pd;
-    out->interleave = 0;
-    return true;
+    out->block = t->block;
+    out->lanes_per_row = t->lpr;
+    out->chunks = t->chunks;
+    out->rows_per_step = t->rs;
+    out->depth = t->pd;
+    if (dt == 0 && t->row == 128 && m < kFewRowsF64) {
+        out->lanes_per_row = 64;
+        out->chunks = 1;
+    } else if (t->lpr < 64 && m >= kManyRows) {
+        out->grid = 2 * cu_count;
+    }
 }
 
 modap_status ensure_scalar_parts(modap_ctx *c, int count) {
@@ -1049,10 +1077,7 @@ modap_status modap_set_system(modap_ctx *c, int64_t m, int64_t n, modap_dtype st
     }
     if (!ok && cache_lookup(c, &t)) ok = configure(c, t) == MODAP_OK;
     if (!ok) {
-        if (!choose_shape(c->dt, c->ldA, &t)) {
-            release_system(c);
-            return fail(c, MODAP_E_INVAL, "rows too long for the one-pass sweep shapes");
-        }
+        choose_shape(c->dt, c->ldA, m, c->cu_count, &t);
         c->tile_forced = false;
         if ((st = configure(c, t))) {
             release_system(c);
@@ -1389,7 +1414,7 @@ modap_status modap_set_tile(modap_ctx *c, const modap_tile *t) {
         c->tile_forced = false;
         if (!c->loaded) return MODAP_OK;
         modap_tile d{};
-        if (!choose_shape(c->dt, c->ldA, &d)) return fail(c, MODAP_E_INVAL, "no built-in shape");
+        choose_shape(c->dt, c->ldA, c->m, c->cu_count, &d);
         HIP_TRY(c, hipStreamSynchronize(c->stream));
         return configure(c, d);
     }
@@ -1431,7 +1456,8 @@ modap_status modap_autotune(modap_ctx *c, int reps, modap_tile *best) {
     constexpr float kMargin = 0.98f;
     std::vector<modap_tile> order;
     modap_tile def{};
-    if (choose_shape(c->dt, c->ldA, &def) && def.kind == 0) order.push_back(def);
+    choose_shape(c->dt, c->ldA, c->m, c->cu_count, &def);
+    if (def.kind == 0) order.push_back(def);
     for (int i = 0; i < cnt; ++i) {
         if (tab[i].has_v != hv) continue;
         if (coverage(c->dt, tab[i].lpr, tab[i].chunks) < c->ldA) continue;
@@ -1570,12 +1596,15 @@ hipError_t aux_rhs_exact(int dt, const void *A, int64_t ldA, int64_t m, int64_t 
 
 bool static_sweep_plan(int dt, int64_t ldA, int64_t m, int64_t n, int cu_count, StaticPlan *out) {
     modap_tile t{};
-    if (!choose_shape(dt, ldA, &t) || t.kind != 0) return false;
+    choose_shape(dt, ldA, m, cu_count, &t);
+    // (FP64 rows above 4096 elements have a one-pass shape, whose partials do
+    // not always fit the static scratch: they stay refused)
+    if (t.kind != 0 || (dt == 0 && ldA > 4096)) return false;
     const SweepKernel *k = find_kernel(dt, t.block, t.lanes_per_row, t.chunks, t.rows_per_step, t.depth, false);
     if (!k) return false;
     // the row mapping of configure() for a band of rows per workgroup
     const int per_step = (t.block / t.lanes_per_row) * t.rows_per_step;
-    int grid = std::max(1, cu_count);
+    int grid = t.grid > 0 ? t.grid : std::max(1, cu_count);
     int64_t rpb = (m + grid - 1) / grid;
     rpb = ((rpb + per_step - 1) / per_step) * per_step;
     grid = (int)((m + rpb - 1) / rpb);
