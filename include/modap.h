@@ -59,9 +59,10 @@
  *   MODAP_RESIDENT_ROWS=k        rows per workgroup the resident form aims for
  *                                (default 32, at least 4)
  *   MODAP_RESIDENT_TIMEOUT_TICKS=t  longest wait of a resident launch at its grid
- *                                barrier, in ticks of the 100 MHz constant clock
- *                                (default 1e8: one second); a longer wait ends the
- *                                launch, and the call reports E_DEVICE
+ *                                barrier, and of a long-row sweep for another
+ *                                workgroup's dot product, in ticks of the 100 MHz
+ *                                constant clock (default 1e8: one second); after a
+ *                                longer wait the call reports E_DEVICE
  *   MODAP_BATCH_SHORT=0          batches sweep short rows one to a wavefront
  *                                instead of four
  */
@@ -150,7 +151,8 @@ typedef struct {
 } modap_stats;
 
 /* Kernel shape of the sweep (see modap_set_tile).  kind 0 = one pass with a
- * whole row on chip, kind 1 = split-row two-phase form for very long rows. */
+ * whole row on chip, kind 1 = split-row form for very long rows: two phases
+ * when forced by modap_set_tile, else one read of A where that is faster. */
 typedef struct {
     int32_t kind;
     int32_t block;          /* threads per workgroup */

@@ -35,6 +35,7 @@
 #include "modap.h"
 #include "readback.hpp"
 #include "resident.hpp"
+#include "sweep_relay.hpp"
 #include "sweep_split.hpp"
 #include "modap_device.hpp"
 #include "sweep_table.hpp"
@@ -75,6 +76,13 @@ struct modap_ctx {
     void *pdot = nullptr;
     size_t pdot_bytes = 0;
     double *wrow = nullptr;
+    // one-read form of long rows (sweep_relay.hpp), used in place of the two phases
+    bool relay_ok = false;
+    bool relay_now = false;      // the last sweep queued took it
+    int relay_tiles = 0, relay_bands = 0;
+    int64_t relay_tile = 0, relay_rows = 0, relay_ldPart = 0;
+    uint64_t *relay_words = nullptr;
+    uint32_t relay_base = 0;     // number of the next launch's first row
     int64_t rows_per_block = 0;  // one-pass sweep: row mapping (see SweepArgs)
     int64_t block_stride = 0;
     int64_t step_stride = 0;
@@ -149,6 +157,15 @@ const SplitKernels *split_for(int dt) {
     }
 }
 
+// Systems of at least this many bytes, cut into tiles of at least this many
+// bytes a row, take the one-read form of long rows; below, the two phases are
+// as fast or faster (us an iteration, one read and two phases, 4% of the rows
+// violated: FP64 9000 x 1000 (72 MB) 44.8 and 41.9, 9000 x 2000 55.4 and 56.3,
+// 9000 x 18000 224 and 265; BF16 17000 x 40000, whose tile rows have 11 KiB,
+// 322 and 303, 30000 x 40000 (14.6 KiB) 422 and 436; with a third violated
+// FP64 9000 x 18000 230 and 328, 14000 x 28000 497 and 691).
+constexpr int64_t kRelayMinBytes = int64_t(128) << 20;
+constexpr int64_t kRelayMinTileBytes = 14 * 1024;
 constexpr int64_t kMaxBandRows = 4096;  // rows per band of the split-row form (its row list)
 
 // Built-in choice of the fused sweep's shape, by storage type and padded row
@@ -375,6 +392,18 @@ bool translation_possible(const modap_ctx *c) { return c->vpend_maybe || (c->V &
 
 int reduce_grid(const modap_ctx *c) { return (int)((c->n + 63) / 64); }
 
+size_t relay_word_bytes(const modap_ctx *c) {
+    return sizeof(uint64_t) * (size_t)c->relay_bands * (size_t)c->relay_tiles * (kRelayRing * 4);
+}
+
+// Longest wait of a resident launch at its grid barrier, and of a long-row
+// sweep for a peer's dot product, in ticks of the 100 MHz constant clock.
+constexpr int64_t kTimeoutTicks = 100000000;   // one second
+int64_t timeout_ticks() {
+    const char *e = std::getenv("MODAP_RESIDENT_TIMEOUT_TICKS");
+    return e ? std::atoll(e) : kTimeoutTicks;
+}
+
 int last_slot(const modap_ctx *c) { return (int)((c->jn - 1) & 1); }
 
 Decide decide_params(const modap_params *p, int track) {
@@ -413,8 +442,22 @@ SweepArgs sweep_args(modap_ctx *c) {
     return a;
 }
 
+// The one-read form of long rows serves the built-in choice of the split-row
+// form.  Its launch is cooperative and its rows are numbered by the host, so a
+// stream under capture takes the two phases.
+bool use_relay(const modap_ctx *c) {
+    if (!c->relay_ok || c->tile_forced || !c->skern) return false;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return cap == hipStreamCaptureStatusNone;
+}
+
 // Launch the sweep of the configured form (events: start/end of its kernels).
 modap_status launch_sweep(modap_ctx *c, const SweepArgs &a, bool hv, hipEvent_t e0, hipEvent_t e1) {
+    c->relay_now = use_relay(c);
     if (!c->skern) {
         HIP_TRY(c, (hv ? c->kern_v : c->kern_nov)->launch(a, c->tile.grid, c->stream, e0, e1));
         return MODAP_OK;
@@ -441,6 +484,26 @@ modap_status launch_sweep(modap_ctx *c, const SweepArgs &a, bool hv, hipEvent_t 
     s.dmax_part = c->dmax_part;
     s.binf_part = c->binf_part;
     if (e0) HIP_TRY(c, hipEventRecord(e0, c->stream));
+    if (c->relay_now) {
+        // numbers of rows are used once; long before they come round the words start afresh
+        if (c->relay_base > 0xf0000000u) {
+            HIP_TRY(c, hipMemsetAsync(c->relay_words, 0, relay_word_bytes(c), c->stream));
+            c->relay_base = 1;
+        }
+        RelayArgs r{};
+        s.ntiles = c->relay_tiles;
+        s.rows_per_band = c->relay_rows;
+        s.ldPart = c->relay_ldPart;
+        r.s = s;
+        r.tile = c->relay_tile;
+        r.words = c->relay_words;
+        r.base = c->relay_base;
+        r.timeout_ticks = timeout_ticks();
+        HIP_TRY(c, c->skern->relay(r, c->relay_bands * c->relay_tiles, hv, c->stream));
+        c->relay_base += (uint32_t)c->relay_rows;
+        if (e1) HIP_TRY(c, hipEventRecord(e1, c->stream));
+        return MODAP_OK;
+    }
     HIP_TRY(c, c->skern->dot(s, c->tile.grid, c->ntiles, hv, c->stream));
     HIP_TRY(c, c->skern->finish(s, c->finish_blocks, hv, c->stream));
     HIP_TRY(c, c->skern->axpy(s, c->tile.grid, c->ntiles, c->stream));
@@ -451,9 +514,9 @@ modap_status launch_sweep(modap_ctx *c, const SweepArgs &a, bool hv, hipEvent_t 
 ReduceArgs reduce_args(modap_ctx *c) {
     ReduceArgs r{};
     r.part = c->part;
-    r.ldPart = c->ldPart;
-    r.G = c->tile.grid;
-    r.Gs = c->skern ? c->finish_blocks : c->tile.grid;
+    r.ldPart = c->relay_now ? c->relay_ldPart : c->ldPart;
+    r.G = c->relay_now ? c->relay_bands : c->tile.grid;
+    r.Gs = c->relay_now ? c->relay_bands : c->skern ? c->finish_blocks : c->tile.grid;
     r.acc_f64 = c->dt == 0;
     r.n = c->n;
     r.ldA = c->ldA;
@@ -599,6 +662,11 @@ modap_status enqueue_settle(modap_ctx *c, const modap_params *p, int track) {
     return MODAP_OK;
 }
 
+modap_status fault_status(modap_ctx *c) {
+    return fail(c, MODAP_E_DEVICE,
+                "a launch gave up waiting for its other workgroups; the context's data are void until set_system");
+}
+
 // Wait for everything queued and read the committed state (and, for a query,
 // up to two vectors of doubles to host memory).
 modap_status read_back(modap_ctx *c, State *out, const double *src0 = nullptr, double *dst0 = nullptr, int64_t n0 = 0,
@@ -628,10 +696,7 @@ modap_status read_back(modap_ctx *c, State *out, const double *src0 = nullptr, d
         if (n1) std::memcpy(dst1, c->rb.buf + n0, sizeof(double) * (size_t)n1);
     }
     *out = c->rb.view->st;
-    if (c->rb.view->fault)
-        return fail(c, MODAP_E_DEVICE,
-                    "a resident launch gave up waiting at a grid barrier; the context's data are void until set_system");
-    return MODAP_OK;
+    return c->rb.view->fault ? fault_status(c) : MODAP_OK;
 }
 
 void fill_stats(modap_stats *o, const State &k) {
@@ -690,6 +755,8 @@ void release_resident(modap_ctx *c) {
 
 void release_system(modap_ctx *c) {
     free_dev(c->cert);
+    free_dev(c->relay_words);
+    c->relay_ok = false;
     release_resident(c);
     free_dev(c->bref);
     free_dev(c->wsum);
@@ -726,7 +793,6 @@ modap_status launch_scatter(modap_ctx *c, int64_t k, const int64_t *rows, const 
 // workgroups lengthen the barrier).
 constexpr int64_t kResidentBand = 96 * 1024;
 constexpr int64_t kResidentRows = 32;
-constexpr int64_t kResidentTimeoutTicks = 100000000;   // one second of the 100 MHz constant clock
 
 modap_status plan_resident(modap_ctx *c) {
     release_resident(c);
@@ -755,6 +821,44 @@ modap_status plan_resident(modap_ctx *c) {
     c->res_ldR = (int)ldR;
     c->res_lds = lds;
     c->res_ok = true;
+    return MODAP_OK;
+}
+
+// The one-read form of long rows (sweep_relay.hpp): one workgroup per CU, the
+// columns in tiles of equal width (a multiple of 128 bytes), as many bands of
+// rows as CUs remain per tile.
+modap_status plan_relay(modap_ctx *c) {
+    c->relay_ok = false;
+    modap_tile t{};
+    choose_shape(c->dt, c->ldA, c->m, c->cu_count, &t);
+    if (t.kind != 1 || c->m * c->ldA * (int64_t)c->es < kRelayMinBytes) return MODAP_OK;
+    const int64_t most = relay_tile(c->dt), line = 128 / (int64_t)c->es;
+    const int64_t tiles = (c->ldA + most - 1) / most;
+    if (tiles > kRelayMaxTiles || tiles > c->cu_count || c->ldA / tiles * (int64_t)c->es < kRelayMinTileBytes)
+        return MODAP_OK;
+    int per_cu = 0;
+    const void *f = split_for(c->dt)->relay_fn;
+    if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)relay_hold(c->dt)) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, kRelayThreads + 128, relay_hold(c->dt)) != hipSuccess ||
+        per_cu < 1) {
+        (void)hipGetLastError();
+        return MODAP_OK;
+    }
+    int64_t bands = c->cu_count / tiles;
+    const int64_t rows = (c->m + bands - 1) / bands;
+    bands = (c->m + rows - 1) / rows;
+    c->relay_tiles = (int)tiles;
+    c->relay_tile = std::min(most, ((c->ldA + tiles - 1) / tiles + line - 1) / line * line);
+    c->relay_rows = rows;
+    c->relay_bands = (int)bands;
+    c->relay_ldPart = (c->ldA + 63) / 64 * 64;
+    modap_status st;
+    if ((st = ensure_part(c, (size_t)bands * (size_t)c->relay_ldPart * acc_size(c->dt)))) return st;
+    if ((st = ensure_scalar_parts(c, (int)bands))) return st;
+    HIP_TRY(c, hipMalloc(&c->relay_words, relay_word_bytes(c)));
+    HIP_TRY(c, hipMemsetAsync(c->relay_words, 0, relay_word_bytes(c), c->stream));
+    c->relay_base = 1;
+    c->relay_ok = true;
     return MODAP_OK;
 }
 
@@ -798,8 +902,7 @@ modap_status launch_resident(modap_ctx *c, const modap_params *p, int track, int
     r.dmax_part = c->res_dmax;
     r.binf_part = c->res_binf;
     r.progress = progress;
-    r.timeout_ticks = kResidentTimeoutTicks;
-    if (const char *e = std::getenv("MODAP_RESIDENT_TIMEOUT_TICKS")) r.timeout_ticks = std::atoll(e);   // tests
+    r.timeout_ticks = timeout_ticks();
     HIP_TRY(c, aux_resident_launch(c->dt, r, c->res_grid, c->res_lds, c->stream));
     c->jn += K;
     *bytes += (double)K * sweep_bytes(c, hv);
@@ -1084,7 +1187,7 @@ modap_status modap_set_system(modap_ctx *c, int64_t m, int64_t n, modap_dtype st
             return st;
         }
     }
-    if ((st = plan_resident(c))) {
+    if ((st = plan_resident(c)) || (st = plan_relay(c))) {
         release_system(c);
         return st;
     }
@@ -1358,6 +1461,7 @@ modap_status modap_eval_sweep(modap_ctx *c, const double *x, double *r, double *
     if ((st = launch_reduce(c, ra))) return st;
     PublishArgs pa{};
     pa.tot = c->tot;
+    pa.fault = &c->ctl->fault;
     if (staged) {
         HIP_TRY(c, c->rb.reserve(c->n + nr));
         pa.src[0] = c->y_eval;
@@ -1375,6 +1479,7 @@ modap_status modap_eval_sweep(modap_ctx *c, const double *x, double *r, double *
         std::memcpy(y, c->rb.buf, sizeof(double) * (size_t)c->n);
         if (r) std::memcpy(r, c->rb.buf + c->n, sizeof(double) * (size_t)c->m);
     }
+    if (c->rb.view->fault) return fault_status(c);
     const Totals to = c->rb.view->tot;
     if (h) *h = to.h;
     if (max_viol) *max_viol = to.dmax;
@@ -1503,7 +1608,7 @@ modap_status modap_autotune(modap_ctx *c, int reps, modap_tile *best) {
         (void)configure(c, keep);
         return st;
     }
-    c->tile_forced = true;
+    if (c->tile.kind == 0) c->tile_forced = true;   // (rows too long for a one-pass shape: nothing was timed)
     cache_store(c, c->tile);
     if (best) *best = c->tile;
     return MODAP_OK;

@@ -27,6 +27,7 @@ const SweepKernel *sweep_kernels_1(int *count);
 const SweepKernel *sweep_kernels_2(int *count);
 
 struct SplitArgs;
+struct RelayArgs;
 // Split-row two-phase kernels of one storage type (workgroup of 256, C chunks
 // per column tile).
 struct SplitKernels {
@@ -36,6 +37,9 @@ struct SplitKernels {
     hipError_t (*dot)(const SplitArgs &, int bands, int tiles, bool has_v, hipStream_t);
     hipError_t (*finish)(const SplitArgs &, int blocks, bool has_v, hipStream_t);
     hipError_t (*axpy)(const SplitArgs &, int bands, int tiles, hipStream_t);
+    // the one-read form (sweep_relay.hpp): cooperative launch, and its kernel
+    hipError_t (*relay)(const RelayArgs &, int grid, bool has_v, hipStream_t);
+    const void *relay_fn;
 };
 const SplitKernels *split_kernels_0();
 const SplitKernels *split_kernels_1();
