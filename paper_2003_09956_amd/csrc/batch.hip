@@ -80,15 +80,12 @@ struct modap_batch {
     bool dirty = true;
     std::vector<int32_t> order;            // alive system ids in table order
     std::vector<BatchSys> h_sys;
-    std::vector<int32_t> h_item_sys;
-    std::vector<int32_t> h_item_order;     // items by decreasing size (queue order)
+    std::vector<BatchItem> h_items;        // by decreasing size (queue order)
     std::vector<BatchCol> h_cols;
     BatchSys *d_sys = nullptr;
     size_t sys_cap = 0;
-    int32_t *d_item_sys = nullptr;
-    size_t item_cap = 0;
-    int32_t *d_item_order = nullptr;
-    size_t order_cap = 0;
+    BatchItem *d_items = nullptr;
+    size_t item_cap = 0, prt_cap = 0;
     BatchCol *d_cols = nullptr;
     size_t cols_cap = 0;
     void *part = nullptr;
@@ -206,9 +203,11 @@ modap_status ensure_bytes(modap_batch *c, unsigned char *&p, size_t &cap, size_t
     return MODAP_OK;
 }
 
-int64_t rows_per_item(const modap_batch *c, const BSys &s) {
-    return plan_rows_per_item(s.m, s.ldA, (int64_t)c->es, c->tile.item_kib[bucket_of(s.C)], c->tile.min_items,
-                              kBatchWaves);
+// A system's cut: the unit is the rows that the wavefronts of a workgroup have
+// in flight (see batch_item).
+BatchCut cut_of(const modap_batch *c, const BSys &s, int32_t rpw, int32_t chunks, const modap_batch_tile &t) {
+    return plan_cut(s.m, s.ldA, (int64_t)c->es, t.item_kib[bucket_of(s.C)], t.min_items,
+                    batch_depth(rpw, chunks) * kBatchWaves * rpw, kGroupCells);
 }
 
 const void *sweep_fn(int dt);
@@ -218,10 +217,22 @@ modap_status rebuild(modap_batch *c) {
     HIP_TRY(c, hipStreamSynchronize(c->stream));  // the previous tables may still be read
     c->order.clear();
     c->h_sys.clear();
-    c->h_item_sys.clear();
-    std::vector<int64_t> item_bytes;
+    c->h_items.clear();
     c->h_cols.clear();
-    int64_t items = 0, part = 0;
+    // persistent grid: as many workgroups as are resident at once (two per CU
+    // for FP32 and FP64 storage, one for BF16) unless tuned.  Measured on the
+    // 512-system FP32 families: the mix 6.40 against 6.28 TB/s at one per CU,
+    // the n = 256 family (short rows) 4.95 against 3.87 TB/s.
+    if (c->per_cu == 0 &&
+        (hipOccupancyMaxActiveBlocksPerMultiprocessor(&c->per_cu, sweep_fn(c->dt), 256, 0) != hipSuccess ||
+         c->per_cu < 1))
+        c->per_cu = 1;
+    c->grid = c->tile.grid > 0 ? c->tile.grid : c->cu_count * c->per_cu;
+    int64_t all_bytes = 0;
+    for (const BSys &s : c->sys)
+        if (s.alive) all_bytes += s.m * s.ldA * (int64_t)c->es;
+    std::vector<int64_t> item_bytes;
+    int64_t parts = 0, part = 0;
     double bytes = 0.0;
     for (size_t id = 0; id < c->sys.size(); ++id) {
         const BSys &s = c->sys[id];
@@ -244,46 +255,55 @@ modap_status rebuild(modap_batch *c) {
         d.ynp = s.ynp;
         d.R = (int32_t)((s.n + 63) / 64);
         kernel_form(c->dt, s, &d.RPW, &d.C);
-        d.rows_per_item = rows_per_item(c, s);
-        d.item0 = items;
-        d.nitems = (s.m + d.rows_per_item - 1) / d.rows_per_item;
+        const BatchCut cut = cut_of(c, s, d.RPW, d.C, c->tile);
+        const int64_t row_bytes = s.ldA * (int64_t)c->es;
+        const int64_t ncells = (s.m + cut.rows_per_cell - 1) / cut.rows_per_cell;
+        const int64_t per_item = plan_cells_per_item(cut, row_bytes, all_bytes, c->grid);
+        d.rows_per_cell = cut.rows_per_cell;
+        d.G = cut.cells;
+        d.grouped = per_item == cut.cells;
+        d.prt0 = parts;
+        d.nprt = d.grouped ? (ncells + cut.cells - 1) / cut.cells : ncells;
         d.part0 = part;
         const int32_t idx = (int32_t)c->h_sys.size();
-        for (int64_t q = 0; q < d.nitems; ++q) {
-            c->h_item_sys.push_back(idx);
-            const int64_t rows = std::min(d.rows_per_item, s.m - q * d.rows_per_item);
-            item_bytes.push_back(rows * s.ldA * (int64_t)c->es);
+        for (int64_t q = 0; q < ncells; q += per_item) {
+            const int64_t count = std::min(per_item, ncells - q);
+            c->h_items.push_back(BatchItem{idx, (int32_t)q, (int32_t)count, (int32_t)(d.grouped ? q / per_item : q)});
+            item_bytes.push_back(std::min(count * d.rows_per_cell, s.m - q * d.rows_per_cell) * row_bytes);
         }
         for (int32_t blk = 0; blk < d.R; ++blk) c->h_cols.push_back(BatchCol{idx, blk});
-        items += d.nitems;
-        part += d.nitems * s.ldA;
+        parts += d.nprt;
+        part += d.nprt * s.ldA;
         bytes += (double)s.m * (double)s.n * (double)c->es + 24.0 * (double)s.m;
         c->h_sys.push_back(d);
         c->order.push_back((int32_t)id);
     }
+    const size_t items = c->h_items.size();
     c->nitems = (int)items;
     c->bytes_per_iter = bytes;
     // hand out the largest items first (ties in item order): the workgroups
     // then end on small items and finish close together
-    c->h_item_order.resize((size_t)items);
-    for (int64_t q = 0; q < items; ++q) c->h_item_order[(size_t)q] = (int32_t)q;
-    std::stable_sort(c->h_item_order.begin(), c->h_item_order.end(),
-                     [&](int32_t u, int32_t v) { return item_bytes[(size_t)u] > item_bytes[(size_t)v]; });
+    {
+        std::vector<int32_t> order(items);
+        for (size_t q = 0; q < items; ++q) order[q] = (int32_t)q;
+        std::stable_sort(order.begin(), order.end(),
+                         [&](int32_t u, int32_t v) { return item_bytes[(size_t)u] > item_bytes[(size_t)v]; });
+        std::vector<BatchItem> sorted(items);
+        for (size_t q = 0; q < items; ++q) sorted[q] = c->h_items[(size_t)order[q]];
+        c->h_items.swap(sorted);
+    }
     modap_status st;
     if ((st = ensure_buf(c, c->d_sys, c->sys_cap, std::max<size_t>(1, c->h_sys.size())))) return st;
-    size_t cap = c->item_cap;
-    if ((st = ensure_buf(c, c->d_item_sys, cap, std::max<size_t>(1, (size_t)items)))) return st;
-    if (cap != c->item_cap) {
-        size_t c2 = 0, c3 = 0, c4 = 0;
-        free_dev(c->h_part);
+    size_t cap = c->prt_cap;
+    if ((st = ensure_buf(c, c->h_part, cap, std::max<size_t>(1, (size_t)parts)))) return st;
+    if (cap != c->prt_cap) {
+        size_t c3 = 0, c4 = 0;
         free_dev(c->dmax_part);
         free_dev(c->binf_part);
-        if ((st = ensure_buf(c, c->h_part, c2, cap)) || (st = ensure_buf(c, c->dmax_part, c3, cap)) ||
-            (st = ensure_buf(c, c->binf_part, c4, cap)))
-            return st;
-        c->item_cap = cap;
+        if ((st = ensure_buf(c, c->dmax_part, c3, cap)) || (st = ensure_buf(c, c->binf_part, c4, cap))) return st;
+        c->prt_cap = cap;
     }
-    if ((st = ensure_buf(c, c->d_item_order, c->order_cap, std::max<size_t>(1, (size_t)items)))) return st;
+    if ((st = ensure_buf(c, c->d_items, c->item_cap, std::max<size_t>(1, items)))) return st;
     if ((st = ensure_buf(c, c->d_cols, c->cols_cap, std::max<size_t>(1, c->h_cols.size())))) return st;
     const size_t pbytes = std::max<size_t>(16, (size_t)part * acc_size(c->dt));
     if (pbytes > c->part_bytes) {
@@ -294,22 +314,11 @@ modap_status rebuild(modap_batch *c) {
     if (!c->h_sys.empty()) {
         HIP_TRY(c, hipMemcpyAsync(c->d_sys, c->h_sys.data(), sizeof(BatchSys) * c->h_sys.size(),
                                   hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(c, hipMemcpyAsync(c->d_item_sys, c->h_item_sys.data(), sizeof(int32_t) * c->h_item_sys.size(),
-                                  hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(c, hipMemcpyAsync(c->d_item_order, c->h_item_order.data(),
-                                  sizeof(int32_t) * c->h_item_order.size(), hipMemcpyHostToDevice, c->stream));
+        HIP_TRY(c, hipMemcpyAsync(c->d_items, c->h_items.data(), sizeof(BatchItem) * items, hipMemcpyHostToDevice,
+                                  c->stream));
         HIP_TRY(c, hipMemcpyAsync(c->d_cols, c->h_cols.data(), sizeof(BatchCol) * c->h_cols.size(),
                                   hipMemcpyHostToDevice, c->stream));
     }
-    // persistent grid: as many workgroups as are resident at once (two per CU
-    // for FP32 and FP64 storage, one for BF16) unless tuned.  Measured on the
-    // 512-system FP32 families: the mix 6.40 against 6.28 TB/s at one per CU,
-    // the n = 256 family (short rows) 4.95 against 3.87 TB/s.
-    if (c->per_cu == 0 &&
-        (hipOccupancyMaxActiveBlocksPerMultiprocessor(&c->per_cu, sweep_fn(c->dt), 256, 0) != hipSuccess ||
-         c->per_cu < 1))
-        c->per_cu = 1;
-    c->grid = c->tile.grid > 0 ? c->tile.grid : c->cu_count * c->per_cu;
     c->grid = std::max(1, std::min(c->grid, std::max(1, c->nitems)));
     c->dirty = false;
     return MODAP_OK;
@@ -320,8 +329,7 @@ BatchArgs batch_args(modap_batch *c) {
     a.sys = c->d_sys;
     a.nsys = (int32_t)c->h_sys.size();
     a.nitems = c->nitems;
-    a.item_sys = c->d_item_sys;
-    a.item_order = c->d_item_order;
+    a.items = c->d_items;
     a.part = c->part;
     a.h_part = c->h_part;
     a.dmax_part = c->dmax_part;
@@ -630,8 +638,7 @@ void modap_batch_destroy(modap_batch *c) {
     (void)hipStreamSynchronize(c->stream);
     for (BSys &s : c->sys) release_sys(s);
     free_dev(c->d_sys);
-    free_dev(c->d_item_sys);
-    free_dev(c->d_item_order);
+    free_dev(c->d_items);
     free_dev(c->d_cols);
     free_dev(c->part);
     free_dev(c->h_part);
@@ -1097,11 +1104,20 @@ modap_status modap_batch_autotune(modap_batch *c, int reps, modap_batch_tile *be
     // the cut of every live system under a tile: a candidate that cuts them
     // all as the incumbent does is the same work, and is not timed (its
     // timing could only differ by noise)
-    auto cut_of = [&](const modap_batch_tile &t) {
+    int64_t total = 0;
+    for (const BSys &s : c->sys)
+        if (s.alive) total += s.m * s.ldA * (int64_t)c->es;
+    auto all_cuts = [&](const modap_batch_tile &t) {
         std::vector<int64_t> v;
+        const int64_t grid = t.grid > 0 ? t.grid : c->cu_count * std::max(1, c->per_cu);
         for (const BSys &s : c->sys)
-            if (s.alive) v.push_back(plan_rows_per_item(s.m, s.ldA, (int64_t)c->es, t.item_kib[bucket_of(s.C)],
-                                                         t.min_items, kBatchWaves));
+            if (s.alive) {
+                int32_t rpw = 1, chunks = 1;
+                kernel_form(c->dt, s, &rpw, &chunks);
+                const BatchCut cut = cut_of(c, s, rpw, chunks, t);
+                v.insert(v.end(), {cut.rows_per_cell, cut.cells,
+                                   plan_cells_per_item(cut, s.ldA * (int64_t)c->es, total, grid)});
+            }
         return v;
     };
     // a work item costs a few microseconds beyond its rows (queue, state,
@@ -1114,18 +1130,18 @@ modap_status modap_batch_autotune(modap_batch *c, int reps, modap_batch_tile *be
             modap_status s2;
             if ((s2 = time_tile(cur, &win))) return s2;
             int pick = cur.item_kib[q];
-            std::vector<int64_t> cut = cut_of(cur);
+            std::vector<int64_t> cut = all_cuts(cur);
             for (int kib : sizes) {
                 if (kib == cur.item_kib[q]) continue;
                 modap_batch_tile t = cur;
                 t.item_kib[q] = kib;
-                if (cut_of(t) == cut) continue;
+                if (all_cuts(t) == cut) continue;
                 float ms = 0.f;
                 if ((s2 = time_tile(t, &ms))) return s2;
                 if (ms < win * kMargin) {
                     win = ms;
                     pick = kib;
-                    cut = cut_of(t);
+                    cut = all_cuts(t);
                 }
             }
             cur.item_kib[q] = pick;
@@ -1150,18 +1166,18 @@ modap_status modap_batch_autotune(modap_batch *c, int reps, modap_batch_tile *be
         float win = 0.f;
         if ((st = time_tile(lifted, &win))) return st;
         int pick = inc;
-        std::vector<int64_t> cut = cut_of(lifted);
+        std::vector<int64_t> cut = all_cuts(lifted);
         for (int mi : {1, 2, 4, 8, 16}) {
             if (mi == inc) continue;
             modap_batch_tile t = lifted;
             t.min_items = mi;
-            if (cut_of(t) == cut) continue;
+            if (all_cuts(t) == cut) continue;
             float ms = 0.f;
             if ((st = time_tile(t, &ms))) return st;
             if (ms < win * kMargin) {
                 win = ms;
                 pick = mi;
-                cut = cut_of(t);
+                cut = all_cuts(t);
             }
         }
         if (pick != inc) {

@@ -12,12 +12,14 @@
 //                 fourth row of the band; the item's x and v are staged in
 //                 LDS and each lane keeps C 16-byte chunks of its partial y in
 //                 registers, C = 1, 2, 4 or 8 chosen per system from its row
-//                 length.  Each item writes
-//                 its own partial y and scalars, so a system's result does not
-//                 depend on which workgroup took which item, nor on the other
-//                 systems in the batch.
-//   reduce_batch  one workgroup per 64 columns of a system: the system's item
-//                 partials summed in item order, the previous step made
+//                 length.  The sums of y are cut into cells and groups of
+//                 cells that depend on the system alone; an item is a group or
+//                 some of its cells, and sums are formed in the same order
+//                 either way, so a system's result does not depend on which
+//                 workgroup took which item, nor on the other systems in the
+//                 batch.
+//   reduce_batch  one workgroup per 64 columns of a system: the system's
+//                 partials summed in order, the previous step made
 //                 permanent in x, and the next sweep's working vectors.
 //
 // The decision on a check is taken, as in the single-system library, by the
@@ -49,10 +51,20 @@ struct BatchSys {
     int32_t R;              // 64-column blocks: ceil(n/64)
     int32_t C;              // 16-byte chunks per lane: (64/RPW)*VEC*C >= ldA
     int32_t RPW;            // rows a wavefront sweeps at once: 1, or 4 (16 lanes per row)
-    int32_t pad;
-    int64_t item0, nitems;  // the system's work items
-    int64_t part0;          // Acc offset of the first item's partial y (stride ldA)
-    int64_t rows_per_item;
+    int32_t G;              // cells per group
+    int64_t prt0, nprt;     // the system's partials: one per cell, or one per group (`grouped`)
+    int64_t part0;          // Acc offset of the first partial y (stride ldA)
+    int64_t rows_per_cell;
+    int32_t grouped, pad;
+};
+
+// A work item: consecutive cells of one system, a whole group if the system's
+// partials are by group.
+struct BatchItem {
+    int32_t sys;
+    int32_t cell;           // first cell, counted in the system
+    int32_t count;          // cells
+    int32_t prt;            // first partial, counted in the system
 };
 
 // A 64-column block of one system (one workgroup of the reduction).
@@ -65,12 +77,11 @@ struct BatchArgs {
     const BatchSys *sys;
     int32_t nsys;
     int32_t nitems;
-    const int32_t *item_sys;  // [nitems] the system of each item; a system's items are consecutive
-    const int32_t *item_order;  // [nitems] the item handed out at each queue position
-    void *part;               // per-item partial y
-    int64_t *h_part;          // [nitems]
-    double *dmax_part;        // [nitems]
-    double *binf_part;        // [nitems]
+    const BatchItem *items;   // [nitems] in queue order (largest first)
+    void *part;               // partial y of the cells or groups
+    int64_t *h_part;          // [partials]
+    double *dmax_part;        // [partials]
+    double *binf_part;        // [partials]
     int32_t *queue;           // next item to take; zero before every sweep
     int64_t j;                // index of this iteration (all systems advance together)
     int32_t decide;           // the sweep settles the previous check (all but a call's first)
@@ -82,6 +93,14 @@ struct BatchArgs {
 };
 
 constexpr int kBatchWaves = 4;  // wavefronts per workgroup of sweep_batch
+// Steps of rows in flight per wavefront, by rows per step and chunks per lane.
+// Eight chunks fill the registers with two; rows of up to four chunks take
+// four steps, since one BF16 workgroup a CU with two had 15 KB in flight (128
+// systems of 9 MB: 306 us an iteration with two steps, 234 with four; eight
+// spilled).  The short form gained nothing from four (1500 systems of 0.5 MB:
+// 226 us against 213).
+constexpr int batch_depth(int RPW, int C) { return RPW == 1 && C <= 4 ? 4 : 2; }
+constexpr int kGroupCells = 8;  // most cells of a group
 constexpr int kBatchCmax = 8;   // largest C compiled
 
 // Stage the item's x_j = x_{j-1} - s*y_{j-1} (one rounding) and v in LDS,
@@ -127,96 +146,114 @@ __device__ __forceinline__ void batch_stage(const BatchSys &S, bool apply_v, dou
     }
 }
 
-// End of a work item: the wavefronts' partials of y summed in LDS and
-// written as the item's partial (lanes with `owner` set hold the partial of
-// their columns col_of(c)), and the item's h, dmax and ||b||inf.
+// Hand-over of the wavefronts' partials at the ends of an item's cells.
+struct CellEnd {
+    int arrived;   // partials left in LDS so far: kBatchWaves a cell
+    int summed;    // cells whose partials have been used
+    int64_t h[kBatchWaves];
+    double dmax[kBatchWaves], binf[kBatchWaves];
+};
+
+// End of the item's q-th cell for one wavefront.  It leaves its partial of y
+// (lanes with `owner` set hold that of their columns col_of(c)) and its h,
+// dmax and ||b||inf in its part of the LDS and goes on with the next cell; the
+// last wavefront to arrive sums the columns, (w0 + w2) + (w1 + w3).  A cell
+// that is a partial of its own is written; in a grouped system the sums are
+// added up in LDS in cell order and the group's last cell writes them.  No
+// barrier: a wavefront waits only if another is still in the cell before
+// (that one reaches this cell's end without waiting for anyone but earlier
+// cells, so every wait ends).
 template <int DT, int C, typename ColOf>
-__device__ __forceinline__ void batch_item_end(const BatchArgs &a, const BatchSys &S, int64_t k, int64_t band,
-                                               typename Store<DT>::Acc (&yacc)[C][Store<DT>::VEC], int64_t h,
-                                               double dmax, double binf,
+__device__ __forceinline__ void batch_cell_end(const BatchArgs &a, const BatchSys &S, const BatchItem &it, int q,
+                                               typename Store<DT>::Acc (&yacc)[C][Store<DT>::VEC], int64_t h, double dmax,
+                                               double binf,
                                                typename Store<DT>::Acc (*lds)[kBatchCmax * 64 * Store<DT>::VEC],
-                                               int64_t *hsh, double *dsh, double *bsh, ColOf col_of, bool owner) {
+                                               CellEnd &ce, ColOf col_of, bool owner) {
     using Acc = typename Store<DT>::Acc;
     constexpr int VEC = Store<DT>::VEC;
     constexpr int AV = 16 / (int)sizeof(Acc);
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t ldA = S.ldA;
-    // The wavefronts' partials are summed pairwise in LDS (the staging space
-    // is free once every wavefront has left the row loop):
-    // (w0 + w2) + (w1 + w3); wavefront 0 writes the item's partial.
-    auto put = [&](Acc *dst) {
-        if (!owner) return;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    while (__hip_atomic_load(&ce.summed, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < q) __builtin_amdgcn_s_sleep(1);
+    if (owner) {
 #pragma unroll
         for (int c = 0; c < C; ++c)
 #pragma unroll
             for (int e = 0; e < VEC; e += AV) {
                 uint4 w;
                 __builtin_memcpy(&w, &yacc[c][e], 16);
-                *reinterpret_cast<uint4 *>(dst + col_of(c) + e) = w;
+                *reinterpret_cast<uint4 *>(lds[wave] + col_of(c) + e) = w;
             }
-    };
-    auto add = [&](const Acc *src) {
-#pragma unroll
-        for (int c = 0; c < C; ++c)
-#pragma unroll
-            for (int e = 0; e < VEC; e += AV) {
-                Acc t4[AV];
-                const uint4 u = *reinterpret_cast<const uint4 *>(src + col_of(c) + e);
-                __builtin_memcpy(t4, &u, 16);
-#pragma unroll
-                for (int q = 0; q < AV; ++q) yacc[c][e + q] += t4[q];
-            }
-    };
+    }
     if (lane == 0) {
-        hsh[wave] = h;
-        dsh[wave] = dmax;
-        bsh[wave] = binf;
+        ce.h[wave] = h;
+        ce.dmax[wave] = dmax;
+        ce.binf[wave] = binf;
     }
-    __syncthreads();
-    if (wave >= 2) put(lds[wave - 2]);
-    __syncthreads();
-    if (wave < 2) add(lds[wave]);
-    __syncthreads();
-    if (wave == 1) put(lds[0]);
-    __syncthreads();
-    if (wave == 0 && owner) {
-        add(lds[0]);
-        Acc *part = reinterpret_cast<Acc *>(a.part) + S.part0 + band * ldA;
+    int before = 0;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    if (lane == 0) before = __hip_atomic_fetch_add(&ce.arrived, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_WORKGROUP);
+    before = __builtin_amdgcn_readfirstlane(before);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    if (before != q * kBatchWaves + kBatchWaves - 1) return;
+    const bool add = S.grouped && q > 0, keep = S.grouped && q + 1 < it.count;
+    const int64_t prt = it.prt + (S.grouped ? 0 : q);
+    Acc *part = reinterpret_cast<Acc *>(a.part) + S.part0 + prt * S.ldA;
+    Acc *group = lds[kBatchWaves];
+    for (int col = lane * AV; col < S.ldA; col += 64 * AV) {
+        Acc w[kBatchWaves][AV];
 #pragma unroll
-        for (int c = 0; c < C; ++c) {
-            if (col_of(c) >= ldA) continue;
-#pragma unroll
-            for (int e = 0; e < VEC; e += AV) {
-                uint4 w;
-                __builtin_memcpy(&w, &yacc[c][e], 16);
-                *reinterpret_cast<uint4 *>(part + col_of(c) + e) = w;
-            }
+        for (int g = 0; g < kBatchWaves; ++g) {
+            const uint4 u = *reinterpret_cast<const uint4 *>(lds[g] + col);
+            __builtin_memcpy(w[g], &u, 16);
         }
+        Acc sum[AV];
+#pragma unroll
+        for (int k = 0; k < AV; ++k) sum[k] = (w[0][k] + w[2][k]) + (w[1][k] + w[3][k]);
+        uint4 u;
+        if (add) {
+            Acc g[AV];
+            u = *reinterpret_cast<const uint4 *>(group + col);
+            __builtin_memcpy(g, &u, 16);
+#pragma unroll
+            for (int k = 0; k < AV; ++k) sum[k] = g[k] + sum[k];
+        }
+        __builtin_memcpy(&u, sum, 16);
+        if (keep)
+            *reinterpret_cast<uint4 *>(group + col) = u;
+        else
+            store_global(reinterpret_cast<uint4 *>(part + col), u);
     }
-    if (tid == 0) {
+    if (lane == 0 && !keep) {
         int64_t hh = 0;
         double dd = 0.0, bm = 0.0;
         for (int g = 0; g < kBatchWaves; ++g) {
-            hh += hsh[g];
-            dd = max_nan(dd, dsh[g]);
-            bm = max_nan(bm, bsh[g]);
+            hh += ce.h[g];
+            dd = max_nan(dd, ce.dmax[g]);
+            bm = max_nan(bm, ce.binf[g]);
         }
-        a.h_part[k] = hh;
-        a.dmax_part[k] = dd;
-        a.binf_part[k] = bm;
+        const int64_t k = S.prt0 + prt;
+        store_global(a.h_part + k, hh);
+        store_global(a.dmax_part + k, dd);
+        store_global(a.binf_part + k, bm);
     }
+    // LDS has been read: the next cell's partials may come
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    if (lane == 0) __hip_atomic_store(&ce.summed, q + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __builtin_amdgcn_s_waitcnt(0);   // the stores are done before rows are counted again
 }
 
-// One work item: rows [r0, r1) of system S, wavefront w taking rows r0+w,
+// One work item: the rows [r0, r1) of its cells, wavefront w taking rows r0+w,
 // r0+w+4, ...  The item's x (with the previous step applied) and v are staged
 // once in LDS, and every lane reads its columns from there for each row; the
-// lane's partial y and two rows in flight stay in registers.  Every branch
-// that guards a barrier is uniform over the workgroup.
+// lane's partial y and the D rows in flight stay in registers.  At the end of a
+// cell the partial is written and starts again from zero, with the next
+// cell's rows already on their way.  Every branch that guards a barrier is
+// uniform over the workgroup.
 template <int DT, int C>
-__device__ void batch_item(const BatchArgs &a, const BatchSys &Sref, int64_t k,
+__device__ void batch_item(const BatchArgs &a, const BatchSys &Sref, const BatchItem it,
                            typename Store<DT>::Acc (*lds)[kBatchCmax * 64 * Store<DT>::VEC],
-                           int64_t *hsh, double *dsh, double *bsh) {
+                           CellEnd &ce) {
     using St = Store<DT>;
     using Acc = typename St::Acc;
     using T = typename St::T;
@@ -224,20 +261,20 @@ __device__ void batch_item(const BatchArgs &a, const BatchSys &Sref, int64_t k,
     constexpr int CW = 64 * VEC;                   // columns per chunk
     constexpr int AV = 16 / (int)sizeof(Acc);      // Acc per 16-byte vector
     constexpr int COLS = C * CW;                   // staged columns (>= ldA)
+    constexpr int D = batch_depth(1, C);           // rows in flight
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform per wavefront
     // The system's fields are read once per item: held in memory, they would
     // be read again after every store the compiler cannot tell apart from them.
     const BatchSys S = Sref;
-    const int64_t band = k - S.item0;
-    const int64_t r0 = band * S.rows_per_item;
-    const int64_t r1 = min(S.m, r0 + S.rows_per_item);
+    const int64_t r0 = it.cell * S.rows_per_cell;
+    const int64_t r1 = min(S.m, r0 + it.count * S.rows_per_cell);
     const int64_t ldA = S.ldA;
     auto col_of = [&](int c) -> int { return c * CW + lane * VEC; };
     const char *Ab = reinterpret_cast<const char *>(S.A);
     const int64_t row_bytes = ldA * (int64_t)sizeof(T);
 
-    // this wavefront's rows; the first two are requested before the state is settled
+    // this wavefront's rows; the first D are requested before the state is settled
     const int64_t nrows = r1 - r0;
     const int64_t nmine = nrows > wave ? (nrows - wave + kBatchWaves - 1) / kBatchWaves : 0;
     auto row_of = [&](int64_t t) -> int64_t { return r0 + wave + t * kBatchWaves; };
@@ -255,13 +292,13 @@ __device__ void batch_item(const BatchArgs &a, const BatchSys &Sref, int64_t k,
 #pragma unroll
         for (int c = 0; c < C; ++c) buf[c] = load_row_vec(rr, (uint32_t)(col_of(c) * (int)sizeof(T)));
     };
-    uint4 bufA[C], bufB[C];
-    double bA, nA, bB, nB;
-    load_row(bufA, bA, nA, 0);
-    load_row(bufB, bB, nB, 1);
+    uint4 buf[D][C];
+    double bi[D], ni[D];
+#pragma unroll
+    for (int i = 0; i < D; ++i) load_row(buf[i], bi[i], ni[i], i);
 
     Pending pd{S.ctl, a.j, S.tot, S.ynp, S.R, a.decide, a.dp, nullptr};
-    const State st = sweep_state(pd, lane, band == 0 && tid == 0);
+    const State st = sweep_state(pd, lane, it.cell == 0 && tid == 0);
     if (a.check_status && st.status != ST_RUNNING) return;
     const bool apply_v = st.vpend_valid || st.v_idx >= 0;
     const double s = a.decide ? st.s : 0.0;
@@ -335,20 +372,37 @@ __device__ void batch_item(const BatchArgs &a, const BatchSys &Sref, int64_t k,
             dmax = r;
         }
     };
+    // The wavefront's steps of a cell are a multiple of D (the cut sees to it),
+    // but for the system's last one: every cell starts with buffer 0.
+    const int64_t spc = S.rows_per_cell / kBatchWaves;
     int64_t t = 0;
-    for (; t + 2 <= nmine; t += 2) {
-        process(bufA, bA, nA, t);   // t is even: never the 64th row of a group
-        load_row(bufA, bA, nA, t + 2);
-        process(bufB, bB, nB, t + 1);
-        if (keep_b && (((t + 2) & 63) == 0 || t + 2 == nmine)) write_b(t + 1);
-        load_row(bufB, bB, nB, t + 3);
+    for (int c = 0; c < it.count; ++c) {
+        const int64_t end = min(nmine, (int64_t)(c + 1) * spc);
+        for (; t + D <= end; t += D)
+#pragma unroll
+            for (int i = 0; i < D; ++i) {
+                process(buf[i], bi[i], ni[i], t + i);
+                // t is a multiple of D: only its last row can end a group of 64
+                if (i == D - 1 && keep_b && (((t + D) & 63) == 0 || t + D == nmine)) write_b(t + D - 1);
+                load_row(buf[i], bi[i], ni[i], t + i + D);
+            }
+        if (t < end) {
+#pragma unroll
+            for (int i = 0; i < D - 1; ++i)
+                if (t + i < end) process(buf[i], bi[i], ni[i], t + i);
+            t = end;
+            if (keep_b) write_b(t - 1);
+        }
+        batch_cell_end<DT, C>(a, S, it, c, yacc, h, dmax, binf, lds + 2, ce, col_of, true);
+#pragma unroll
+        for (int q = 0; q < C; ++q)
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) yacc[q][e] = (Acc)0;
+        if (!S.grouped) {   // a group's counts run on over its cells
+            h = 0;
+            dmax = binf = 0.0;
+        }
     }
-    if (t < nmine) {
-        process(bufA, bA, nA, t);
-        if (keep_b) write_b(t);
-    }
-
-    batch_item_end<DT, C>(a, S, k, band, yacc, h, dmax, binf, lds, hsh, dsh, bsh, col_of, true);
 }
 
 // One work item of a system with short rows (ldA <= 16 VEC C elements): a row
@@ -361,9 +415,9 @@ __device__ void batch_item(const BatchArgs &a, const BatchSys &Sref, int64_t k,
 // form with eight rows of 8 lanes measured no faster, and its registers cost
 // the whole persistent kernel an occupancy level.)
 template <int DT, int C>
-__device__ void batch_item_short(const BatchArgs &a, const BatchSys &Sref, int64_t k,
+__device__ void batch_item_short(const BatchArgs &a, const BatchSys &Sref, const BatchItem it,
                                  typename Store<DT>::Acc (*lds)[kBatchCmax * 64 * Store<DT>::VEC],
-                                 int64_t *hsh, double *dsh, double *bsh) {
+                                 CellEnd &ce) {
     using St = Store<DT>;
     using Acc = typename St::Acc;
     using T = typename St::T;
@@ -372,15 +426,15 @@ __device__ void batch_item_short(const BatchArgs &a, const BatchSys &Sref, int64
     constexpr int CW = LPR * VEC;                  // columns per chunk
     constexpr int AV = 16 / (int)sizeof(Acc);
     constexpr int COLS = C * CW;
+    constexpr int D = batch_depth(RPW, C);         // steps in flight
     constexpr int64_t PER = kBatchWaves * RPW;     // rows per step of the workgroup
     constexpr uint32_t kOutside = 0x80000000u;     // a byte offset past every item
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = lane / LPR, gl = lane % LPR;
     const BatchSys S = Sref;
-    const int64_t band = k - S.item0;
-    const int64_t r0 = band * S.rows_per_item;
-    const int64_t r1 = min(S.m, r0 + S.rows_per_item);
+    const int64_t r0 = it.cell * S.rows_per_cell;
+    const int64_t r1 = min(S.m, r0 + it.count * S.rows_per_cell);
     const int64_t ldA = S.ldA;
     auto col_of = [&](int c) -> int { return c * CW + gl * VEC; };
     const int64_t row_bytes = ldA * (int64_t)sizeof(T);
@@ -402,13 +456,13 @@ __device__ void batch_item_short(const BatchArgs &a, const BatchSys &Sref, int64
         for (int c = 0; c < C; ++c)
             buf[c] = load_row_vec(rr, ok && col_of(c) < ldA ? base + (uint32_t)(col_of(c) * (int)sizeof(T)) : kOutside);
     };
-    uint4 bufA[C], bufB[C];
-    double bA, nA, bB, nB;
-    load_rows(bufA, bA, nA, 0);
-    load_rows(bufB, bB, nB, 1);
+    uint4 buf[D][C];
+    double bi[D], ni[D];
+#pragma unroll
+    for (int i = 0; i < D; ++i) load_rows(buf[i], bi[i], ni[i], i);
 
     Pending pd{S.ctl, a.j, S.tot, S.ynp, S.R, a.decide, a.dp, nullptr};
-    const State st = sweep_state(pd, lane, band == 0 && tid == 0);
+    const State st = sweep_state(pd, lane, it.cell == 0 && tid == 0);
     if (a.check_status && st.status != ST_RUNNING) return;
     const bool apply_v = st.vpend_valid || st.v_idx >= 0;
     batch_stage<DT>(S, apply_v, a.decide ? st.s : 0.0, lds[0], lds[1], COLS);
@@ -486,49 +540,58 @@ __device__ void batch_item_short(const BatchArgs &a, const BatchSys &Sref, int64
             for (int e = 0; e < VEC; ++e) yacc[c][e] = fma(w, av[e], yacc[c][e]);
         }
     };
+    // as in batch_item: a multiple of D steps a cell but for the last one
+    const int64_t spc = S.rows_per_cell / PER;
     int64_t t = 0;
-    for (; t + 2 <= nmine; t += 2) {
-        process(bufA, bA, nA, t);   // t is even: its rows never end a group of 64
-        load_rows(bufA, bA, nA, t + 2);
-        process(bufB, bB, nB, t + 1);
-        if (keep_b && ((((t + 2) * RPW) & 63) == 0 || t + 2 == nmine)) write_b(t + 1);
-        load_rows(bufB, bB, nB, t + 3);
-    }
-    if (t < nmine) {
-        process(bufA, bA, nA, t);
-        if (keep_b) write_b(t);
-    }
-    // the row groups' partials (lanes gl, gl + 16, gl + 32, gl + 48 hold the
-    // same columns), added pairwise: (g0 + g1) + (g2 + g3), the same bits in
-    // every group
+    for (int c = 0; c < it.count; ++c) {
+        const int64_t end = min(nmine, (int64_t)(c + 1) * spc);
+        for (; t + D <= end; t += D)
 #pragma unroll
-    for (int c = 0; c < C; ++c)
+            for (int i = 0; i < D; ++i) {
+                process(buf[i], bi[i], ni[i], t + i);
+                // t is a multiple of D: only its last rows can end a group of 64
+                if (i == D - 1 && keep_b && ((((t + D) * RPW) & 63) == 0 || t + D == nmine)) write_b(t + D - 1);
+                load_rows(buf[i], bi[i], ni[i], t + i + D);
+            }
+        if (t < end) {
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-            Acc v = yacc[c][e];
-#pragma unroll
-            for (int o = LPR; o < 16; o <<= 1) v += __shfl_xor(v, o, 64);
-            if constexpr (LPR <= 16) v = xor_add<16>(v);
-            if constexpr (LPR <= 32) v = xor_add<32>(v);
-            yacc[c][e] = v;
+            for (int i = 0; i < D - 1; ++i)
+                if (t + i < end) process(buf[i], bi[i], ni[i], t + i);
+            t = end;
+            if (keep_b) write_b(t - 1);
         }
-    h = (decltype(h))wave_total((double)h);   // an integer below 2^53: exact
-    dmax = wave_max_nan(dmax);
-    binf = wave_max_nan(binf);
-    batch_item_end<DT, C>(a, S, k, band, yacc, h, dmax, binf, lds, hsh, dsh, bsh, col_of, g == 0);
+        // the row groups' partials (lanes gl, gl + 16, gl + 32, gl + 48 hold the
+        // same columns), added pairwise: (g0 + g1) + (g2 + g3), the same bits in
+        // every group
+#pragma unroll
+        for (int q = 0; q < C; ++q)
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) yacc[q][e] = xor_add<32>(xor_add<16>(yacc[q][e]));
+        const int64_t hw = (int64_t)wave_total((double)h);   // an integer below 2^53: exact
+        const double dw = wave_max_nan(dmax), bw = wave_max_nan(binf);
+        batch_cell_end<DT, C>(a, S, it, c, yacc, hw, dw, bw, lds + 2, ce, col_of, g == 0);
+#pragma unroll
+        for (int q = 0; q < C; ++q)
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) yacc[q][e] = (Acc)0;
+        if (!S.grouped) {   // a group's counts run on over its cells
+            h = 0;
+            dmax = binf = 0.0;
+        }
+    }
 }
 
 // Persistent sweep over every item of the batch.  Each workgroup takes queue
-// positions until they are exhausted (every workgroup reaches the end); a
-// position names an item through item_order, largest items first, so that the
-// last items to start are small ones and the workgroups finish together.
+// positions until they are exhausted (every workgroup reaches the end); the
+// items are in queue order, largest first, so that the last items to start are
+// small ones and the workgroups finish together.
 template <int DT>
 __global__ __launch_bounds__(256) void sweep_batch(const BatchArgs a) {
     using Acc = typename Store<DT>::Acc;
     constexpr int VEC = Store<DT>::VEC;
-    __shared__ __attribute__((aligned(16))) Acc lds[2][kBatchCmax * 64 * VEC];
-    __shared__ int64_t hsh[kBatchWaves];
-    __shared__ double dsh[kBatchWaves], bsh[kBatchWaves];
+    // the item's x and v, the wavefronts' partials of a cell, the group's sum
+    __shared__ __attribute__((aligned(16))) Acc lds[2 + kBatchWaves + 1][kBatchCmax * 64 * VEC];
+    __shared__ CellEnd ce;
     __shared__ int s_pos;
     if (threadIdx.x == 0) s_pos = atomicAdd(a.queue, 1);
     __syncthreads();
@@ -538,21 +601,24 @@ __global__ __launch_bounds__(256) void sweep_batch(const BatchArgs a) {
         // the other threads through LDS after the item's last barrier
         int next = 0;
         __syncthreads();  // every thread has read s_pos
-        if (threadIdx.x == 0) next = atomicAdd(a.queue, 1);
-        const int k = load_global(a.item_order + pos);
-        const BatchSys &S = a.sys[a.item_sys[k]];
+        if (threadIdx.x == 0) {
+            next = atomicAdd(a.queue, 1);
+            ce.arrived = ce.summed = 0;   // seen by all behind the barrier that follows the staging
+        }
+        const BatchItem k = a.items[pos];
+        const BatchSys &S = a.sys[k.sys];
         if (S.RPW == 4) {
             switch (S.C) {
-                case 1: batch_item_short<DT, 1>(a, S, k, lds, hsh, dsh, bsh); break;
-                case 2: batch_item_short<DT, 2>(a, S, k, lds, hsh, dsh, bsh); break;
-                default: batch_item_short<DT, 4>(a, S, k, lds, hsh, dsh, bsh); break;
+                case 1: batch_item_short<DT, 1>(a, S, k, lds, ce); break;
+                case 2: batch_item_short<DT, 2>(a, S, k, lds, ce); break;
+                default: batch_item_short<DT, 4>(a, S, k, lds, ce); break;
             }
         } else {
             switch (S.C) {
-                case 1: batch_item<DT, 1>(a, S, k, lds, hsh, dsh, bsh); break;
-                case 2: batch_item<DT, 2>(a, S, k, lds, hsh, dsh, bsh); break;
-                case 4: batch_item<DT, 4>(a, S, k, lds, hsh, dsh, bsh); break;
-                default: batch_item<DT, 8>(a, S, k, lds, hsh, dsh, bsh); break;
+                case 1: batch_item<DT, 1>(a, S, k, lds, ce); break;
+                case 2: batch_item<DT, 2>(a, S, k, lds, ce); break;
+                case 4: batch_item<DT, 4>(a, S, k, lds, ce); break;
+                default: batch_item<DT, 8>(a, S, k, lds, ce); break;
             }
         }
         if (threadIdx.x == 0) s_pos = next;
@@ -573,7 +639,35 @@ __device__ __forceinline__ int running_systems(const BatchArgs &a, int sl) {
     return w[0] + w[1] + w[2] + w[3];
 }
 
-// Column sums of a system's item partials (item order, FP64), the previous
+// Wavefront w's share of a column: the groups w, w + 4, w + 8, ..., in order,
+// U groups of up to CELLS partials requested together.  A group's cells are
+// added in Acc and in order, as the sweep adds them when it keeps the group.
+template <int CELLS, int U, typename Acc>
+__device__ __forceinline__ double group_sums(const Acc *part, int64_t ldA, int G, int64_t nprt, int64_t col, int wave) {
+    double acc = 0.0;
+    const int64_t ng = (nprt + G - 1) / G;
+    for (int64_t q = wave; q < ng; q += U * kBatchWaves) {
+        Acc v[U][CELLS];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int k = 0; k < CELLS; ++k)
+                v[u][k] = part[min((q + u * kBatchWaves) * G + min(k, G - 1), nprt - 1) * ldA + col];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t g = q + u * kBatchWaves;
+            if (g >= ng) break;
+            Acc s = v[u][0];
+#pragma unroll
+            for (int k = 1; k < CELLS; ++k)
+                if (k < G && g * G + k < nprt) s += v[u][k];
+            acc += (double)s;
+        }
+    }
+    return acc;
+}
+
+// Column sums of a system's groups (in order, FP64), the previous
 // step made permanent in x, and the next sweep's working vectors.  One
 // workgroup per 64-column block; block 0 of a system also forms its totals.
 // Workgroup 0 empties the item queue for the next sweep.  The work of a block
@@ -584,28 +678,29 @@ __device__ __forceinline__ int running_systems(const BatchArgs &a, int sl) {
 // rows, whose index is in the state, wait for it.
 template <typename Acc>
 __global__ __launch_bounds__(256) void reduce_batch(const BatchArgs a, const BatchCol *cols) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) *a.queue = 0;
     // A solve launches one workgroup more: it tells the host, which polls the
     // word, how many systems run on after check j - 1 (settled by this
-    // iteration's sweep), so no counting kernel or copy follows.
-    if (a.progress && blockIdx.x == gridDim.x - 1) {
+    // iteration's sweep), so no counting kernel or copy follows.  What every
+    // workgroup reads alike is read before the first store, so that it comes
+    // in scalar loads: behind that branch the compiler took vector loads, 92
+    // registers for 60, and the reduction of 1500 small systems 21 us for 13.
+    const bool teller = a.progress && blockIdx.x == gridDim.x - 1;
+    const BatchCol cb = cols[teller ? 0 : blockIdx.x];
+    const BatchSys S = a.sys[cb.sys];
+    const State P = S.ctl->st[slot_of(a.j - 1)];
+    const int64_t sched_len = S.ctl->sched_len;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *a.queue = 0;
+    if (teller) {
         const int cnt = running_systems(a, slot_of(a.j - 1));
         if (threadIdx.x == 0)
             __hip_atomic_store(a.progress, ((uint64_t)(a.j + 1) << 32) | (uint32_t)cnt, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_SYSTEM);
         return;
     }
-    const BatchCol cb = cols[blockIdx.x];
-    const BatchSys S = a.sys[cb.sys];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t col = (int64_t)cb.blk * 64 + lane;
     const bool in = col < S.n;
-    const State P = S.ctl->st[slot_of(a.j - 1)];
-    const int64_t sched_len = S.ctl->sched_len;
     const Acc *part = reinterpret_cast<const Acc *>(a.part) + S.part0;
-    double acc = 0.0;
-    if (in)
-        for (int64_t q = wave; q < S.nitems; q += kBatchWaves) acc += (double)part[q * S.ldA + col];
     double xo = 0.0, yprev = 0.0, ws = 0.0, vp = 0.0;
     if (wave == 0 && in) {
         xo = S.x[col];
@@ -616,11 +711,16 @@ __global__ __launch_bounds__(256) void reduce_batch(const BatchArgs a, const Bat
     int64_t h = 0;
     double dm = 0.0, bm = 0.0;
     if (cb.blk == 0)
-        for (int64_t q = tid; q < S.nitems; q += 256) {
-            h += a.h_part[S.item0 + q];
-            dm = max_nan(dm, a.dmax_part[S.item0 + q]);
-            bm = max_nan(bm, a.binf_part[S.item0 + q]);
+        for (int64_t q = tid; q < S.nprt; q += 256) {
+            h += a.h_part[S.prt0 + q];
+            dm = max_nan(dm, a.dmax_part[S.prt0 + q]);
+            bm = max_nan(bm, a.binf_part[S.prt0 + q]);
         }
+    const int G = S.grouped ? 1 : S.G;
+    const double acc = !in                           ? 0.0
+                       : G > 1                       ? group_sums<kGroupCells, 1>(part, S.ldA, G, S.nprt, col, wave)
+                       : S.nprt <= 2 * kBatchWaves ? group_sums<1, 2>(part, S.ldA, 1, S.nprt, col, wave)
+                                                     : group_sums<1, 8>(part, S.ldA, 1, S.nprt, col, wave);
     if (P.status != ST_RUNNING) return;
     __shared__ double sh[kBatchWaves][64];
     sh[wave][lane] = acc;

@@ -12,26 +12,52 @@ namespace modap_host {
 // a wavefront (C = 1, 2, 4, 8).
 inline int bucket_of(int C) { return C == 1 ? 0 : C == 2 ? 1 : C == 4 ? 2 : 3; }
 
-// Rows of one work item of a system: about cap_kib KiB of A, but a small
-// system is still cut into min_items items of at least kMinItemKib KiB, so
-// that a batch of few systems spreads over the device; a multiple of the
-// wavefronts of a workgroup.  The partition depends on the system and the
-// tile only, never on the other systems of the batch.  Eight items per system
-// by default: a batch of few systems needs them to fill the device, while on
-// a batch of many small systems every item costs a few microseconds of its
-// own and fewer measure faster (the autotuner tries 1 to 16).
+// The cut of a system.  It depends on the system and the tile only, never on
+// the other systems of the batch, so a system's results do not depend on them.
+// The rows are cut into groups of about item_kib KiB of A, but into at least
+// eight (min_items, if given) of at least kMinItemKib KiB; a group's partial
+// of y is what the reduction adds up.  A group is cut into up to kGroupCells
+// cells of at least cell_kib KiB (one, if min_items was given), whose partials
+// are added in order -- by the sweep, where an item is a whole group, or by
+// the reduction, where it is less: the same sums either way.  `unit` rows are
+// the step that cells are a multiple of.  A cell's end costs the sweep ten rows
+// of LDS traffic, so its size goes with the element: 256 KiB in 2 and 4 bytes
+// (in 512 KiB a BF16 system of 6.7 MB takes 48 us an iteration for 25), 512
+// KiB in 8 (in 256, 200 systems of 8 MB take 280 us for 271).
 constexpr int64_t kMinItems = 8;
 constexpr int64_t kMinItemKib = 32;
 constexpr int32_t kMaxMinItems = 64;
-inline int64_t plan_rows_per_item(int64_t m, int64_t ldA, int64_t elem_bytes, int32_t cap_kib, int32_t min_items,
-                                  int64_t waves) {
-    const int64_t sys_kib = m * ldA * elem_bytes / 1024;
-    const int64_t cap = std::max<int32_t>(1, cap_kib);
+struct BatchCut {
+    int64_t rows_per_cell;
+    int32_t cells;          // cells per group
+};
+inline int64_t cell_kib(int64_t elem_bytes) { return std::max<int64_t>(256, 64 * elem_bytes); }
+inline BatchCut plan_cut(int64_t m, int64_t ldA, int64_t elem_bytes, int32_t item_kib, int32_t min_items, int64_t unit,
+                         int32_t max_cells) {
+    const int64_t row_bytes = ldA * elem_bytes;
+    const int64_t sys_kib = m * row_bytes / 1024, cap = std::max<int32_t>(1, item_kib);
     const int64_t least = min_items > 0 ? min_items : kMinItems;
     const int64_t kib = std::min(cap, std::max(kMinItemKib, sys_kib / least));
-    int64_t r = kib * 1024 / (ldA * elem_bytes);
-    r = std::max<int64_t>(waves, (r + waves - 1) / waves * waves);
-    return std::min<int64_t>(r, (m + waves - 1) / waves * waves);
+    BatchCut c{0, 1};
+    if (min_items <= 0) c.cells = (int32_t)std::clamp<int64_t>(kib / cell_kib(elem_bytes), 1, max_cells);
+    int64_t r = kib * 1024 / (row_bytes * c.cells);
+    r = std::max(unit, (r + unit - 1) / unit * unit);
+    c.rows_per_cell = std::min(r, (m + unit - 1) / unit * unit);
+    return c;
+}
+
+// Cells of one work item: whole groups in a batch that fills the device with
+// them, fewer cells in a smaller one, so that it has about kItemsPerWorkgroup
+// items for each workgroup of the grid.  Cells that are written one by one
+// spread a small batch over the device (seven BF16 systems of 78 MB in all:
+// 210 us an iteration as 56 groups, 56 as 184 cells), but writing and
+// reading back eight times the partials costs a large one (the 512-system
+// family, 15.8 GB: 2.65 ms a sweep by cells, 2.36 by groups).
+constexpr int64_t kItemsPerWorkgroup = 4;
+inline int64_t plan_cells_per_item(const BatchCut &cut, int64_t row_bytes, int64_t batch_bytes, int64_t grid) {
+    const int64_t want = batch_bytes / std::max<int64_t>(1, grid * kItemsPerWorkgroup);
+    const int64_t cells = std::max<int64_t>(1, want / (cut.rows_per_cell * row_bytes));
+    return 2 * cells > cut.cells ? cut.cells : cells;
 }
 
 // Row form of a system: rows of at most 64 16-byte vectors (C == 1) run four
