@@ -5,6 +5,7 @@
 #pragma once
 
 #include "modap_device.hpp"
+#include "readback.hpp"
 
 namespace modap {
 
@@ -79,12 +80,13 @@ __global__ __launch_bounds__(256) void row_norms(const void *A, int64_t ldA, int
     }
 }
 
-// Raises *flag when any of p[0..count) is NaN or infinite.
-__global__ void check_finite(const double *p, int64_t count, int *flag) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        if (!isfinite(p[i])) atomicOr(flag, 1);
-    }
+// Raises *flag when any of p[0..np) or q[0..nq) is NaN or infinite.
+__global__ void check_finite(const double *p, int64_t np, const double *q, int64_t nq, unsigned long long *flag) {
+    const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    bool bad = false;
+    for (int64_t i = first; i < np; i += step) bad |= !isfinite(p[i]);
+    for (int64_t i = first; i < nq; i += step) bad |= !isfinite(q[i]);
+    if (bad) atomicOr(flag, 1ull);
 }
 
 // Threads of a reduction workgroup.  Measured on the FP32 n = 8192 system
@@ -329,8 +331,9 @@ __global__ void ctl_begin(Ctrl *c, int sl, int64_t max_steps) {
 }
 
 // A fresh state (set_system): both slots.
-__global__ void ctl_init(Ctrl *c) {
+__global__ void ctl_init(Ctrl *c, DataChecks *checks) {
     if (threadIdx.x != 0) return;
+    if (checks) *checks = DataChecks{ULLONG_MAX, 0};
     State s{};
     s.v_idx = -1;
     s.status = ST_RUNNING;
@@ -382,11 +385,58 @@ __global__ __launch_bounds__(1024) void sched_to_vpend(Ctrl *c, int sl, double *
     }
 }
 
-__global__ void ctl_set_drift(Ctrl *c, int sl, int64_t T) {
-    if (threadIdx.x != 0) return;
+__device__ __forceinline__ void start_schedule(Ctrl *c, int sl, int64_t T) {
     c->sched_len = T;
     c->st[sl].sched_pos = 0;
     c->st[sl].v_idx = -1;
+}
+
+__global__ void ctl_set_drift(Ctrl *c, int sl, int64_t T) {
+    if (threadIdx.x == 0) start_schedule(c, sl, T);
+}
+
+// A drift schedule in device memory taken in with one pass: T rows of n at
+// stride ldv copied to rows of ldA (zeros past n) and checked; the last
+// workgroup starts the schedule, or one of no rows if an entry is not finite,
+// and tells the host which.  (Cleared, copied by a copy engine, checked and
+// the flag copied back, behind a free, an allocation and two waits, a schedule
+// of 16 rows of 1000 took 106 us; with this and a kept buffer 17.)  *flag and
+// *arrived are zero between launches.  At most kDriftGroups workgroups: each
+// arrival costs a release to the device (512 of them took 50 us).
+constexpr int kDriftCols = 1024;
+constexpr int kDriftGroups = 128;
+__global__ __launch_bounds__(256) void drift_in(const double *src, int64_t ldv, int64_t n, int64_t T, double *V,
+                                                int64_t ldA, unsigned long long *flag, Ctrl *ctl, int sl,
+                                                HostView *view, uint32_t *arrived, uint32_t seq) {
+    bool bad = false;
+    const int64_t chunks = (ldA + kDriftCols - 1) / kDriftCols;   // a workgroup takes one chunk of a row at a time
+    for (int64_t w = blockIdx.x; w < T * chunks; w += gridDim.x) {
+        const int64_t row = w / chunks, col0 = w % chunks * kDriftCols + threadIdx.x;
+        double v[kDriftCols / 256];
+#pragma unroll
+        for (int k = 0; k < kDriftCols / 256; ++k) {
+            const int64_t col = col0 + k * 256;
+            v[k] = col < n ? src[row * ldv + col] : 0.0;
+        }
+#pragma unroll
+        for (int k = 0; k < kDriftCols / 256; ++k) {
+            const int64_t col = col0 + k * 256;
+            bad |= !isfinite(v[k]);
+            if (col < ldA) V[row * ldA + col] = v[k];
+        }
+    }
+    if (bad) atomicOr(flag, 1ull);
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    if (gridDim.x > 1 &&
+        __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) != gridDim.x - 1)
+        return;
+    __hip_atomic_store(arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long any = atomicExch(flag, 0ull);
+    start_schedule(ctl, sl, any ? 0 : T);
+    view->fault = any != 0;
+    __hip_atomic_store(&view->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Row replacement in place (one workgroup per replaced row): copy the new

@@ -7,16 +7,18 @@
 #include <stdint.h>
 
 #include "modap_device.hpp"
+#include "readback.hpp"
 
 namespace modap {
 
 // ||a_i||^2 of rows [0, m) in FP64; *bad <- min index of a zero or non-finite row.
 hipError_t aux_row_norms(int dt, const void *A, int64_t ldA, int64_t m, int64_t n, double *nu,
                          unsigned long long *bad, hipStream_t s);
-// *flag <- 1 when p[0..count) holds a NaN or infinity.
-hipError_t aux_check_finite(const double *p, int64_t count, int *flag, hipStream_t s);
-// Both state slots fresh (running, no translation pending, no drift).
-hipError_t aux_ctl_init(Ctrl *c, hipStream_t s);
+// *flag <- 1 when p[0..np) or q[0..nq) holds a NaN or infinity.
+hipError_t aux_check_finite(const double *p, int64_t np, const double *q, int64_t nq, unsigned long long *flag,
+                            hipStream_t s);
+// Both state slots fresh (running, no translation pending, no drift), and nothing found by the checks yet.
+hipError_t aux_ctl_init(Ctrl *c, DataChecks *checks, hipStream_t s);
 // Replace k rows in place (see scatter_rows).
 hipError_t aux_scatter_rows(int dt, void *A, int64_t ldA, int64_t m, int64_t n, int64_t k, const int64_t *rows,
                             const void *new_rows, const double *new_b, double *b, double *bref, double *nu, Ctrl *ctl,

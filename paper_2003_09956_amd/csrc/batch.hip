@@ -41,6 +41,7 @@ struct BSys {
     bool alive = false;
     int64_t m = 0, n = 0, ldA = 0;
     void *A = nullptr;
+    void *vectors = nullptr;   // the allocation of everything below but V
     double *b = nullptr, *nu = nullptr, *x = nullptr, *y = nullptr, *vpend = nullptr, *V = nullptr;
     double *bref = nullptr, *wsum = nullptr;   // the data are bref + A wsum (see certify.hpp)
     int64_t T = 0;
@@ -107,8 +108,7 @@ struct modap_batch {
     unsigned char *cert = nullptr, *cert_list = nullptr;
     size_t cert_cap = 0, cert_list_cap = 0;
     modap_host::Readback rb;              // results read back by the host (see readback.hpp)
-    unsigned long long *bad = nullptr;
-    int *flag = nullptr;
+    DataChecks *checks = nullptr;
     void *stage = nullptr;
     size_t stage_bytes = 0;
     std::vector<hipEvent_t> events;
@@ -130,20 +130,9 @@ modap_status b_from_device(modap_batch *c, void *dst, const void *src, size_t by
 
 void release_sys(BSys &s) {
     free_dev(s.A);
-    free_dev(s.b);
-    free_dev(s.nu);
-    free_dev(s.x);
-    free_dev(s.y);
-    free_dev(s.vpend);
-    free_dev(s.bref);
-    free_dev(s.wsum);
+    free_dev(s.vectors);
     free_dev(s.V);
-    free_dev(s.work);
-    free_dev(s.ctl);
-    free_dev(s.tot);
-    free_dev(s.ynp);
-    s.alive = false;
-    s.T = 0;
+    s = BSys{};
 }
 
 BSys *find_sys(modap_batch *c, int64_t id) {
@@ -588,6 +577,110 @@ modap_status certify_stopped(modap_batch *c, const modap_params *p, int *count, 
     return read_states(c, states);
 }
 
+// A new system of the batch.  `owned`, if given, is A in device memory with
+// rows of the padded length (zeros past n); it becomes the batch's on success.
+modap_status add_system(modap_batch *c, int64_t m, int64_t n, const void *A, int64_t lda, const double *b,
+                        const double *x0, int on_dev, void *owned, int64_t *id) {
+    if (!c) return MODAP_E_INVAL;
+    if (!id) return fail(c, MODAP_E_INVAL, "id is NULL");
+    const char *msg = nullptr;
+    if (check_system(m, n, lda, A, b, c->dt, &msg)) return fail(c, MODAP_E_INVAL, msg);
+    const int64_t v = vec_elems(c->dt);
+    const int64_t ldA = (n + v - 1) / v * v;
+    if (ldA > max_row(c->dt))
+        return fail(c, MODAP_E_INVAL, "rows longer than the batched sweep covers (" + std::to_string(max_row(c->dt)) +
+                                          " elements): use a single-system context");
+    if (!on_dev) {
+        if (!all_finite(b, m)) return fail(c, MODAP_E_INVAL, "b has a non-finite entry");
+        if (x0 && !all_finite(x0, n)) return fail(c, MODAP_E_INVAL, "x0 has a non-finite entry");
+    }
+    DeviceGuard g(c->device);
+    BSys s;
+    s.m = m;
+    s.n = n;
+    s.ldA = ldA;
+    s.C = chunks_for(c->dt, ldA);
+    const size_t abytes = (size_t)m * (size_t)ldA * c->es;
+    const size_t vbytes = sizeof(double) * (size_t)ldA;
+    const size_t wbytes = 3 * acc_size(c->dt) * (size_t)ldA;
+    auto cleanup = [&](modap_status st) {
+        if (owned) s.A = nullptr;
+        release_sys(s);
+        return st;
+    };
+    Pieces pc;
+    pc.add(s.x, vbytes);
+    pc.add(s.y, vbytes);
+    pc.add(s.vpend, vbytes);
+    pc.add(s.wsum, vbytes);
+    pc.add(s.work, wbytes);
+    const size_t zeros = pc.total;   // everything so far starts as zeros
+    pc.add(s.b, sizeof(double) * m);
+    pc.add(s.bref, sizeof(double) * m);
+    pc.add(s.nu, sizeof(double) * m);
+    pc.add(s.ctl, sizeof(Ctrl));
+    pc.add(s.tot, sizeof(Totals));
+    pc.add(s.ynp, sizeof(double) * (size_t)((n + 63) / 64));
+    hipError_t e = hipSuccess;
+    if (owned) s.A = owned;
+    if ((!owned && (e = hipMalloc(&s.A, abytes)) != hipSuccess) || (e = pc.alloc(s.vectors)) != hipSuccess)
+        return cleanup(hip_fail(c, e, "hipMalloc"));
+    modap_status st = MODAP_OK;
+    auto q = [&](hipError_t r, const char *what) {
+        if (r != hipSuccess && st == MODAP_OK) st = hip_fail(c, r, what);
+    };
+    const hipMemcpyKind kind = on_dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
+    if (!owned) {
+        if (ldA != n) q(hipMemsetAsync(s.A, 0, abytes, c->stream), "hipMemsetAsync");
+        q(hipMemcpy2DAsync(s.A, (size_t)ldA * c->es, A, (size_t)lda * c->es, (size_t)n * c->es, (size_t)m, kind,
+                           c->stream),
+          "hipMemcpy2DAsync");
+    }
+    q(hipMemsetAsync(s.vectors, 0, zeros, c->stream), "hipMemsetAsync");
+    q(hipMemcpyAsync(s.b, b, sizeof(double) * m, kind, c->stream), "copy b");
+    if (x0) q(hipMemcpyAsync(s.x, x0, sizeof(double) * n, kind, c->stream), "copy x0");
+    q(hipMemcpyAsync(s.bref, s.b, sizeof(double) * m, hipMemcpyDeviceToDevice, c->stream), "copy b");
+    q(aux_ctl_init(s.ctl, c->checks, c->stream), "ctl_init launch");
+    q(aux_row_norms(c->dt, s.A, ldA, m, n, s.nu, &c->checks->bad, c->stream), "row_norms launch");
+    if (on_dev) q(aux_check_finite(s.b, m, s.x, n, &c->checks->flag, c->stream), "check_finite launch");
+    DataChecks found{};
+    if (st == MODAP_OK) q(read_checks(c->rb, c->checks, c->stream, &found), "reading the checks");
+    if (st) (void)hipStreamSynchronize(c->stream);   // what was queued may still use the memory
+    if (st) return cleanup(st);
+    if (found.flag) return cleanup(fail(c, MODAP_E_INVAL, "b or x0 has a non-finite entry"));
+    if (found.bad != ULLONG_MAX) return cleanup(fail(c, MODAP_E_ZERO_ROW, "row " + std::to_string(found.bad) + " is zero or not finite"));
+    s.alive = true;
+    // a fresh system's committed state must sit in the batch's slot
+    // (jn-1)&1: ctl_init filled both slots
+    size_t slot = c->sys.size();
+    for (size_t i = 0; i < c->sys.size(); ++i)
+        if (!c->sys[i].alive && !c->sys[i].A) {
+            slot = i;
+            break;
+        }
+    if (slot == c->sys.size()) c->sys.push_back(s);
+    else c->sys[slot] = s;
+    *id = (int64_t)slot;
+    c->dirty = true;
+    c->err.clear();
+    return MODAP_OK;
+}
+
+void fill_stats(const State &k, modap_stats *out) {
+    *out = modap_stats{};
+    out->iters = k.steps;
+    out->sweeps = k.sweeps;
+    out->converged = k.feasible;
+    out->state = k.status;
+    out->max_viol = k.dmax;
+    out->h = k.h;
+    out->y_norm = k.ynorm;
+    out->b_inf = k.binf;
+    out->eps_abs = k.eps_abs;
+    out->certified = k.certified;
+    out->b_drift = k.bdrift;
+}
+
 }  // namespace
 
 // Certificate of the stops of the given systems (used by the server, which
@@ -600,6 +693,27 @@ modap_status modap_batch_certify_ids(modap_batch *c, const modap_params *p, cons
         if (!find_sys(c, ids[q])) return fail(c, MODAP_E_INVAL, "unknown system id");
     if (modap_status st = certify_systems(c, std::vector<int64_t>(ids, ids + count), p)) return st;
     HIP_TRY(c, hipStreamSynchronize(c->stream));
+    return MODAP_OK;
+}
+
+modap_status modap_batch_adopt(modap_batch *c, int64_t m, int64_t n, void *A, const double *b, const double *x0,
+                               int64_t *id) {
+    TraceRange trace_("modap_batch_add");
+    return add_system(c, m, n, A, n, b, x0, 1, A, id);
+}
+
+modap_status modap_batch_states(modap_batch *c, const int64_t *ids, int64_t count, modap_stats *out) {
+    TraceRange trace_("modap_batch_states");
+    if (!c) return MODAP_E_INVAL;
+    DeviceGuard g(c->device);
+    for (int64_t q = 0; q < count; ++q)
+        if (!find_sys(c, ids[q])) return fail(c, MODAP_E_INVAL, "unknown system id");
+    modap_status st;
+    const State *states = nullptr;
+    if ((st = rebuild(c)) || (st = read_states(c, &states))) return st;
+    std::vector<int64_t> at(c->sys.size(), -1);
+    for (size_t k = 0; k < c->order.size(); ++k) at[(size_t)c->order[k]] = (int64_t)k;
+    for (int64_t q = 0; q < count; ++q) fill_stats(states[at[(size_t)ids[q]]], out + q);
     return MODAP_OK;
 }
 
@@ -622,8 +736,7 @@ modap_status modap_batch_create(int device, void *hip_stream, modap_dtype storag
     bool ok = hipGetDeviceProperties(&prop, device) == hipSuccess;
     if (ok) c->cu_count = prop.multiProcessorCount;
     ok = ok && hipMalloc(&c->queue, sizeof(int32_t)) == hipSuccess &&
-         hipMalloc(&c->bad, sizeof(unsigned long long)) == hipSuccess && hipMalloc(&c->flag, sizeof(int)) == hipSuccess &&
-         c->rb.create() == hipSuccess;
+         hipMalloc(&c->checks, sizeof(DataChecks)) == hipSuccess && c->rb.create(c->stream) == hipSuccess;
     if (!ok) {
         modap_batch_destroy(c);
         return MODAP_E_DEVICE;
@@ -649,8 +762,7 @@ void modap_batch_destroy(modap_batch *c) {
     free_dev(c->rhs);
     free_dev(c->cert);
     free_dev(c->cert_list);
-    free_dev(c->bad);
-    free_dev(c->flag);
+    free_dev(c->checks);
     free_dev(c->stage);
     c->rb.destroy();
     for (hipEvent_t e : c->events) (void)hipEventDestroy(e);
@@ -660,93 +772,7 @@ void modap_batch_destroy(modap_batch *c) {
 modap_status modap_batch_add(modap_batch *c, int64_t m, int64_t n, const void *A, int64_t lda, const double *b,
                              const double *x0, int on_dev, int64_t *id) {
     TraceRange trace_("modap_batch_add");
-    if (!c) return MODAP_E_INVAL;
-    if (!id) return fail(c, MODAP_E_INVAL, "id is NULL");
-    const char *msg = nullptr;
-    if (check_system(m, n, lda, A, b, c->dt, &msg)) return fail(c, MODAP_E_INVAL, msg);
-    const int64_t v = vec_elems(c->dt);
-    const int64_t ldA = (n + v - 1) / v * v;
-    if (ldA > max_row(c->dt))
-        return fail(c, MODAP_E_INVAL, "rows longer than the batched sweep covers (" + std::to_string(max_row(c->dt)) +
-                                          " elements): use a single-system context");
-    if (!on_dev) {
-        if (!all_finite(b, m)) return fail(c, MODAP_E_INVAL, "b has a non-finite entry");
-        if (x0 && !all_finite(x0, n)) return fail(c, MODAP_E_INVAL, "x0 has a non-finite entry");
-    }
-    DeviceGuard g(c->device);
-    BSys s;
-    s.m = m;
-    s.n = n;
-    s.ldA = ldA;
-    s.C = chunks_for(c->dt, ldA);
-    const size_t abytes = (size_t)m * (size_t)ldA * c->es;
-    const size_t vbytes = sizeof(double) * (size_t)ldA;
-    const size_t wbytes = 3 * acc_size(c->dt) * (size_t)ldA;
-    auto cleanup = [&](modap_status st) {
-        release_sys(s);
-        return st;
-    };
-    hipError_t e = hipSuccess;
-    if ((e = hipMalloc(&s.A, abytes)) != hipSuccess || (e = hipMalloc(&s.b, sizeof(double) * m)) != hipSuccess ||
-        (e = hipMalloc(&s.nu, sizeof(double) * m)) != hipSuccess || (e = hipMalloc(&s.x, vbytes)) != hipSuccess ||
-        (e = hipMalloc(&s.y, vbytes)) != hipSuccess || (e = hipMalloc(&s.vpend, vbytes)) != hipSuccess ||
-        (e = hipMalloc(&s.wsum, vbytes)) != hipSuccess || (e = hipMalloc(&s.bref, sizeof(double) * m)) != hipSuccess ||
-        (e = hipMalloc(&s.work, wbytes)) != hipSuccess || (e = hipMalloc(&s.ctl, sizeof(Ctrl))) != hipSuccess ||
-        (e = hipMalloc(&s.tot, sizeof(Totals))) != hipSuccess ||
-        (e = hipMalloc(&s.ynp, sizeof(double) * (size_t)((n + 63) / 64))) != hipSuccess)
-        return cleanup(hip_fail(c, e, "hipMalloc"));
-    modap_status st = MODAP_OK;
-    auto q = [&](hipError_t r, const char *what) {
-        if (r != hipSuccess && st == MODAP_OK) st = hip_fail(c, r, what);
-    };
-    if (ldA != n) q(hipMemsetAsync(s.A, 0, abytes, c->stream), "hipMemsetAsync");
-    q(hipMemcpy2DAsync(s.A, (size_t)ldA * c->es, A, (size_t)lda * c->es, (size_t)n * c->es, (size_t)m,
-                       on_dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, c->stream),
-      "hipMemcpy2DAsync");
-    q(hipMemcpyAsync(s.b, b, sizeof(double) * m, on_dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, c->stream),
-      "copy b");
-    q(hipMemsetAsync(s.x, 0, vbytes, c->stream), "hipMemsetAsync");
-    if (x0)
-        q(hipMemcpyAsync(s.x, x0, sizeof(double) * n, on_dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
-                         c->stream),
-          "copy x0");
-    q(hipMemsetAsync(s.y, 0, vbytes, c->stream), "hipMemsetAsync");
-    q(hipMemsetAsync(s.vpend, 0, vbytes, c->stream), "hipMemsetAsync");
-    q(hipMemsetAsync(s.wsum, 0, vbytes, c->stream), "hipMemsetAsync");
-    q(hipMemcpyAsync(s.bref, s.b, sizeof(double) * m, hipMemcpyDeviceToDevice, c->stream), "copy b");
-    q(hipMemsetAsync(s.work, 0, wbytes, c->stream), "hipMemsetAsync");
-    const unsigned long long none = ULLONG_MAX;
-    q(hipMemcpyAsync(c->bad, &none, sizeof none, hipMemcpyHostToDevice, c->stream), "copy");
-    q(hipMemsetAsync(c->flag, 0, sizeof(int), c->stream), "hipMemsetAsync");
-    q(aux_row_norms(c->dt, s.A, ldA, m, n, s.nu, c->bad, c->stream), "row_norms launch");
-    if (on_dev) {
-        q(aux_check_finite(s.b, m, c->flag, c->stream), "check_finite launch");
-        q(aux_check_finite(s.x, n, c->flag, c->stream), "check_finite launch");
-    }
-    q(aux_ctl_init(s.ctl, c->stream), "ctl_init launch");
-    unsigned long long bad = 0;
-    int flag = 0;
-    q(hipMemcpyAsync(&bad, c->bad, sizeof bad, hipMemcpyDeviceToHost, c->stream), "copy");
-    q(hipMemcpyAsync(&flag, c->flag, sizeof flag, hipMemcpyDeviceToHost, c->stream), "copy");
-    q(hipStreamSynchronize(c->stream), "hipStreamSynchronize");
-    if (st) return cleanup(st);
-    if (flag) return cleanup(fail(c, MODAP_E_INVAL, "b or x0 has a non-finite entry"));
-    if (bad != ULLONG_MAX) return cleanup(fail(c, MODAP_E_ZERO_ROW, "row " + std::to_string(bad) + " is zero or not finite"));
-    s.alive = true;
-    // a fresh system's committed state must sit in the batch's slot
-    // (jn-1)&1: ctl_init filled both slots
-    size_t slot = c->sys.size();
-    for (size_t i = 0; i < c->sys.size(); ++i)
-        if (!c->sys[i].alive && !c->sys[i].A) {
-            slot = i;
-            break;
-        }
-    if (slot == c->sys.size()) c->sys.push_back(s);
-    else c->sys[slot] = s;
-    *id = (int64_t)slot;
-    c->dirty = true;
-    c->err.clear();
-    return MODAP_OK;
+    return add_system(c, m, n, A, lda, b, x0, on_dev, nullptr, id);
 }
 
 modap_status modap_batch_remove(modap_batch *c, int64_t id) {
@@ -999,21 +1025,7 @@ modap_status modap_batch_query(modap_batch *c, int64_t id, double *x, double *b,
         if (x) std::memcpy(x, c->rb.buf, sizeof(double) * (size_t)nx);
         if (b) std::memcpy(b, c->rb.buf + nx, sizeof(double) * (size_t)nb);
     }
-    const State k = c->rb.view->st;
-    if (out) {
-        *out = modap_stats{};
-        out->iters = k.steps;
-        out->sweeps = k.sweeps;
-        out->converged = k.feasible;
-        out->state = k.status;
-        out->max_viol = k.dmax;
-        out->h = k.h;
-        out->y_norm = k.ynorm;
-        out->b_inf = k.binf;
-        out->eps_abs = k.eps_abs;
-        out->certified = k.certified;
-        out->b_drift = k.bdrift;
-    }
+    if (out) fill_stats(c->rb.view->st, out);
     return MODAP_OK;
 }
 

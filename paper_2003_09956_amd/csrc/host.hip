@@ -57,10 +57,12 @@ struct modap_ctx {
     void *A = nullptr;
     double *b = nullptr, *nu = nullptr, *x = nullptr, *y = nullptr, *vpend = nullptr;
     double *bref = nullptr;      // [m] right-hand side at zero translation: the data are bref + A wsum
+    void *vectors = nullptr;     // the allocation of every vector of the system
     double *wsum = nullptr;      // [ldA] FP64 sum of the translations applied since the last rebase
     int *claim = nullptr;        // [m] row claims of a device-side replacement (zero between calls)
-    double *V = nullptr;
+    double *V = nullptr;         // [T x ldA] drift schedule, in an allocation of V_cap doubles
     int64_t T = 0;
+    size_t V_cap = 0;
     bool vpend_maybe = false;   // a translation may be pending on the device
     int64_t jn = 0;             // index of the next iteration; state of jn-1 is committed
 
@@ -97,11 +99,11 @@ struct modap_ctx {
     void *work = nullptr;        // [3 x ldA] accumulation type: x, v and y of the next sweep
     void *work_eval = nullptr;
 
+    void *small = nullptr;       // the allocation of ctl, tot and checks
     Ctrl *ctl = nullptr;
     Readback rb;                 // results read back by the host (see readback.hpp)
     double *x_eval = nullptr, *y_eval = nullptr, *r_eval = nullptr;
-    unsigned long long *bad = nullptr;
-    int *flag = nullptr;
+    DataChecks *checks = nullptr;
 
     // staging for host-side update inputs
     void *stage = nullptr;
@@ -758,23 +760,11 @@ void release_system(modap_ctx *c) {
     free_dev(c->relay_words);
     c->relay_ok = false;
     release_resident(c);
-    free_dev(c->bref);
-    free_dev(c->wsum);
-    free_dev(c->claim);
     free_dev(c->A);
+    free_dev(c->vectors);
     free_dev(c->wrow);
-    free_dev(c->b);
-    free_dev(c->nu);
-    free_dev(c->x);
-    free_dev(c->y);
-    free_dev(c->vpend);
     free_dev(c->V);
-    free_dev(c->ynp);
-    free_dev(c->work);
-    free_dev(c->work_eval);
-    free_dev(c->x_eval);
-    free_dev(c->y_eval);
-    free_dev(c->r_eval);
+    c->V_cap = 0;
     c->T = 0;
     c->loaded = false;
 }
@@ -1007,7 +997,121 @@ void cache_store(const modap_ctx *c, const modap_tile &t) {
     std::fclose(f);
 }
 
+// A new system.  `owned`, if given, is A in device memory with rows of the
+// padded length (zeros past n); it becomes the context's on success.
+modap_status set_system(modap_ctx *c, int64_t m, int64_t n, modap_dtype storage, const void *A, int64_t lda,
+                        const double *b, const double *x0, int on_dev, void *owned) {
+    modap_status st = check_ctx(c, false);
+    if (st) return st;
+    const char *msg = nullptr;
+    if ((st = check_system(m, n, lda, A, b, (int)storage, &msg))) return fail(c, st, msg);
+    if (!on_dev) {
+        if (!all_finite(b, m)) return fail(c, MODAP_E_INVAL, "b has a non-finite entry");
+        if (x0 && !all_finite(x0, n)) return fail(c, MODAP_E_INVAL, "x0 has a non-finite entry");
+    }
+    DeviceGuard g(c->device);
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    release_system(c);
+    c->dt = (int)storage;
+    c->es = elem_size(c->dt);
+    c->m = m;
+    c->n = n;
+    const int64_t v = vec_elems(c->dt);
+    c->ldA = (n + v - 1) / v * v;
+    c->vpend_maybe = false;
+    c->jn = 0;
+    const size_t abytes = (size_t)m * (size_t)c->ldA * c->es;
+    struct Adopted {   // an adopted A stays the caller's until the call succeeds
+        modap_ctx *c;
+        bool held;
+        ~Adopted() {
+            if (held) c->A = nullptr;
+        }
+    } adopted{c, owned != nullptr};
+    if (owned)
+        c->A = owned;
+    else
+        HIP_TRY(c, hipMalloc(&c->A, abytes));
+    // x, y, the one-shot translation and the evaluation point are padded with
+    // zeros to ldA so that the sweep reads whole 16-byte vectors of them.
+    const size_t vbytes = sizeof(double) * (size_t)c->ldA, wbytes = 3 * acc_size(c->dt) * (size_t)c->ldA;
+    Pieces pc;
+    pc.add(c->x, vbytes);
+    pc.add(c->y, vbytes);
+    pc.add(c->vpend, vbytes);
+    pc.add(c->wsum, vbytes);
+    pc.add(c->x_eval, vbytes);
+    pc.add(c->y_eval, vbytes);
+    pc.add(c->work, wbytes);
+    pc.add(c->work_eval, wbytes);
+    pc.add(c->claim, sizeof(int) * m);
+    const size_t zeros = pc.total;   // everything so far starts as zeros
+    pc.add(c->b, sizeof(double) * m);
+    pc.add(c->bref, sizeof(double) * m);
+    pc.add(c->nu, sizeof(double) * m);
+    pc.add(c->r_eval, sizeof(double) * m);
+    pc.add(c->ynp, sizeof(double) * (size_t)reduce_grid(c));
+    HIP_TRY(c, pc.alloc(c->vectors));
+    HIP_TRY(c, hipMemsetAsync(c->vectors, 0, zeros, c->stream));
+    if (!owned) {
+        if (c->ldA != n) HIP_TRY(c, hipMemsetAsync(c->A, 0, abytes, c->stream));
+        HIP_TRY(c, hipMemcpy2DAsync(c->A, (size_t)c->ldA * c->es, A, (size_t)lda * c->es, (size_t)n * c->es, (size_t)m,
+                                    on_dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, c->stream));
+    }
+    if ((st = to_device(c, c->b, b, sizeof(double) * m, on_dev))) return st;
+    if (x0 && (st = to_device(c, c->x, x0, sizeof(double) * n, on_dev))) return st;
+    HIP_TRY(c, hipMemcpyAsync(c->bref, c->b, sizeof(double) * m, hipMemcpyDeviceToDevice, c->stream));
+    HIP_TRY(c, aux_ctl_init(c->ctl, c->checks, c->stream));
+    HIP_TRY(c, aux_row_norms(c->dt, c->A, c->ldA, m, n, c->nu, &c->checks->bad, c->stream));
+    if (on_dev) HIP_TRY(c, aux_check_finite(c->b, m, c->x, n, &c->checks->flag, c->stream));
+    HIP_TRY(c, c->rb.reserve(std::min(n, Readback::kMaxStaged)));   // for the reading of x
+    DataChecks found{};
+    HIP_TRY(c, read_checks(c->rb, c->checks, c->stream, &found));
+    if (found.flag) {
+        if (owned) c->A = nullptr;
+        release_system(c);
+        return fail(c, MODAP_E_INVAL, "b or x0 has a non-finite entry");
+    }
+    if (found.bad != ULLONG_MAX) {
+        if (owned) c->A = nullptr;
+        release_system(c);
+        return fail(c, MODAP_E_ZERO_ROW, "row " + std::to_string(found.bad) + " is zero or not finite");
+    }
+    modap_tile t{};
+    bool ok = false;
+    if (c->tile_forced) {
+        t = c->tile;
+        t.grid = 0;
+        ok = configure(c, t) == MODAP_OK;
+    }
+    if (!ok && cache_lookup(c, &t)) ok = configure(c, t) == MODAP_OK;
+    if (!ok) {
+        choose_shape(c->dt, c->ldA, m, c->cu_count, &t);
+        c->tile_forced = false;
+        if ((st = configure(c, t))) {
+            if (owned) c->A = nullptr;
+        release_system(c);
+            return st;
+        }
+    }
+    if ((st = plan_resident(c)) || (st = plan_relay(c))) {
+        if (owned) c->A = nullptr;
+        release_system(c);
+        return st;
+    }
+    adopted.held = false;
+    c->loaded = true;
+    c->err.clear();
+    return MODAP_OK;
+}
+
 }  // namespace
+
+modap_status modap_adopt_system(modap_ctx *c, int64_t m, int64_t n, modap_dtype storage, void *A, const double *b,
+                                const double *x0) {
+    TraceRange trace_("modap_set_system");
+    return set_system(c, m, n, storage, A, n, b, x0, 1, A);
+}
 
 extern "C" {
 
@@ -1045,15 +1149,16 @@ modap_status modap_create(int device, void *hip_stream, modap_ctx **out) {
     }
     c->cu_count = prop.multiProcessorCount;
     c->stream = reinterpret_cast<hipStream_t>(hip_stream);  // NULL: the device's default stream
-    bool ok = hipMalloc(&c->ctl, sizeof(Ctrl)) == hipSuccess && hipMalloc(&c->tot, sizeof(Totals)) == hipSuccess &&
-              hipMalloc(&c->bad, sizeof(unsigned long long)) == hipSuccess &&
-              hipMalloc(&c->flag, sizeof(int)) == hipSuccess &&
-              c->rb.create() == hipSuccess;
+    Pieces pc;
+    pc.add(c->ctl, sizeof(Ctrl));
+    pc.add(c->tot, sizeof(Totals));
+    pc.add(c->checks, sizeof(DataChecks));
+    const bool ok = pc.alloc(c->small) == hipSuccess && c->rb.create(c->stream) == hipSuccess;
     if (!ok) {
         modap_destroy(c);
         return MODAP_E_NOMEM;
     }
-    hipLaunchKernelGGL(ctl_init, dim3(1), dim3(64), 0, c->stream, c->ctl);
+    hipLaunchKernelGGL(ctl_init, dim3(1), dim3(64), 0, c->stream, c->ctl, c->checks);
     if (hipPeekAtLastError() != hipSuccess || hipStreamSynchronize(c->stream) != hipSuccess) {
         (void)hipGetLastError();
         modap_destroy(c);
@@ -1074,10 +1179,7 @@ void modap_destroy(modap_ctx *c) {
     free_dev(c->h_part);
     free_dev(c->dmax_part);
     free_dev(c->binf_part);
-    free_dev(c->ctl);
-    free_dev(c->tot);
-    free_dev(c->bad);
-    free_dev(c->flag);
+    free_dev(c->small);
     free_dev(c->stage);
     c->rb.destroy();
     for (hipEvent_t e : c->events) (void)hipEventDestroy(e);
@@ -1087,113 +1189,7 @@ void modap_destroy(modap_ctx *c) {
 modap_status modap_set_system(modap_ctx *c, int64_t m, int64_t n, modap_dtype storage, const void *A, int64_t lda,
                               const double *b, const double *x0, int on_dev) {
     TraceRange trace_("modap_set_system");
-    modap_status st = check_ctx(c, false);
-    if (st) return st;
-    const char *msg = nullptr;
-    if ((st = check_system(m, n, lda, A, b, (int)storage, &msg))) return fail(c, st, msg);
-    if (!on_dev) {
-        if (!all_finite(b, m)) return fail(c, MODAP_E_INVAL, "b has a non-finite entry");
-        if (x0 && !all_finite(x0, n)) return fail(c, MODAP_E_INVAL, "x0 has a non-finite entry");
-    }
-    DeviceGuard g(c->device);
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    release_system(c);
-    c->dt = (int)storage;
-    c->es = elem_size(c->dt);
-    c->m = m;
-    c->n = n;
-    const int64_t v = vec_elems(c->dt);
-    c->ldA = (n + v - 1) / v * v;
-    c->vpend_maybe = false;
-    c->jn = 0;
-    const size_t abytes = (size_t)m * (size_t)c->ldA * c->es;
-    HIP_TRY(c, hipMalloc(&c->A, abytes));
-    HIP_TRY(c, hipMalloc(&c->b, sizeof(double) * m));
-    HIP_TRY(c, hipMalloc(&c->bref, sizeof(double) * m));
-    HIP_TRY(c, hipMalloc(&c->claim, sizeof(int) * m));
-    HIP_TRY(c, hipMalloc(&c->nu, sizeof(double) * m));
-    // x, y, the one-shot translation and the evaluation point are padded with
-    // zeros to ldA so that the sweep reads whole 16-byte vectors of them.
-    const size_t vbytes = sizeof(double) * (size_t)c->ldA;
-    HIP_TRY(c, hipMalloc(&c->x, vbytes));
-    HIP_TRY(c, hipMalloc(&c->y, vbytes));
-    HIP_TRY(c, hipMalloc(&c->vpend, vbytes));
-    HIP_TRY(c, hipMalloc(&c->wsum, vbytes));
-    HIP_TRY(c, hipMalloc(&c->x_eval, vbytes));
-    HIP_TRY(c, hipMalloc(&c->y_eval, vbytes));
-    const size_t wbytes = 3 * acc_size(c->dt) * (size_t)c->ldA;
-    HIP_TRY(c, hipMalloc(&c->work, wbytes));
-    HIP_TRY(c, hipMalloc(&c->work_eval, wbytes));
-    HIP_TRY(c, hipMemsetAsync(c->work, 0, wbytes, c->stream));
-    HIP_TRY(c, hipMemsetAsync(c->work_eval, 0, wbytes, c->stream));
-    HIP_TRY(c, hipMemsetAsync(c->x, 0, vbytes, c->stream));
-    HIP_TRY(c, hipMemsetAsync(c->x_eval, 0, vbytes, c->stream));
-    HIP_TRY(c, hipMemsetAsync(c->y_eval, 0, vbytes, c->stream));
-    HIP_TRY(c, hipMalloc(&c->r_eval, sizeof(double) * m));
-    HIP_TRY(c, hipMalloc(&c->ynp, sizeof(double) * (size_t)reduce_grid(c)));
-    if (c->ldA != n) HIP_TRY(c, hipMemsetAsync(c->A, 0, abytes, c->stream));
-    HIP_TRY(c, hipMemcpy2DAsync(c->A, (size_t)c->ldA * c->es, A, (size_t)lda * c->es, (size_t)n * c->es, (size_t)m,
-                                on_dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, c->stream));
-    if ((st = to_device(c, c->b, b, sizeof(double) * m, on_dev))) return st;
-    if (x0 && (st = to_device(c, c->x, x0, sizeof(double) * n, on_dev))) return st;
-    HIP_TRY(c, hipMemsetAsync(c->y, 0, vbytes, c->stream));
-    HIP_TRY(c, hipMemsetAsync(c->vpend, 0, vbytes, c->stream));
-    HIP_TRY(c, hipMemsetAsync(c->wsum, 0, vbytes, c->stream));
-    HIP_TRY(c, hipMemsetAsync(c->claim, 0, sizeof(int) * m, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(c->bref, c->b, sizeof(double) * m, hipMemcpyDeviceToDevice, c->stream));
-    const unsigned long long none = ULLONG_MAX;
-    HIP_TRY(c, hipMemcpyAsync(c->bad, &none, sizeof none, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(c, hipMemsetAsync(c->flag, 0, sizeof(int), c->stream));
-    const int nb = (int)((m + 3) / 4);
-    switch (c->dt) {
-        case 0: hipLaunchKernelGGL(row_norms<0>, dim3(nb), dim3(256), 0, c->stream, (const void *)c->A, c->ldA, m, n, c->nu, c->bad); break;
-        case 1: hipLaunchKernelGGL(row_norms<1>, dim3(nb), dim3(256), 0, c->stream, (const void *)c->A, c->ldA, m, n, c->nu, c->bad); break;
-        default: hipLaunchKernelGGL(row_norms<2>, dim3(nb), dim3(256), 0, c->stream, (const void *)c->A, c->ldA, m, n, c->nu, c->bad); break;
-    }
-    LAUNCH_TRY(c, "row_norms launch");
-    if (on_dev) {
-        hipLaunchKernelGGL(check_finite, dim3(64), dim3(256), 0, c->stream, (const double *)c->b, m, c->flag);
-        hipLaunchKernelGGL(check_finite, dim3(64), dim3(256), 0, c->stream, (const double *)c->x, n, c->flag);
-        LAUNCH_TRY(c, "check_finite launch");
-    }
-    hipLaunchKernelGGL(ctl_init, dim3(1), dim3(64), 0, c->stream, c->ctl);
-    LAUNCH_TRY(c, "ctl_init launch");
-    unsigned long long bad = 0;
-    int flag = 0;
-    HIP_TRY(c, hipMemcpyAsync(&bad, c->bad, sizeof bad, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(&flag, c->flag, sizeof flag, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    if (flag) {
-        release_system(c);
-        return fail(c, MODAP_E_INVAL, "b or x0 has a non-finite entry");
-    }
-    if (bad != ULLONG_MAX) {
-        release_system(c);
-        return fail(c, MODAP_E_ZERO_ROW, "row " + std::to_string(bad) + " is zero or not finite");
-    }
-    modap_tile t{};
-    bool ok = false;
-    if (c->tile_forced) {
-        t = c->tile;
-        t.grid = 0;
-        ok = configure(c, t) == MODAP_OK;
-    }
-    if (!ok && cache_lookup(c, &t)) ok = configure(c, t) == MODAP_OK;
-    if (!ok) {
-        choose_shape(c->dt, c->ldA, m, c->cu_count, &t);
-        c->tile_forced = false;
-        if ((st = configure(c, t))) {
-            release_system(c);
-            return st;
-        }
-    }
-    if ((st = plan_resident(c)) || (st = plan_relay(c))) {
-        release_system(c);
-        return st;
-    }
-    c->loaded = true;
-    c->err.clear();
-    return MODAP_OK;
+    return set_system(c, m, n, storage, A, lda, b, x0, on_dev, nullptr);
 }
 
 modap_status modap_set_x(modap_ctx *c, const double *x, int on_dev) {
@@ -1272,33 +1268,41 @@ modap_status modap_set_drift(modap_ctx *c, int64_t T, const double *V, int64_t l
         LAUNCH_TRY(c, "sched_to_vpend launch");
         c->vpend_maybe = true;
     }
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    free_dev(c->V);
     c->T = 0;
-    if (T > 0 && V) {
-        // rows padded with zeros to ldA, like x
-        const size_t vb = sizeof(double) * (size_t)T * (size_t)c->ldA;
-        HIP_TRY(c, hipMalloc(&c->V, vb));
-        HIP_TRY(c, hipMemsetAsync(c->V, 0, vb, c->stream));
+    const size_t want = T > 0 && V ? (size_t)T * (size_t)c->ldA : 0;
+    if (!want || want > c->V_cap || want < c->V_cap / 4) {   // (the kept schedule is at most four times what is needed)
+        if (c->V) HIP_TRY(c, hipStreamSynchronize(c->stream));
+        free_dev(c->V);
+        c->V_cap = 0;
+        if (want) HIP_TRY(c, hipMalloc(&c->V, sizeof(double) * want));
+        c->V_cap = want;
+    }
+    if (!want) {
+        hipLaunchKernelGGL(ctl_set_drift, dim3(1), dim3(64), 0, c->stream, c->ctl, sl, (int64_t)0);
+        LAUNCH_TRY(c, "ctl_set_drift launch");
+        return MODAP_OK;
+    }
+    // rows padded with zeros to ldA, like x
+    if (!on_dev) {
+        if (c->ldA != c->n) HIP_TRY(c, hipMemsetAsync(c->V, 0, sizeof(double) * want, c->stream));
         HIP_TRY(c, hipMemcpy2DAsync(c->V, sizeof(double) * c->ldA, V, sizeof(double) * ldv, sizeof(double) * c->n,
-                                    (size_t)T, on_dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, c->stream));
+                                    (size_t)T, hipMemcpyHostToDevice, c->stream));
         c->T = T;
+        hipLaunchKernelGGL(ctl_set_drift, dim3(1), dim3(64), 0, c->stream, c->ctl, sl, T);
+        LAUNCH_TRY(c, "ctl_set_drift launch");
+        return MODAP_OK;
     }
-    if (on_dev && c->T > 0) {
-        HIP_TRY(c, hipMemsetAsync(c->flag, 0, sizeof(int), c->stream));
-        hipLaunchKernelGGL(check_finite, dim3(64), dim3(256), 0, c->stream, (const double *)c->V, c->T * c->ldA, c->flag);
-        int flag = 0;
-        HIP_TRY(c, hipMemcpyAsync(&flag, c->flag, sizeof flag, hipMemcpyDeviceToHost, c->stream));
-        HIP_TRY(c, hipStreamSynchronize(c->stream));
-        if (flag) {
-            free_dev(c->V);
-            c->T = 0;
-            hipLaunchKernelGGL(ctl_set_drift, dim3(1), dim3(64), 0, c->stream, c->ctl, sl, (int64_t)0);
-            return fail(c, MODAP_E_INVAL, "drift has a non-finite entry");
-        }
+    const int64_t work = T * ((c->ldA + kDriftCols - 1) / kDriftCols);
+    hipLaunchKernelGGL(drift_in, dim3((unsigned)std::min<int64_t>(work, kDriftGroups)), dim3(256), 0, c->stream, V,
+                       ldv, c->n, T, c->V, c->ldA, &c->checks->flag, c->ctl, sl, c->rb.dev, c->rb.arrived, ++c->rb.seq);
+    LAUNCH_TRY(c, "drift_in launch");
+    HIP_TRY(c, c->rb.wait(c->stream));
+    if (c->rb.view->fault) {
+        free_dev(c->V);
+        c->V_cap = 0;
+        return fail(c, MODAP_E_INVAL, "drift has a non-finite entry");
     }
-    hipLaunchKernelGGL(ctl_set_drift, dim3(1), dim3(64), 0, c->stream, c->ctl, sl, c->T);
-    LAUNCH_TRY(c, "ctl_set_drift launch");
+    c->T = T;
     return MODAP_OK;
 }
 
@@ -1638,13 +1642,14 @@ hipError_t aux_row_norms(int dt, const void *A, int64_t ldA, int64_t m, int64_t 
     return hipPeekAtLastError();
 }
 
-hipError_t aux_check_finite(const double *p, int64_t count, int *flag, hipStream_t s) {
-    hipLaunchKernelGGL(check_finite, dim3(64), dim3(256), 0, s, p, count, flag);
+hipError_t aux_check_finite(const double *p, int64_t np, const double *q, int64_t nq, unsigned long long *flag,
+                            hipStream_t s) {
+    hipLaunchKernelGGL(check_finite, dim3(64), dim3(256), 0, s, p, np, q, nq, flag);
     return hipPeekAtLastError();
 }
 
-hipError_t aux_ctl_init(Ctrl *c, hipStream_t s) {
-    hipLaunchKernelGGL(ctl_init, dim3(1), dim3(64), 0, s, c);
+hipError_t aux_ctl_init(Ctrl *c, DataChecks *checks, hipStream_t s) {
+    hipLaunchKernelGGL(ctl_init, dim3(1), dim3(64), 0, s, c, checks);
     return hipPeekAtLastError();
 }
 
@@ -1726,7 +1731,7 @@ bool static_sweep_plan(int dt, int64_t ldA, int64_t m, int64_t n, int cu_count, 
 hipError_t static_sweep_launch(int dt, const StaticPlan &plan, const SweepScratch &s, const void *A, int64_t ldA,
                                int64_t m, int64_t n, const double *b, const double *x, double *r, double *y,
                                int64_t *h, double *max_viol, hipStream_t stream) {
-    hipLaunchKernelGGL(ctl_init, dim3(1), dim3(64), 0, stream, s.ctl);
+    hipLaunchKernelGGL(ctl_init, dim3(1), dim3(64), 0, stream, s.ctl, (DataChecks *)nullptr);
     hipError_t e = aux_row_norms(dt, A, ldA, m, n, s.nu, s.bad, stream);
     if (e != hipSuccess) return e;
     const int sg = (int)std::min<int64_t>(1024, (ldA + 255) / 256);

@@ -50,6 +50,28 @@ void free_dev(P *&p) {
     p = nullptr;
 }
 
+// Several arrays in one device allocation (of each system, the vectors and
+// small results): an allocation and a release each time a system comes and
+// goes, in place of a dozen.
+struct Pieces {
+    static constexpr int kMax = 20;
+    void **at[kMax];
+    size_t off[kMax], total = 0;
+    int count = 0;
+    template <typename P>
+    void add(P *&p, size_t bytes) {
+        at[count] = reinterpret_cast<void **>(&p);
+        off[count++] = total;
+        total += (bytes + 255) / 256 * 256;
+    }
+    hipError_t alloc(void *&base) {
+        const hipError_t e = hipMalloc(&base, total);
+        if (e != hipSuccess) base = nullptr;
+        for (int k = 0; e == hipSuccess && k < count; ++k) *at[k] = static_cast<char *>(base) + off[k];
+        return e;
+    }
+};
+
 }  // namespace modap_host
 
 #define HIP_TRY(c, expr)                                                \

@@ -14,6 +14,18 @@
 // unless the system's committed state is an uncertified stop).  Synchronises.
 modap_status modap_batch_certify_ids(modap_batch *batch, const modap_params *p, const int64_t *ids, int64_t count);
 
+// The states of the given batch systems, read in one request (as the stats of
+// modap_batch_query without vectors).  Synchronises.
+modap_status modap_batch_states(modap_batch *batch, const int64_t *ids, int64_t count, modap_stats *out);
+
+// As modap_batch_add and modap_set_system of device data, for an A that is in
+// device memory already with rows of the padded length (zeros past n): it
+// becomes the batch's or the context's if the call succeeds.
+modap_status modap_batch_adopt(modap_batch *batch, int64_t m, int64_t n, void *A, const double *b, const double *x0,
+                               int64_t *id);
+modap_status modap_adopt_system(modap_ctx *ctx, int64_t m, int64_t n, modap_dtype storage, void *A, const double *b,
+                                const double *x0);
+
 namespace modap {
 
 // A stateless one-pass sweep in the library's built-in launch shape (the shape

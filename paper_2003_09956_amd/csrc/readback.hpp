@@ -12,6 +12,7 @@
 #include <immintrin.h>
 
 #include <atomic>
+#include <cstring>
 #include <stdint.h>
 
 #include "modap_device.hpp"
@@ -27,6 +28,14 @@ struct alignas(128) HostView {
     uint32_t running;       // systems still running (batch)
     uint64_t pad0;
     alignas(128) uint32_t seq;   // the last result that is complete
+};
+
+// What the checks of a system's data report: the first bad row (see
+// row_norms) and whether b or x has a non-finite entry.  Adjacent, so that one
+// request reads both back.
+struct DataChecks {
+    unsigned long long bad;
+    unsigned long long flag;
 };
 
 struct PublishArgs {
@@ -88,11 +97,11 @@ struct Readback {
     double *buf = nullptr, *buf_dev = nullptr;
     size_t cap = 0;                        // doubles
 
-    hipError_t create() {
+    hipError_t create(hipStream_t s) {
         hipError_t e = hipHostMalloc(&view, sizeof(modap::HostView), hipHostMallocMapped);
         if (e == hipSuccess) e = hipHostGetDevicePointer(reinterpret_cast<void **>(&dev), view, 0);
         if (e == hipSuccess) e = hipMalloc(&arrived, sizeof(uint32_t));
-        if (e == hipSuccess) e = hipMemset(arrived, 0, sizeof(uint32_t));
+        if (e == hipSuccess) e = hipMemsetAsync(arrived, 0, sizeof(uint32_t), s);
         if (e == hipSuccess) *view = modap::HostView{};
         return e;
     }
@@ -148,5 +157,19 @@ struct Readback {
         return e == hipSuccess ? wait(s) : e;
     }
 };
+
+// The checks of a system's data, once the work queued on `s` is done.
+inline hipError_t read_checks(Readback &rb, const modap::DataChecks *checks, hipStream_t s, modap::DataChecks *out) {
+    static_assert(sizeof(modap::DataChecks) == 2 * sizeof(double), "read back as two doubles");
+    hipError_t e = rb.reserve(2);
+    if (e != hipSuccess) return e;
+    modap::PublishArgs a{};
+    a.src[0] = reinterpret_cast<const double *>(checks);
+    a.dst[0] = rb.buf_dev;
+    a.count[0] = 2;
+    e = rb.run(a, s);
+    if (e == hipSuccess) std::memcpy(out, rb.buf, sizeof *out);
+    return e;
+}
 
 }  // namespace modap_host

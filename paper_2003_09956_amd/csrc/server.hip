@@ -38,10 +38,12 @@ struct Req {
     double footprint = 0.0;
     // submission: copies of the caller's inputs, made by modap_server_submit
     // and released at admission -- host inputs in host memory, device inputs
-    // in device memory of the server (A row-major with lda = n, V with ldv = n)
+    // in device memory of the server (V with ldv = n; A as the batch and the
+    // contexts hold it, rows padded to ldA with zeros, and handed over at
+    // admission; mem holds b, x0 and V)
     std::vector<char> hA;
     std::vector<double> hb, hx0, hV;
-    void *dA = nullptr;
+    void *dA = nullptr, *mem = nullptr;
     double *db = nullptr, *dx0 = nullptr, *dV = nullptr;
     bool has_x0 = false;
     int64_t T = 0;
@@ -95,6 +97,7 @@ struct modap_server {
     modap_batch *batch = nullptr;
     hipStream_t batch_stream = nullptr;
     hipStream_t copy_stream = nullptr;    // staging of device-side update inputs
+    hipStream_t spare = nullptr;          // the stream of the last request with a context of its own, for the next
     std::vector<Stage> stages;
     int batch_live = 0;
     std::vector<Req> reqs;              // every request, indexed by ticket
@@ -164,9 +167,8 @@ void release_inputs(Req &r) {
     std::vector<double>().swap(r.hx0);
     std::vector<double>().swap(r.hV);
     free_dev(r.dA);
-    free_dev(r.db);
-    free_dev(r.dx0);
-    free_dev(r.dV);
+    free_dev(r.mem);
+    r.db = r.dx0 = r.dV = nullptr;
 }
 
 // Remove retired tickets from the list of live requests.
@@ -174,6 +176,27 @@ void compact_live(modap_server *s) {
     s->live_ids.erase(std::remove_if(s->live_ids.begin(), s->live_ids.end(),
                                      [s](int64_t id) { return s->reqs[(size_t)id].state != RQ_LIVE; }),
                       s->live_ids.end());
+}
+
+// Streams of requests with a context of their own: creating one takes about
+// 350 us, so one that is no longer used is kept for the next such request.
+hipError_t take_stream(modap_server *s, Req &r) {
+    if (s->spare) {
+        r.stream = s->spare;
+        s->spare = nullptr;
+        return hipSuccess;
+    }
+    const hipError_t e = hipStreamCreateWithFlags(&r.stream, hipStreamNonBlocking);
+    if (e != hipSuccess) r.stream = nullptr;
+    return e;
+}
+
+void give_stream(modap_server *s, Req &r) {
+    if (r.stream && !s->spare)
+        s->spare = r.stream;
+    else if (r.stream)
+        (void)hipStreamDestroy(r.stream);
+    r.stream = nullptr;
 }
 
 void drop(modap_server *s, Req &r) {
@@ -185,9 +208,8 @@ void drop(modap_server *s, Req &r) {
         modap_destroy(r.ctx);
         --s->long_live;
     }
-    if (r.stream) (void)hipStreamDestroy(r.stream);
+    give_stream(s, r);
     r.ctx = nullptr;
-    r.stream = nullptr;
     r.bid = -1;
     s->used -= r.footprint;
     --s->live;
@@ -198,16 +220,19 @@ void drop(modap_server *s, Req &r) {
 modap_status admit(modap_server *s, Req &r, double now) {
     modap_status st;
     const int od = r.on_dev;
-    const void *A = od ? (const void *)r.dA : (const void *)r.hA.data();
+    const void *A = od ? nullptr : (const void *)r.hA.data();
     const double *b = od ? r.db : r.hb.data();
     const double *x0 = !r.has_x0 ? nullptr : od ? r.dx0 : r.hx0.data();
     const double *V = r.T == 0 ? nullptr : od ? r.dV : r.hV.data();
     if (batched(s, r)) {
         int64_t id = -1;
-        if ((st = modap_batch_add(s->batch, r.m, r.n, A, r.n, b, x0, od, &id))) {
+        st = od ? modap_batch_adopt(s->batch, r.m, r.n, r.dA, b, x0, &id)
+                : modap_batch_add(s->batch, r.m, r.n, A, r.n, b, x0, 0, &id);
+        if (st) {
             r.error = modap_batch_last_error(s->batch);
             return st;
         }
+        r.dA = nullptr;
         if (r.T > 0 && (st = modap_batch_set_drift(s->batch, id, r.T, V, r.n, od))) {
             r.error = modap_batch_last_error(s->batch);
             (void)modap_batch_remove(s->batch, id);
@@ -217,20 +242,21 @@ modap_status admit(modap_server *s, Req &r, double now) {
         r.bid = id;
         ++s->batch_live;
     } else {
-        if (hipStreamCreateWithFlags(&r.stream, hipStreamNonBlocking) != hipSuccess) {
-            r.stream = nullptr;
+        if (take_stream(s, r) != hipSuccess) {
             r.error = "hipStreamCreateWithFlags failed";
             return MODAP_E_DEVICE;
         }
         st = modap_create(s->device, r.stream, &r.ctx);
-        if (!st) st = modap_set_system(r.ctx, r.m, r.n, (modap_dtype)s->dt, A, r.n, b, x0, od);
+        if (!st)
+            st = od ? modap_adopt_system(r.ctx, r.m, r.n, (modap_dtype)s->dt, r.dA, b, x0)
+                    : modap_set_system(r.ctx, r.m, r.n, (modap_dtype)s->dt, A, r.n, b, x0, 0);
+        if (!st) r.dA = nullptr;
         if (!st && r.T > 0) st = modap_set_drift(r.ctx, r.T, V, r.n, od);
         if (st) {
             r.error = r.ctx ? modap_last_error(r.ctx) : "context creation failed";
             if (r.ctx) modap_destroy(r.ctx);
-            (void)hipStreamDestroy(r.stream);
+            give_stream(s, r);
             r.ctx = nullptr;
-            r.stream = nullptr;
             return st;
         }
     }
@@ -310,6 +336,7 @@ void modap_server_destroy(modap_server *s) {
         (void)hipFree(t.p);
         (void)hipEventDestroy(t.used);
     }
+    if (s->spare) (void)hipStreamDestroy(s->spare);
     if (s->copy_stream) (void)hipStreamDestroy(s->copy_stream);
     if (s->batch_stream) (void)hipStreamDestroy(s->batch_stream);
     delete s;
@@ -352,11 +379,20 @@ modap_status modap_server_submit(modap_server *s, int64_t m, int64_t n, const vo
         }
     } else {
         DeviceGuard g(s->device);
-        hipError_t e = hipMalloc(&r.dA, ab);
-        if (e == hipSuccess) e = hipMalloc(&r.db, sizeof(double) * (size_t)m);
-        if (e == hipSuccess && x0) e = hipMalloc(&r.dx0, sizeof(double) * (size_t)n);
-        if (e == hipSuccess && T > 0) e = hipMalloc(&r.dV, sizeof(double) * (size_t)T * (size_t)n);
-        if (e == hipSuccess) e = hipMemcpyAsync(r.dA, A, ab, hipMemcpyDeviceToDevice, s->copy_stream);
+        const size_t row = (size_t)n * s->es, ldA = (size_t)r.ldA * s->es;
+        Pieces pc;
+        pc.add(r.db, sizeof(double) * (size_t)m);
+        if (x0) pc.add(r.dx0, sizeof(double) * (size_t)n);
+        if (T > 0) pc.add(r.dV, sizeof(double) * (size_t)T * (size_t)n);
+        hipError_t e = hipMalloc(&r.dA, ldA * (size_t)m);
+        if (e == hipSuccess) e = pc.alloc(r.mem);
+        if (e == hipSuccess && ldA == row) {
+            e = hipMemcpyAsync(r.dA, A, ab, hipMemcpyDeviceToDevice, s->copy_stream);
+        } else if (e == hipSuccess) {
+            e = hipMemsetAsync(r.dA, 0, ldA * (size_t)m, s->copy_stream);
+            if (e == hipSuccess)
+                e = hipMemcpy2DAsync(r.dA, ldA, A, row, row, (size_t)m, hipMemcpyDeviceToDevice, s->copy_stream);
+        }
         if (e == hipSuccess) e = hipMemcpyAsync(r.db, b, sizeof(double) * (size_t)m, hipMemcpyDeviceToDevice, s->copy_stream);
         if (e == hipSuccess && x0)
             e = hipMemcpyAsync(r.dx0, x0, sizeof(double) * (size_t)n, hipMemcpyDeviceToDevice, s->copy_stream);
@@ -476,29 +512,36 @@ modap_status modap_server_round(modap_server *s, double now, int64_t *outstandin
         const Req &r = s->reqs[(size_t)id];
         if (r.state == RQ_LIVE && !r.in_batch) HIP_TRY(s, hipStreamSynchronize(r.stream));
     }
-    // Stops of batched requests get their FP64 certificate here (a request
-    // with a context of its own had it queued after its iterations).
-    if (s->params.certify && s->batch_live > 0) {
-        std::vector<int64_t> ids;
-        for (int64_t id : s->live_ids) {
-            Req &r = s->reqs[(size_t)id];
-            if (r.state != RQ_LIVE || !r.in_batch) continue;
-            modap_stats q{};
-            if ((st = modap_batch_query(s->batch, r.bid, nullptr, nullptr, &q, 0)))
-                return fail(s, st, "query of a live request failed");
-            if (q.state == 1 && !q.certified) ids.push_back(r.bid);
-        }
-        if (!ids.empty() && (st = modap_batch_certify_ids(s->batch, &s->params, ids.data(), (int64_t)ids.size())))
+    // The batched requests' states in one request.  Their stops get their FP64
+    // certificate here (a request with a context of its own had it queued
+    // after its iterations).
+    std::vector<int64_t> ids, stops;
+    for (int64_t id : s->live_ids) {
+        const Req &r = s->reqs[(size_t)id];
+        if (r.state == RQ_LIVE && r.in_batch) ids.push_back(r.bid);
+    }
+    std::vector<modap_stats> now_at(ids.size());
+    if (!ids.empty() && (st = modap_batch_states(s->batch, ids.data(), (int64_t)ids.size(), now_at.data())))
+        return fail(s, st, "query of a live request failed");
+    if (s->params.certify)
+        for (size_t q = 0; q < ids.size(); ++q)
+            if (now_at[q].state == 1 && !now_at[q].certified) stops.push_back(ids[q]);
+    if (!stops.empty()) {
+        if ((st = modap_batch_certify_ids(s->batch, &s->params, stops.data(), (int64_t)stops.size())))
             return fail(s, st, modap_batch_last_error(s->batch));
+        if ((st = modap_batch_states(s->batch, ids.data(), (int64_t)ids.size(), now_at.data())))
+            return fail(s, st, "query of a live request failed");
     }
     const double t_end = now + elapsed_since(t0);
+    size_t batched_at = 0;
     for (int64_t id : s->live_ids) {
         Req &r = s->reqs[(size_t)id];
         if (r.state != RQ_LIVE) continue;
         modap_stats q{};
-        st = r.in_batch ? modap_batch_query(s->batch, r.bid, nullptr, nullptr, &q, 0)
-                        : modap_query(r.ctx, nullptr, nullptr, &q, 0);
-        if (st) return fail(s, st, "query of a live request failed");
+        if (r.in_batch)
+            q = now_at[batched_at++];
+        else if ((st = modap_query(r.ctx, nullptr, nullptr, &q, 0)))
+            return fail(s, st, "query of a live request failed");
         const double per_sweep = (double)r.m * (double)r.n * (double)s->es + 24.0 * (double)r.m;
         r.bytes += (double)(q.sweeps - r.sweeps_seen) * per_sweep;
         s->bytes += (double)(q.sweeps - r.sweeps_seen) * per_sweep;
