@@ -58,8 +58,8 @@
  *                                iteration instead of the resident form
  *   MODAP_RESIDENT_ROWS=k        rows per workgroup the resident form aims for
  *                                (default 32, at least 4)
- *   MODAP_RESIDENT_TIMEOUT_TICKS=t  longest wait of a resident launch at its grid
- *                                barrier, and of a long-row sweep for another
+ *   MODAP_RESIDENT_TIMEOUT_TICKS=t  longest wait of a resident launch for its other
+ *                                workgroups, and of a long-row sweep for another
  *                                workgroup's dot product, in ticks of the 100 MHz
  *                                constant clock (default 1e8: one second); after a
  *                                longer wait the call reports E_DEVICE
@@ -144,7 +144,7 @@ typedef struct {
     int32_t certified;      /* 1 if the last stop was confirmed by the FP64 certificate (max_viol
                                is then its upper bound of the largest distance) */
     int32_t resident;       /* iterate and solve: 1 if the iterations ran in the resident form (one
-                               launch of many iterations, the rows held in LDS, a grid barrier per
+                               launch of many iterations, the rows held in LDS, an exchange per
                                iteration), 0 if in the two-kernel form; 0 from every other call */
     double b_drift;         /* last certificate: largest |b_i - exact b_i| of the working
                                right-hand side, which the certificate then corrected */

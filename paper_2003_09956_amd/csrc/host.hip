@@ -114,9 +114,8 @@ struct modap_ctx {
     bool res_ok = false;
     int res_grid = 0, res_rows = 0, res_ldR = 0;
     size_t res_lds = 0;
-    void *res_part = nullptr;
-    int64_t *res_h = nullptr;
-    double *res_dmax = nullptr, *res_binf = nullptr;
+    uint64_t *res_words = nullptr;
+    uint32_t res_base = 1;       // number of the next launch's first iteration
 
     // FP64 certificate (scratch allocated at the first certificate of a system)
     void *cert = nullptr;
@@ -398,7 +397,7 @@ size_t relay_word_bytes(const modap_ctx *c) {
     return sizeof(uint64_t) * (size_t)c->relay_bands * (size_t)c->relay_tiles * (kRelayRing * 4);
 }
 
-// Longest wait of a resident launch at its grid barrier, and of a long-row
+// Longest wait of a resident launch for its other workgroups, and of a long-row
 // sweep for a peer's dot product, in ticks of the 100 MHz constant clock.
 constexpr int64_t kTimeoutTicks = 100000000;   // one second
 int64_t timeout_ticks() {
@@ -748,10 +747,7 @@ modap_status status_of(modap_ctx *c, const State &k, bool solve) {
 }
 
 void release_resident(modap_ctx *c) {
-    free_dev(c->res_part);
-    free_dev(c->res_h);
-    free_dev(c->res_dmax);
-    free_dev(c->res_binf);
+    free_dev(c->res_words);
     c->res_ok = false;
 }
 
@@ -780,7 +776,7 @@ modap_status launch_scatter(modap_ctx *c, int64_t k, const int64_t *rows, const 
 // in the LDS of at most kResidentMaxGrid workgroups at kResidentBand bytes
 // each.  The grid is the larger of that minimum and one workgroup per
 // kResidentRows rows (fewer rows per workgroup shorten the sweep; more
-// workgroups lengthen the barrier).
+// workgroups lengthen the exchange).
 constexpr int64_t kResidentBand = 96 * 1024;
 constexpr int64_t kResidentRows = 32;
 
@@ -801,11 +797,10 @@ modap_status plan_resident(modap_ctx *c) {
     if (hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, c->device) != hipSuccess ||
         lds + kResidentStaticLds > (size_t)max_lds)
         return MODAP_OK;
-    const size_t acc = acc_size(c->dt);
-    HIP_TRY(c, hipMalloc(&c->res_part, 2 * (size_t)kResidentMaxGrid * (size_t)ldR * acc));
-    HIP_TRY(c, hipMalloc(&c->res_h, 2 * sizeof(int64_t) * (size_t)grid));
-    HIP_TRY(c, hipMalloc(&c->res_dmax, 2 * sizeof(double) * (size_t)grid));
-    HIP_TRY(c, hipMalloc(&c->res_binf, 2 * sizeof(double) * (size_t)grid));
+    const size_t words = (size_t)resident_all_words(c->dt, (int)ldR, kResidentMaxGrid);
+    HIP_TRY(c, hipMalloc(&c->res_words, sizeof(uint64_t) * words));
+    HIP_TRY(c, hipMemsetAsync(c->res_words, 0, sizeof(uint64_t) * words, c->stream));
+    c->res_base = 1;
     c->res_grid = (int)grid;
     c->res_rows = (int)rows;
     c->res_ldR = (int)ldR;
@@ -865,8 +860,6 @@ bool use_resident(const modap_ctx *c, const modap_params *p) {
 modap_status launch_resident(modap_ctx *c, const modap_params *p, int track, int64_t K, uint64_t *progress,
                              double *bytes) {
     const bool hv = translation_possible(c);
-    // (the arrival counters were cleared by the last workgroup of the previous
-    // launch, or by set_system; the fault flag stays raised)
     ResidentArgs r{};
     r.A = c->A;
     r.ldA = c->ldA;
@@ -887,13 +880,12 @@ modap_status launch_resident(modap_ctx *c, const modap_params *p, int track, int
     r.j0 = c->jn;
     r.K = K;
     r.dp = decide_params(p, track);
-    r.part = c->res_part;
-    r.h_part = c->res_h;
-    r.dmax_part = c->res_dmax;
-    r.binf_part = c->res_binf;
+    r.words = c->res_words;
+    r.base = c->res_base;
     r.progress = progress;
     r.timeout_ticks = timeout_ticks();
     HIP_TRY(c, aux_resident_launch(c->dt, r, c->res_grid, c->res_lds, c->stream));
+    c->res_base += (uint32_t)K;
     c->jn += K;
     *bytes += (double)K * sweep_bytes(c, hv);
     return MODAP_OK;

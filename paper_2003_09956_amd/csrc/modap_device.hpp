@@ -14,7 +14,7 @@ enum : int32_t {
     ST_NUMERIC = 3,
     ST_LIMIT = 4,
     ST_BAD_ROW = 5,
-    ST_FAULT = 0xff,      // told to the host only: a resident launch gave up at a grid barrier
+    ST_FAULT = 0xff,      // told to the host only: a resident launch gave up waiting
     ST_UNCERTIFIED = 6,   // the FP64 certificate cannot confirm eps: eps_abs lies below its rounding bound
 };
 
@@ -47,10 +47,8 @@ struct alignas(128) Ctrl {
     State st[2];
     int64_t step_limit;   // no step is taken once steps reaches this (set per call)
     int64_t sched_len;    // rows in the drift schedule
-    uint32_t barrier;     // arrivals at the grid barriers of a resident launch (zero before each)
-    uint32_t fault;       // a resident launch gave up waiting at a grid barrier
-    uint32_t exits;       // workgroups of a resident launch that have left it (zero before each)
-    uint32_t pad32;
+    uint32_t fault;       // a launch gave up waiting for its other workgroups
+    uint32_t pad32[3];
     int64_t pad[12];
 };
 

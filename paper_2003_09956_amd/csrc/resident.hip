@@ -47,7 +47,7 @@ size_t resident_lds_bytes(int dt, int rows, int ldR) {
     auto up16 = [](size_t v) { return (v + 15) & ~(size_t)15; };
     const size_t es = dt == 0 ? 8 : dt == 1 ? 4 : 2, acc = dt == 0 ? 8 : 4;
     return up16((size_t)rows * ldR * es) + 3 * up16((size_t)rows * 8) + 3 * (size_t)ldR * 8 + 2 * up16((size_t)ldR * acc) +
-           (size_t)kResidentWaves * ldR * acc;
+           kSumSlots * sizeof(double) + (size_t)kResidentWaves * ldR * acc;
 }
 
 }  // namespace modap

@@ -5,25 +5,34 @@
 // whatever its size.  Here one cooperative launch of G workgroups runs K
 // iterations of the method (section 3: Map of the positive slices, eq. 7,
 // Reduce(+), the eq. 10 test, the step of eq. 12 or Algorithm 1, the
-// translation of the data) with one grid barrier per iteration and no other
-// synchronisation:
+// translation of the data), and the workgroups meet once per iteration:
 //
 //   * each workgroup copies its band of rows (and their b, ||a_i||^2) into
 //     LDS once, and reads them from there in every iteration;
 //   * per iteration it sweeps its band (eight wavefronts, four rows at a time
 //     each, lanes over the columns) and writes one partial y and its h, dmax,
-//     ||b||inf to one of two buffers (alternating by iteration);
-//   * after the barrier every workgroup sums all G partials in the same order,
-//     takes the same decision and step in FP64 on its own copy of x, y and the
-//     running sum of translations (identical arithmetic on identical data
-//     gives identical results in every workgroup), and goes on.
-// A workgroup can be at most one barrier ahead of another, so it never
-// overwrites partials that another is still reading.
+//     ||b||inf to one of two sets of words (alternating by iteration), each
+//     word 32 bits of data and the 32-bit number of the iteration (FP64 takes
+//     two words);
+//   * every workgroup reads the words of all G until they carry this
+//     iteration's number, sums the partials in the same order, takes the same
+//     decision and step in FP64 on its own copy of x, y and the running sum of
+//     translations (identical arithmetic on identical data gives identical
+//     results in every workgroup), and goes on.
+// There is no barrier besides: the words are the data and their arrival in
+// one.  (With partials, a release, an arrival counter that all poll and only
+// then the reads -- four trips to memory in a row -- an iteration took, of
+// FP64 64 x 128 4.5 us and now 3.6, 256 x 1024 5.9 and 4.9, 500 x 700 7.7 and
+// 6.5; of FP32 256 x 1024 12.2 and 4.5, 400 x 1600 13.3 and 5.5: the partial
+// words of 4 bytes were slow to write through.)  A workgroup writes a set
+// again two iterations later: by then it has read every other workgroup's
+// words of the iteration between, and each of those was written after its
+// workgroup had read the set.  The numbers go on from launch to launch.
 //
-// Every wait at the barrier is bounded by the device's constant clock: a
-// workgroup that waits longer than timeout_ticks raises ctl->fault and
-// leaves, and so do the others once they see it, so the grid always drains.
-// A launch with a fault writes nothing back (its results are void).
+// Every wait is bounded by the device's constant clock: a workgroup that
+// waits longer than timeout_ticks raises ctl->fault and leaves, and so do the
+// others once they see it or wait as long, so the grid always drains.  A
+// launch with a fault writes nothing back (its results are void).
 //
 // At the end workgroup 0 writes x, y, the translation sum, the working
 // vectors of the two-kernel path and the final state (into both slots); each
@@ -54,45 +63,87 @@ struct ResidentArgs {
     int64_t j0;             // the launch runs under the committed state of slot (j0-1)&1
     int64_t K;              // iterations
     Decide dp;
-    void *part;             // [2 x kResidentMaxGrid x ldR] accumulation type
-    int64_t *h_part;        // [2 x G]
-    double *dmax_part;      // [2 x G]
-    double *binf_part;      // [2 x G]
+    uint64_t *words;        // [2 x kResidentMaxGrid x resident_words(DT, ldR)]
+    uint32_t base;          // number of the launch's first iteration (a set of words is cleared to number 0)
     uint64_t *progress;     // host memory or null: told the last check and its status when the launch ends
-    int64_t timeout_ticks;  // constant-clock (100 MHz) ticks a workgroup waits at the barrier
+    int64_t timeout_ticks;  // constant-clock (100 MHz) ticks a workgroup waits for the others
 };
 
-// Arrival k (k = 0, 1, ...) at the grid barrier of a resident launch: every
-// workgroup's writes before it are visible to every workgroup after it.
-// false if the wait timed out or another workgroup gave up.  A workgroup that
-// gives up sets the top bit of the arrival counter (so that one read tells a
-// waiting workgroup both) and raises ctl->fault for the host.
-constexpr uint32_t kBarrierFault = 0x80000000u;
+// Words of one workgroup and iteration: the columns' (the low halves of all,
+// then for FP64 the high halves), then h, dmax and ||b||inf.
+constexpr int kTotalWords = 5;
+__host__ __device__ constexpr int resident_words(int dt, int ldR) { return (dt == 0 ? 2 : 1) * ldR + kTotalWords; }
+// All words of a context: two sets of the workgroups' and two of FP64 sums.
+__host__ __device__ constexpr int64_t resident_all_words(int dt, int ldR, int grid) {
+    return 2 * ((int64_t)grid * resident_words(dt, ldR) + 2 * ldR);
+}
 
-__device__ __forceinline__ bool resident_barrier(Ctrl *ctl, uint32_t target, int64_t timeout_ticks) {
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    __shared__ int ok;
-    if (threadIdx.x == 0) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-        __hip_atomic_fetch_add(&ctl->barrier, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const long long t0 = wall_clock64();
-        uint32_t seen;
-        for (;;) {
-            seen = __hip_atomic_load(&ctl->barrier, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (seen >= target) break;
-            if (wall_clock64() - t0 > timeout_ticks) {
-                seen = kBarrierFault;
-                __hip_atomic_fetch_or(&ctl->barrier, kBarrierFault, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(&ctl->fault, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                break;
-            }
+__device__ __forceinline__ void put_word(uint64_t *p, uint32_t v, uint32_t number) {
+    __hip_atomic_store(p, (uint64_t)number << 32 | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint64_t get_word(const uint64_t *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ bool has_number(uint64_t w, uint32_t number) { return (uint32_t)(w >> 32) == number; }
+__device__ __forceinline__ double from_words(uint64_t lo, uint64_t hi) {
+    return __hiloint2double((int)(uint32_t)hi, (int)(uint32_t)lo);
+}
+
+// The value in one word (FP32) or two (FP64).
+template <int W>
+__device__ __forceinline__ double value_of(const uint64_t (&u)[W]) {
+    if constexpr (W == 2)
+        return from_words(u[0], u[1]);
+    else
+        return (double)__uint_as_float((uint32_t)u[0]);
+}
+
+// The clock of one wait: false once it has lasted too long or another
+// workgroup gave up (then ctl->fault is raised).
+struct WaitClock {
+    long long t0;
+    uint32_t turn;
+    __device__ __forceinline__ WaitClock() : t0(wall_clock64()), turn(0) {}
+    __device__ __forceinline__ bool goes_on(Ctrl *ctl, int64_t timeout_ticks) {
+        if (wall_clock64() - t0 > timeout_ticks) {
+            __hip_atomic_store(&ctl->fault, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return false;
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        ok = (seen & kBarrierFault) == 0;
+        return (++turn & 63) != 0 ||
+               __hip_atomic_load(&ctl->fault, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
     }
-    __syncthreads();
-    return ok != 0;
+};
+
+// The sum of column c over the workgroups [g0, g1), at most U of them, in
+// order, FP64.  All words are requested together, slots past g1 reading the
+// last one.
+template <int DT, int U>
+__device__ __forceinline__ bool sum_column(const uint64_t *set, int stride, int ldR, int c, int g0, int g1,
+                                           uint32_t number, Ctrl *ctl, int64_t timeout_ticks, double *sum) {
+    constexpr int W = DT == 0 ? 2 : 1;
+    uint64_t u[U][W];
+    WaitClock wait;
+    for (;;) {
+        bool all = true;
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+#pragma unroll
+            for (int w = 0; w < W; ++w) u[k][w] = get_word(set + (int64_t)min(g0 + k, g1 - 1) * stride + w * ldR + c);
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+#pragma unroll
+            for (int w = 0; w < W; ++w) all &= has_number(u[k][w], number);
+        if (all) break;
+        if (!wait.goes_on(ctl, timeout_ticks)) return false;
+    }
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+        const double v = value_of(u[k]);
+        s += g0 + k < g1 ? v : 0.0;
+    }
+    *sum = s;
+    return true;
 }
 
 template <int DT>
@@ -120,6 +171,7 @@ constexpr int kResidentMaxCols = 512;   // LDS row length limit (8 columns per l
 constexpr int kResidentMaxGrid = 32;    // workgroups of a resident launch at most
 constexpr int kResidentThreads = 512;   // threads of a resident workgroup (8 wavefronts)
 constexpr int kResidentWaves = kResidentThreads / 64;
+constexpr int kSumSlots = kResidentThreads + kResidentMaxGrid;  // doubles of the exchange of sums
 constexpr int kResidentRowsAtOnce = 4;  // rows a wavefront sweeps at once
 constexpr int kResidentStaticLds = 1024; // bytes of static LDS a resident workgroup uses at most
 
@@ -164,12 +216,16 @@ __global__ __launch_bounds__(kResidentThreads) void resident_iterate(const Resid
     off += up16((size_t)ldR * sizeof(Acc));
     Acc *va = reinterpret_cast<Acc *>(lds + off);
     off += up16((size_t)ldR * sizeof(Acc));
+    double *ysum = reinterpret_cast<double *>(lds + off);   // [SL][ldR] or [G][ldR / G]
+    off += kSumSlots * sizeof(double);
     Acc *yw = reinterpret_cast<Acc *>(lds + off);   // [NW][ldR]
     __shared__ double hw[NW * RA], dw[NW * RA], bw[NW * RA], qw[NW];
     __shared__ State st_shared;   // the decision, taken by the last wavefront
-    static_assert((3 * NW * RA + NW) * sizeof(double) + sizeof(State) <= kResidentStaticLds,
+    __shared__ int gave_up;
+    static_assert((3 * NW * RA + NW) * sizeof(double) + sizeof(State) + sizeof(int) <= kResidentStaticLds,
                   "static LDS within what the host plans for");
 
+    if (tid == 0) gave_up = 0;
     // the band, the committed state and the vectors
     const T *Ag = reinterpret_cast<const T *>(a.A);
     for (int i = tid; i < nr * ldR; i += NT) {
@@ -203,10 +259,20 @@ __global__ __launch_bounds__(kResidentThreads) void resident_iterate(const Resid
     }
     __syncthreads();
 
-    // [2][kResidentMaxGrid][ldR]: workgroup g's partial y is row g of its
-    // half (a wavefront's loads and stores of it cover 64 consecutive
-    // columns); rows G.. are never read into a sum
-    Acc *part = reinterpret_cast<Acc *>(a.part);
+    constexpr int WL = resident_words(DT, ldR);
+    static_assert(CPT == 1, "a thread holds one column at most");
+    constexpr int W = DT == 0 ? 2 : 1;
+    // How the sums over the workgroups are formed: of up to eight by a thread
+    // for each column; of more, rows of up to 128 columns by SL threads for
+    // each, PER workgroups to a thread.  Longer rows take two trips: every
+    // workgroup sums its share of the columns and passes the sums on.  Read by
+    // all, G partials of FP64 rows of 256 are 128 KB a workgroup, and took
+    // 5.9 us an iteration of 256 x 1024 for 4.9 in two trips (FP32 500 x 1400
+    // 7.2 and 5.8; short rows lose by the second trip, FP64 64 x 128 3.7 and
+    // 4.3, FP32 128 x 2000 4.3 and 5.0).
+    constexpr int SL = 4, PER = kResidentMaxGrid / SL;
+    const bool slices = CPL <= 2 && G > PER, two = CPL > 2 && G > PER;
+    static_assert(CPL > 2 || SL * ldR <= NT, "a thread for each");
     bool failed = false;
     for (int64_t it = 0; it < a.K; ++it) {
         // the state this sweep runs under
@@ -214,7 +280,9 @@ __global__ __launch_bounds__(kResidentThreads) void resident_iterate(const Resid
         const bool pv = st.vpend_valid != 0;
         const int64_t vi = st.v_idx, sp = st.sched_pos;
         const bool apply = pv || vi >= 0;
-        const int par = (int)(it & 1);
+        const uint32_t number = a.base + (uint32_t)it;
+        uint64_t *set = a.words + (it & 1) * (int64_t)kResidentMaxGrid * WL;
+        uint64_t *mine = set + (int64_t)g * WL;
         Acc xr[CPL], vr[CPL], yacc[CPL];
 #pragma unroll
         for (int k = 0; k < CPL; ++k) {
@@ -292,10 +360,7 @@ __global__ __launch_bounds__(kResidentThreads) void resident_iterate(const Resid
             bw[wave * RA + jl] = binf;
         }
         __syncthreads();
-        // the workgroup's partial y and totals, stored as agent-scope atomics:
-        // they are written through to where every workgroup reads them as
-        // they are stored, so the release at the barrier finds nothing left
-        // to write back
+        // the workgroup's partial y and totals
 #pragma unroll
         for (int k = 0; k < CPT; ++k) {
             const int c = tid + NT * k;
@@ -303,8 +368,12 @@ __global__ __launch_bounds__(kResidentThreads) void resident_iterate(const Resid
                 Acc sum = yw[c];
 #pragma unroll
                 for (int w = 1; w < NW; ++w) sum += yw[w * ldR + c];
-                __hip_atomic_store(&part[((int64_t)par * kResidentMaxGrid + g) * ldR + c], sum, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
+                if constexpr (DT == 0) {
+                    put_word(mine + c, (uint32_t)__double2loint(sum), number);
+                    put_word(mine + ldR + c, (uint32_t)__double2hiint(sum), number);
+                } else {
+                    put_word(mine + c, __float_as_uint(sum), number);
+                }
             }
         }
         if (wave == NW - 1) {   // the workgroup's shares of h, dmax, ||b||inf
@@ -312,13 +381,16 @@ __global__ __launch_bounds__(kResidentThreads) void resident_iterate(const Resid
             const double hh = wave_total(in ? hw[lane] : 0.0);   // integers below 2^53: exact
             const double dd = wave_max_nan(in ? dw[lane] : 0.0);
             const double bm = wave_max_nan(in ? bw[lane] : 0.0);
-            if (lane == 0) {
-                __hip_atomic_store(&a.h_part[par * G + g], (int64_t)hh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(&a.dmax_part[par * G + g], dd, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_store(&a.binf_part[par * G + g], bm, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (lane < kTotalWords) {
+                const uint32_t v = lane == 0   ? (uint32_t)hh
+                                   : lane == 1 ? (uint32_t)__double2loint(dd)
+                                   : lane == 2 ? (uint32_t)__double2hiint(dd)
+                                   : lane == 3 ? (uint32_t)__double2loint(bm)
+                                               : (uint32_t)__double2hiint(bm);
+                put_word(mine + (WL - kTotalWords) + lane, v, number);
             }
         }
-        // Before the barrier (they depend on the state this sweep ran under
+        // Before the wait (they depend on the state this sweep ran under
         // only): the translation this sweep applied joins the FP64 sum, and the
         // drift row due after a step (row sched_pos: the decision either takes
         // it or none) is requested, so that it arrives during the wait.
@@ -330,49 +402,104 @@ __global__ __launch_bounds__(kResidentThreads) void resident_iterate(const Resid
             vcand[k] = (c < a.n && next_due) ? a.V[sp * a.ldV + c] : 0.0;
             if (c < a.n && apply) ws[c] += (pv ? a.vpend[c] : 0.0) + ((a.V && vi >= 0) ? a.V[vi * a.ldV + c] : 0.0);
         }
-        if (!resident_barrier(a.ctl, (uint32_t)(it + 1) * (uint32_t)G, a.timeout_ticks)) {
-            failed = true;
-            break;
-        }
         // every workgroup: y as the sum of the G partials in workgroup order,
         // FP64, and ||y||^2 in a fixed order, by the threads that hold a
         // column; the totals (an integer sum and two maxima, exact in any
         // order) and the decision by the last wavefront, once, shared through
-        // LDS.  Every load is issued before the first use (slots past G are
-        // not read; lanes past G read slot G-1 and are masked out).
+        // LDS (lanes past G read slot G-1 and are masked out).
         const bool decider = wave == NW - 1;
-        const int gl = min(lane, G - 1);
-        int64_t hr = 0;
-        double dr = 0.0, br = 0.0;
-        if (decider) {
-            hr = a.h_part[par * G + gl];
-            dr = a.dmax_part[par * G + gl];
-            br = a.binf_part[par * G + gl];
+        bool here = true;
+        double hr = 0.0, dr = 0.0, br = 0.0, ys = 0.0;
+        const int sl = tid / ldR, c0 = tid - sl * ldR;
+        auto read_totals = [&]() {
+            const uint64_t *tw = set + (int64_t)min(lane, G - 1) * WL + (WL - kTotalWords);
+            uint64_t u[kTotalWords];
+            WaitClock wait;
+            for (;;) {
+                bool all = true;
+#pragma unroll
+                for (int k = 0; k < kTotalWords; ++k) u[k] = get_word(tw + k);
+#pragma unroll
+                for (int k = 0; k < kTotalWords; ++k) all &= has_number(u[k], number);
+                if (all) break;
+                if (!wait.goes_on(a.ctl, a.timeout_ticks)) return false;
+            }
+            hr = (double)(uint32_t)u[0];
+            dr = from_words(u[1], u[2]);
+            br = from_words(u[3], u[4]);
+            return true;
+        };
+        if (two) {
+            // the columns of this workgroup: everyone's partials, one or two to a thread
+            const int B = (ldR + G - 1) / G, first = g * B;
+            uint64_t u[2][W];
+            WaitClock wait;
+            for (;;) {
+                bool all = true;
+#pragma unroll
+                for (int k = 0; k < 2; ++k) {
+                    const int i = min(tid + k * NT, G * B - 1), gg = i / B, c = min(first + i - gg * B, ldR - 1);
+#pragma unroll
+                    for (int w = 0; w < W; ++w) u[k][w] = get_word(set + (int64_t)gg * WL + w * ldR + c);
+                }
+#pragma unroll
+                for (int k = 0; k < 2; ++k)
+#pragma unroll
+                    for (int w = 0; w < W; ++w) all &= has_number(u[k][w], number);
+                if (all) break;
+                if (!wait.goes_on(a.ctl, a.timeout_ticks)) {
+                    here = false;
+                    break;
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+                if (tid + k * NT < G * B) ysum[tid + k * NT] = value_of(u[k]);
+            if (!here) gave_up = 1;
+            __syncthreads();
+            uint64_t *sums = a.words + 2 * (int64_t)kResidentMaxGrid * WL + (it & 1) * (int64_t)(2 * ldR);
+            if (tid < B && first + tid < ldR && !gave_up) {
+                double s = 0.0;
+                for (int gg = 0; gg < G; ++gg) s += ysum[gg * B + tid];
+                put_word(sums + first + tid, (uint32_t)__double2loint(s), number);
+                put_word(sums + ldR + first + tid, (uint32_t)__double2hiint(s), number);
+            }
+            if (decider) here = read_totals() && here;
+            if (tid < ldR)
+                here = sum_column<0, 1>(sums, 0, ldR, tid, 0, 1, number, a.ctl, a.timeout_ticks, &ys) && here;
+        } else {
+            const int g0 = slices ? sl * PER : 0, g1 = min(G, g0 + PER);
+            if (sl < (slices ? SL : 1) && g0 < g1)
+                here = sum_column<DT, PER>(set, WL, ldR, c0, g0, g1, number, a.ctl, a.timeout_ticks, &ys);
+            if (slices && sl < SL) ysum[sl * ldR + c0] = ys;
+            if (decider) here = read_totals() && here;
+        }
+        if (!here) gave_up = 1;
+        if (slices) {
+            __syncthreads();
+            ys = 0.0;
+            if (tid < ldR)
+#pragma unroll
+                for (int k = 0; k < SL; ++k) ys += ysum[k * ldR + tid];
         }
         double q = 0.0;
-#pragma unroll
-        for (int k = 0; k < CPT; ++k) {
-            const int c = tid + NT * k;
-            if (c >= ldR) continue;
-            const Acc *pc = part + (int64_t)par * kResidentMaxGrid * ldR + c;
-            Acc t[kResidentMaxGrid];
-#pragma unroll
-            for (int gg = 0; gg < kResidentMaxGrid; ++gg) t[gg] = gg < G ? pc[(int64_t)gg * ldR] : (Acc)0;
-            double s = 0.0;
-#pragma unroll
-            for (int gg = 0; gg < kResidentMaxGrid; ++gg) s += gg < G ? (double)t[gg] : 0.0;
-            y64[c] = s;
-            q += s * s;
+        if (tid < ldR) {
+            y64[tid] = ys;
+            q = ys * ys;
         }
         if (wave * 64 < ldR) q = wave_total(q);   // (the other wavefronts hold no column)
         if (lane == 0) qw[wave] = q;
         Totals t{};
         if (decider) {   // (while the other wavefronts wait for their loads)
-            t.h = (int64_t)wave_total(lane < G ? (double)hr : 0.0);   // integers below 2^53: exact
+            t.h = (int64_t)wave_total(lane < G ? hr : 0.0);   // integers below 2^53: exact
             t.dmax = wave_max_nan(lane < G ? dr : 0.0);
             t.binf = wave_max_nan(lane < G ? br : 0.0);
         }
         __syncthreads();
+        if (gave_up) {
+            failed = true;
+            break;
+        }
         if (decider) {
             double qq = qw[0];
 #pragma unroll
@@ -383,7 +510,7 @@ __global__ __launch_bounds__(kResidentThreads) void resident_iterate(const Resid
         __syncthreads();
         st = st_shared;
         // the step (x <- x - s y, one rounding) and the translation due at the
-        // next sweep (the row requested before the barrier, when one is due)
+        // next sweep (the row requested before the wait, when one is due)
         const double step = st.s;
         const bool take = st.v_idx >= 0;
 #pragma unroll
@@ -395,18 +522,6 @@ __global__ __launch_bounds__(kResidentThreads) void resident_iterate(const Resid
             va[c] = take ? (Acc)vcand[k] : (Acc)0;
         }
         __syncthreads();
-    }
-    // The last workgroup to leave clears the arrival counters for the next
-    // launch on this stream (a kernel, not a memory set, so that the stream's
-    // work stays kernels only).  Every workgroup has then left its loop, so
-    // none is still reading them; a fault stays raised in ctl->fault.
-    __syncthreads();
-    if (tid == 0) {
-        const uint32_t out = __hip_atomic_fetch_add(&a.ctl->exits, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        if (out == (uint32_t)G - 1) {
-            __hip_atomic_store(&a.ctl->barrier, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&a.ctl->exits, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
     }
     if (failed) {
         if (g == 0 && tid == 0 && a.progress) post_progress(a.progress, a.j0 + a.K - 1, ST_FAULT);
