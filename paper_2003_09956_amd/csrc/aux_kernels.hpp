@@ -23,8 +23,7 @@ __device__ __forceinline__ double load_elem(const void *A, int64_t idx) {
 
 // One 16-byte vector of a row in FP64 (exact).
 template <int DT>
-__device__ __forceinline__ void load_vec64(const void *A, int64_t idx, double (&v)[Store<DT>::VEC]) {
-    const uint4 u = *reinterpret_cast<const uint4 *>(reinterpret_cast<const typename Store<DT>::T *>(A) + idx);
+__device__ __forceinline__ void unpack64(const uint4 u, double (&v)[Store<DT>::VEC]) {
     if constexpr (DT == 0) {
         v[0] = __hiloint2double((int)u.y, (int)u.x);
         v[1] = __hiloint2double((int)u.w, (int)u.z);
@@ -41,6 +40,11 @@ __device__ __forceinline__ void load_vec64(const void *A, int64_t idx, double (&
         }
     }
 }
+template <int DT>
+__device__ __forceinline__ void load_vec64(const void *A, int64_t idx, double (&v)[Store<DT>::VEC]) {
+    unpack64<DT>(*reinterpret_cast<const uint4 *>(reinterpret_cast<const typename Store<DT>::T *>(A) + idx), v);
+}
+
 template <int N>
 __device__ __forceinline__ void load_f64(const double *p, double (&v)[N]) {
     static_assert(N % 2 == 0, "whole 16-byte vectors");

@@ -75,7 +75,12 @@ __device__ __forceinline__ CertWork cert_work(const CertArgs &one, const CertArg
 
 // Rows of a system in groups of 16, four to a wavefront (kRows64); workgroup
 // `first` of the system takes groups first, first + stride, ...  Bound by the
-// read of A (8 flops an FP64 element pair, far below the FP64 vector rate).
+// latency of the reads of A that 8 to 12 wavefronts a CU keep in flight (8
+// flops an FP64 element pair, far below the FP64 vector rate).  With the next
+// chunk requested before this one is used, and the sums of four rows reduced
+// together in place of twelve wavefront sums, 64 FP32 systems of 631 MB took
+// 157 us for 254 and 128 MiB of BF16 rows 44 for 56; more wavefronts with
+// fewer registers each were slower (214 and 73).
 constexpr int kCertGroup = 4 * kRows64;
 template <int DT>
 __global__ __launch_bounds__(256) void cert_dot(const CertArgs one, const CertArgs *list, const CertJob *jobs) {
@@ -83,54 +88,75 @@ __global__ __launch_bounds__(256) void cert_dot(const CertArgs one, const CertAr
     const CertArgs &a = wk.a;
     if (!cert_due(a.ctl, a.sl)) return;
     constexpr int VEC = Store<DT>::VEC, R = kRows64;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const double gm = gamma_of(a.n + 4);
     int64_t h = 0;
     double dup = 0.0, binf = 0.0, drift = 0.0;
     const int64_t groups = (a.m + kCertGroup - 1) / kCertGroup;
+    // Rows are read through a buffer resource each (columns past the row as
+    // zeros), a chunk of 64 vectors of the four ahead of the one in use, the
+    // next group's first chunk while this group's sums are formed; x and wsum,
+    // padded with zeros as the rows are, come from L2.
+    const int64_t row_bytes = a.ldA * (int64_t)sizeof(typename Store<DT>::T);
+    const int chunks = (int)((a.ldA + 64 * VEC - 1) / (64 * VEC));
+    // the bytes [at, at + 64 n) of an array of `bytes`, or what there is of them
+    auto window = [](const void *p, int64_t bytes, int64_t at, int n) {
+        return row_resource(reinterpret_cast<const char *>(p) + at, (uint32_t)min(bytes - at, (int64_t)64 * n));
+    };
+    auto load_rows = [&](uint4 (&u)[R], int64_t g, int ch) {
+        const int64_t row0 = min(g, groups - 1) * kCertGroup + wave * R;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            u[r] = load_row_vec(window(reinterpret_cast<const char *>(a.A) + min(row0 + r, a.m - 1) * row_bytes, row_bytes,
+                                       (int64_t)ch * 1024, 16),
+                                (uint32_t)(lane * 16));
+    };
+    uint4 ahead[R];
+    load_rows(ahead, wk.first, 0);
     for (int64_t g = wk.first; g < groups; g += wk.second) {
-        const int64_t row0 = g * kCertGroup + wave * R;
-        if (row0 >= a.m) continue;
-        // x and wsum are padded with zeros to ldA, as the rows are
+        const int64_t row = g * kCertGroup + wave * R + lane / 16, rowc = min(row, a.m - 1);
+        const double br = load_global(a.bref + rowc), b_now = load_global(a.b + rowc), nu = load_global(a.nu + rowc);
         double dx[R] = {}, dw[R] = {}, sc[R] = {};
-#pragma unroll 2
-        for (int64_t j = (int64_t)lane * VEC; j < a.ldA; j += 64 * VEC) {
-            double e[R][VEC], xj[VEC], wj[VEC];
+#pragma unroll 1
+        for (int ch = 0; ch < chunks; ++ch) {
+            double xj[VEC], wj[VEC];
+            const __amdgpu_buffer_rsrc_t rx = window(a.x, a.ldA * 8, (int64_t)ch * (64 * VEC * 8), VEC * 8),
+                                         rw = window(a.wsum, a.ldA * 8, (int64_t)ch * (64 * VEC * 8), VEC * 8);
 #pragma unroll
-            for (int r = 0; r < R; ++r) load_vec64<DT>(a.A, min(row0 + r, a.m - 1) * a.ldA + j, e[r]);
-            load_f64(a.x + j, xj);
-            load_f64(a.wsum + j, wj);
+            for (int e = 0; e < VEC; e += 2) {
+                const uint32_t at = (uint32_t)((lane * VEC + e) * 8);
+                const uint4 ux = load_cached_vec(rx, at), uw = load_cached_vec(rw, at);
+                __builtin_memcpy(&xj[e], &ux, 16);
+                __builtin_memcpy(&wj[e], &uw, 16);
+            }
+            uint4 u[R];
 #pragma unroll
-            for (int k = 0; k < VEC; ++k) {
-                const double aj = fabs(xj[k]) + fabs(wj[k]);
+            for (int r = 0; r < R; ++r) u[r] = ahead[r];
+            const bool last = ch + 1 == chunks;
+            load_rows(ahead, last ? g + wk.second : g, last ? 0 : ch + 1);
 #pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    dx[r] = __fma_rn(e[r][k], xj[k], dx[r]);
-                    dw[r] = __fma_rn(e[r][k], wj[k], dw[r]);
-                    sc[r] = __fma_rn(fabs(e[r][k]), aj, sc[r]);
+            for (int r = 0; r < R; ++r) {
+                double e[VEC];
+                unpack64<DT>(u[r], e);
+#pragma unroll
+                for (int k = 0; k < VEC; ++k) {
+                    dx[r] = __fma_rn(e[k], xj[k], dx[r]);
+                    dw[r] = __fma_rn(e[k], wj[k], dw[r]);
+                    sc[r] = __fma_rn(fabs(e[k]), fabs(xj[k]) + fabs(wj[k]), sc[r]);
                 }
             }
         }
-        // the wavefront sums, then lane r settles row row0 + r
-        double dxl = 0.0, dwl = 0.0, scl = 0.0;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const double tx = wave_total(dx[r]), tw = wave_total(dw[r]), ts = wave_total(sc[r]);
-            if (lane == r) {
-                dxl = tx;
-                dwl = tw;
-                scl = ts;
-            }
-        }
-        const int64_t row = row0 + lane;
-        if (lane < R && row < a.m) {
-            const double br = a.bref[row];
+        // the wavefront sums, three exchanges for the four rows' sums of a kind;
+        // then lane 16 r settles its row
+        static_assert(R == 4, "the four rows' sums are reduced together");
+        const double dxl = quad_total(dx[0], dx[1], dx[2], dx[3]), dwl = quad_total(dw[0], dw[1], dw[2], dw[3]),
+                     scl = quad_total(sc[0], sc[1], sc[2], sc[3]);
+        if (lane % 16 == 0 && row < a.m) {
             const double bi = br + dwl;
             const double r = dxl - bi;
-            const double nu = a.nu[row];
             const double gb = 4.0 * gm * (scl + fabs(br));
             const double d = ((r + gb) / sqrt(nu)) * (1.0 + 2.0 * gm);
-            drift = max_nan(drift, fabs(a.b[row] - bi));
+            drift = max_nan(drift, fabs(b_now - bi));
             a.b[row] = bi;
             a.bref[row] = bi;
             a.wt[row] = r > 0.0 ? r / nu : 0.0;

@@ -367,6 +367,41 @@ __device__ __forceinline__ double ynorm_of(const double *ynp, int R, int lane) {
     return sqrt(s);
 }
 
+// A buffer resource for one row: wave-uniform base (scalar registers), range
+// = the padded row in bytes, raw addressing (word 3 is the gfx9 value for
+// untyped dword access).  A load addressed past the range returns zeros.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_resource(const char *row, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(row), (short)0, (int)bytes, 0x00020000);
+}
+
+// One 16-byte vector of a row through its resource, at a 32-bit per-lane byte
+// offset.  Rows of A are read exactly once per sweep: the load is non-temporal
+// (aux bit 1) so that the working vectors, b and the partials keep the caches;
+// measured, a cached load makes the sweep 11-19% slower.
+__device__ __forceinline__ uint4 load_row_vec(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+    const u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 2);
+    return make_uint4(t.x, t.y, t.z, t.w);
+}
+
+// The same of a vector that is read again and again: through the caches.
+__device__ __forceinline__ uint4 load_cached_vec(__amdgpu_buffer_rsrc_t r, uint32_t off) {
+    const u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+    return make_uint4(t.x, t.y, t.z, t.w);
+}
+
+// Totals of four per-lane values over the 64 lanes of a wavefront whose lanes
+// are all active: the total of d_j in lanes 16j .. 16j+15.  The lane swaps
+// pair the halves and then the quarters of the wavefront (value j and j+2
+// share a swap across the halves, j and j+1 across the quarters), each pair
+// added lower lane first, and a DPP sum inside each row of 16 lanes finishes:
+// three exchanges for the four values instead of one full sum each.
+template <typename T>
+__device__ __forceinline__ T quad_total(T d0, T d1, T d2, T d3) {
+    const T e02 = lane_swap_add(d0, d2, true);   // lanes 0-31: d0, lanes 32-63: d2
+    const T e13 = lane_swap_add(d1, d3, true);   // lanes 0-31: d1, lanes 32-63: d3
+    return row_total(lane_swap_add(e02, e13, false));
+}
+
 // The decision after a check (eq. 10 test, then eq. 12 or Algorithm 1 step).
 __device__ __forceinline__ State decide(const State &p, const Totals &t, double ynorm, const Decide &d,
                                         int64_t step_limit, int64_t sched_len) {

@@ -154,19 +154,6 @@ __device__ __forceinline__ typename Store<DT>::Acc widen(typename Store<DT>::T v
         return v;
 }
 
-// Totals of four per-lane values over the 64 lanes of a wavefront whose lanes
-// are all active: the total of d_j in lanes 16j .. 16j+15.  The lane swaps
-// pair the halves and then the quarters of the wavefront (value j and j+2
-// share a swap across the halves, j and j+1 across the quarters), each pair
-// added lower lane first, and a DPP sum inside each row of 16 lanes finishes:
-// three exchanges for the four values instead of one full sum each.
-template <typename T>
-__device__ __forceinline__ T quad_total(T d0, T d1, T d2, T d3) {
-    const T e02 = lane_swap_add(d0, d2, true);   // lanes 0-31: d0, lanes 32-63: d2
-    const T e13 = lane_swap_add(d1, d3, true);   // lanes 0-31: d1, lanes 32-63: d3
-    return row_total(lane_swap_add(e02, e13, false));
-}
-
 constexpr int kResidentMaxCols = 512;   // LDS row length limit (8 columns per lane)
 constexpr int kResidentMaxGrid = 32;    // workgroups of a resident launch at most
 constexpr int kResidentThreads = 512;   // threads of a resident workgroup (8 wavefronts)
