@@ -99,16 +99,12 @@ __global__ __launch_bounds__(256) void cert_dot(const CertArgs one, const CertAr
     // padded with zeros as the rows are, come from L2.
     const int64_t row_bytes = a.ldA * (int64_t)sizeof(typename Store<DT>::T);
     const int chunks = (int)((a.ldA + 64 * VEC - 1) / (64 * VEC));
-    // the bytes [at, at + 64 n) of an array of `bytes`, or what there is of them
-    auto window = [](const void *p, int64_t bytes, int64_t at, int n) {
-        return row_resource(reinterpret_cast<const char *>(p) + at, (uint32_t)min(bytes - at, (int64_t)64 * n));
-    };
     auto load_rows = [&](uint4 (&u)[R], int64_t g, int ch) {
         const int64_t row0 = min(g, groups - 1) * kCertGroup + wave * R;
 #pragma unroll
         for (int r = 0; r < R; ++r)
-            u[r] = load_row_vec(window(reinterpret_cast<const char *>(a.A) + min(row0 + r, a.m - 1) * row_bytes, row_bytes,
-                                       (int64_t)ch * 1024, 16),
+            u[r] = load_row_vec(window_resource(reinterpret_cast<const char *>(a.A) + min(row0 + r, a.m - 1) * row_bytes, row_bytes,
+                                                (int64_t)ch * 1024, 1024),
                                 (uint32_t)(lane * 16));
     };
     uint4 ahead[R];
@@ -120,8 +116,8 @@ __global__ __launch_bounds__(256) void cert_dot(const CertArgs one, const CertAr
 #pragma unroll 1
         for (int ch = 0; ch < chunks; ++ch) {
             double xj[VEC], wj[VEC];
-            const __amdgpu_buffer_rsrc_t rx = window(a.x, a.ldA * 8, (int64_t)ch * (64 * VEC * 8), VEC * 8),
-                                         rw = window(a.wsum, a.ldA * 8, (int64_t)ch * (64 * VEC * 8), VEC * 8);
+            const __amdgpu_buffer_rsrc_t rx = window_resource(a.x, a.ldA * 8, (int64_t)ch * (64 * VEC * 8), 64 * VEC * 8),
+                                         rw = window_resource(a.wsum, a.ldA * 8, (int64_t)ch * (64 * VEC * 8), 64 * VEC * 8);
 #pragma unroll
             for (int e = 0; e < VEC; e += 2) {
                 const uint32_t at = (uint32_t)((lane * VEC + e) * 8);

@@ -1426,6 +1426,7 @@ modap_status modap_solve(modap_ctx *c, const modap_params *p, modap_stats *out) 
     return status_of(c, kc, true);
 }
 
+constexpr int64_t kAnnounceGroups = 32;
 modap_status modap_eval_sweep(modap_ctx *c, const double *x, double *r, double *y, int64_t *h, double *max_viol,
                               int on_dev) {
     TraceRange trace_("modap_eval_sweep");
@@ -1454,11 +1455,24 @@ modap_status modap_eval_sweep(modap_ctx *c, const double *x, double *r, double *
     ra.y = on_dev ? y : c->y_eval;
     ra.ctl = nullptr;
     ra.iterate = 0;
+    // Results that stay on the device leave only the totals to tell: the
+    // reduction does it itself, up to kAnnounceGroups workgroups (each waits
+    // for its writes to reach the host's view: a 50 x 200 evaluation takes
+    // 24.8 us, and 26.2 with a launch that publishes).
+    const bool told = on_dev && reduce_grid(c) <= kAnnounceGroups;
+    if (told) {
+        ra.view = c->rb.dev;
+        ra.fault = &c->ctl->fault;
+        ra.arrived = c->rb.arrived;
+        ra.seq = ++c->rb.seq;
+    }
     if ((st = launch_reduce(c, ra))) return st;
     PublishArgs pa{};
     pa.tot = c->tot;
     pa.fault = &c->ctl->fault;
-    if (staged) {
+    if (told) {
+        HIP_TRY(c, c->rb.wait(c->stream));
+    } else if (staged) {
         HIP_TRY(c, c->rb.reserve(c->n + nr));
         pa.src[0] = c->y_eval;
         pa.src[1] = c->r_eval;
@@ -1470,7 +1484,7 @@ modap_status modap_eval_sweep(modap_ctx *c, const double *x, double *r, double *
         if ((st = from_device(c, y, c->y_eval, sizeof(double) * c->n, 0))) return st;
         if (r && (st = from_device(c, r, c->r_eval, sizeof(double) * c->m, 0))) return st;
     }
-    HIP_TRY(c, c->rb.run(pa, c->stream));
+    if (!told) HIP_TRY(c, c->rb.run(pa, c->stream));
     if (staged) {
         std::memcpy(y, c->rb.buf, sizeof(double) * (size_t)c->n);
         if (r) std::memcpy(r, c->rb.buf + c->n, sizeof(double) * (size_t)c->m);
@@ -1723,14 +1737,14 @@ bool static_sweep_plan(int dt, int64_t ldA, int64_t m, int64_t n, int cu_count, 
 hipError_t static_sweep_launch(int dt, const StaticPlan &plan, const SweepScratch &s, const void *A, int64_t ldA,
                                int64_t m, int64_t n, const double *b, const double *x, double *r, double *y,
                                int64_t *h, double *max_viol, hipStream_t stream) {
-    hipLaunchKernelGGL(ctl_init, dim3(1), dim3(64), 0, stream, s.ctl, (DataChecks *)nullptr);
-    hipError_t e = aux_row_norms(dt, A, ldA, m, n, s.nu, s.bad, stream);
+    const int nb = (int)((m + 3) / 4), sg = (int)std::min<int64_t>(1024, (ldA + 255) / 256);
+    switch (dt) {
+        case 0: hipLaunchKernelGGL(static_begin<0>, dim3(nb + sg), dim3(256), 0, stream, A, ldA, m, n, s.nu, s.bad, x, s.work, s.ctl, nb); break;
+        case 1: hipLaunchKernelGGL(static_begin<1>, dim3(nb + sg), dim3(256), 0, stream, A, ldA, m, n, s.nu, s.bad, x, s.work, s.ctl, nb); break;
+        default: hipLaunchKernelGGL(static_begin<2>, dim3(nb + sg), dim3(256), 0, stream, A, ldA, m, n, s.nu, s.bad, x, s.work, s.ctl, nb); break;
+    }
+    hipError_t e = hipPeekAtLastError();
     if (e != hipSuccess) return e;
-    const int sg = (int)std::min<int64_t>(1024, (ldA + 255) / 256);
-    if (dt == 0)
-        hipLaunchKernelGGL(stage_point<double>, dim3(sg), dim3(256), 0, stream, x, n, ldA, s.work);
-    else
-        hipLaunchKernelGGL(stage_point<float>, dim3(sg), dim3(256), 0, stream, x, n, ldA, s.work);
     SweepArgs a{};
     a.A = A;
     a.ldA = ldA;
@@ -1768,11 +1782,12 @@ hipError_t static_sweep_launch(int dt, const StaticPlan &plan, const SweepScratc
     ra.binf_part = s.binf_part;
     ra.tot = s.tot;
     ra.ynp = s.ynp;
+    ra.h_out = h;
+    ra.dmax_out = max_viol;
     if (dt == 0)
         hipLaunchKernelGGL(reduce_y<double>, dim3(plan.R), dim3(kReduceThreads), 0, stream, ra);
     else
         hipLaunchKernelGGL(reduce_y<float>, dim3(plan.R), dim3(kReduceThreads), 0, stream, ra);
-    hipLaunchKernelGGL(copy_totals, dim3(1), dim3(64), 0, stream, (const Totals *)s.tot, h, max_viol);
     return hipPeekAtLastError();
 }
 

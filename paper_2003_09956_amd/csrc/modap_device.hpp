@@ -129,6 +129,8 @@ struct SweepArgs {
     int64_t step_stride;
 };
 
+struct HostView;   // readback.hpp
+
 struct ReduceArgs {
     const void *part;       // [G x ldPart] Acc (float or double per acc_f64)
     int64_t ldPart;
@@ -155,7 +157,12 @@ struct ReduceArgs {
                             // last rebase of b (the exact data are bref + A wsum)
     const double *vpend;    // [ldA] one-shot translation
     int32_t has_v;          // the sweep was compiled with the translation (it applied the state's)
-    int32_t pad2;
+    uint32_t seq;           // with view: the number of the result
+    int64_t *h_out;         // totals to the caller's memory, or null
+    double *dmax_out;
+    HostView *view;         // or null: tell the host the totals (and fault) once every workgroup is done
+    const uint32_t *fault;
+    uint32_t *arrived;      // zero between launches
 };
 
 struct StageArgs {
@@ -387,6 +394,12 @@ __device__ __forceinline__ uint4 load_row_vec(__amdgpu_buffer_rsrc_t r, uint32_t
 __device__ __forceinline__ uint4 load_cached_vec(__amdgpu_buffer_rsrc_t r, uint32_t off) {
     const u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
     return make_uint4(t.x, t.y, t.z, t.w);
+}
+
+// The same for the bytes [at, at + n) of an array of `bytes`, or what there is
+// of them.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t window_resource(const void *p, int64_t bytes, int64_t at, int n) {
+    return row_resource(reinterpret_cast<const char *>(p) + at, (uint32_t)max((int64_t)0, min(bytes - at, (int64_t)n)));
 }
 
 // Totals of four per-lane values over the 64 lanes of a wavefront whose lanes
