@@ -197,10 +197,8 @@ __device__ __forceinline__ void batch_cell_end(const BatchArgs &a, const BatchSy
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
     if (before != q * kBatchWaves + kBatchWaves - 1) return;
     const bool add = S.grouped && q > 0, keep = S.grouped && q + 1 < it.count;
-    const int64_t prt = it.prt + (S.grouped ? 0 : q);
-    Acc *part = reinterpret_cast<Acc *>(a.part) + S.part0 + prt * S.ldA;
     Acc *group = lds[kBatchWaves];
-    for (int col = lane * AV; col < S.ldA; col += 64 * AV) {
+    auto column_sum = [&](int col) {
         Acc w[kBatchWaves][AV];
 #pragma unroll
         for (int g = 0; g < kBatchWaves; ++g) {
@@ -219,28 +217,33 @@ __device__ __forceinline__ void batch_cell_end(const BatchArgs &a, const BatchSy
             for (int k = 0; k < AV; ++k) sum[k] = g[k] + sum[k];
         }
         __builtin_memcpy(&u, sum, 16);
-        if (keep)
-            *reinterpret_cast<uint4 *>(group + col) = u;
-        else
-            store_global(reinterpret_cast<uint4 *>(part + col), u);
-    }
-    if (lane == 0 && !keep) {
-        int64_t hh = 0;
-        double dd = 0.0, bm = 0.0;
-        for (int g = 0; g < kBatchWaves; ++g) {
-            hh += ce.h[g];
-            dd = max_nan(dd, ce.dmax[g]);
-            bm = max_nan(bm, ce.binf[g]);
+        return u;
+    };
+    if (keep) {   // (no global store here: the rows requested ahead stay in flight)
+        for (int col = lane * AV; col < S.ldA; col += 64 * AV) *reinterpret_cast<uint4 *>(group + col) = column_sum(col);
+    } else {
+        const int64_t prt = it.prt + (S.grouped ? 0 : q);
+        Acc *part = reinterpret_cast<Acc *>(a.part) + S.part0 + prt * S.ldA;
+        for (int col = lane * AV; col < S.ldA; col += 64 * AV)
+            store_global(reinterpret_cast<uint4 *>(part + col), column_sum(col));
+        if (lane == 0) {
+            int64_t hh = 0;
+            double dd = 0.0, bm = 0.0;
+            for (int g = 0; g < kBatchWaves; ++g) {
+                hh += ce.h[g];
+                dd = max_nan(dd, ce.dmax[g]);
+                bm = max_nan(bm, ce.binf[g]);
+            }
+            const int64_t k = S.prt0 + prt;
+            store_global(a.h_part + k, hh);
+            store_global(a.dmax_part + k, dd);
+            store_global(a.binf_part + k, bm);
         }
-        const int64_t k = S.prt0 + prt;
-        store_global(a.h_part + k, hh);
-        store_global(a.dmax_part + k, dd);
-        store_global(a.binf_part + k, bm);
+        __builtin_amdgcn_s_waitcnt(0);   // the stores are done before rows are counted again
     }
     // LDS has been read: the next cell's partials may come
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     if (lane == 0) __hip_atomic_store(&ce.summed, q + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-    __builtin_amdgcn_s_waitcnt(0);   // the stores are done before rows are counted again
 }
 
 // One work item: the rows [r0, r1) of its cells, wavefront w taking rows r0+w,

@@ -25,7 +25,7 @@ struct alignas(128) HostView {
     Totals tot;             // the totals of a stateless sweep
     uint64_t progress;      // solve: (settled check + 1) << 8 | its status, written by the next sweep
     uint32_t fault;         // a resident launch gave up waiting
-    uint32_t running;       // systems still running (batch)
+    uint32_t pad32;
     uint64_t pad0;
     alignas(128) uint32_t seq;   // the last result that is complete
 };
