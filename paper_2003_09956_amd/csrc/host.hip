@@ -394,7 +394,7 @@ bool translation_possible(const modap_ctx *c) { return c->vpend_maybe || (c->V &
 int reduce_grid(const modap_ctx *c) { return (int)((c->n + 63) / 64); }
 
 size_t relay_word_bytes(const modap_ctx *c) {
-    return sizeof(uint64_t) * (size_t)c->relay_bands * (size_t)c->relay_tiles * (kRelayRing * 4);
+    return sizeof(uint64_t) * (size_t)c->relay_bands * (size_t)kRelayRing * (size_t)relay_row_words(c->relay_tiles);
 }
 
 // Longest wait of a resident launch for its other workgroups, and of a long-row

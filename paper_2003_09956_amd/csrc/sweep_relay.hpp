@@ -10,7 +10,8 @@
 //   iteration t, streaming wavefronts: y += w(t-D) a(t-D) from LDS; the dot
 //       products of row t, which is in registers; row t to LDS in the place of
 //       row t-D; row t+P requested.
-//   iteration t, publishing wavefront: makes the tile's dots of row t-1 known.
+//   iteration t, publishing wavefront: makes the tile's dots of row t-1 known
+//       (tile 0: the row's b too, when a translation may apply).
 //   iteration t, weighing wavefront: requests every tile's dots of row
 //       t-D+1+F, and from those of row t-D+1, requested F iterations ago,
 //       forms w(t-D+1) = r/||a||^2 for the streaming wavefronts' next iteration.
@@ -34,6 +35,16 @@
 // every peer; a peer that published that row may still have rows down to
 // r+3-2D to read, so kRelayRing slots >= 2D-2 never overwrite an unread word.
 //
+// b is translated in place, so nobody reads it while another workgroup may
+// write it: tile 0 alone reads and writes it, and passes it on with its dots
+// (two more words of a row).  Its publishing wavefront holds the b of 64 rows
+// at a time, in registers by the time the first of them, row 64 q, is
+// published in iteration 64 q + 1; its weighing wavefront, D-3 or more barriers
+// later, is the only one to write them.  (With b read by every tile, a peer up
+// to D-2 iterations behind could read rows that tile 0 had translated already
+// and add the translation twice.)  A launch that cannot translate writes no b,
+// and every tile reads it.
+//
 // The launch is cooperative (every workgroup resident).  A wait is bounded by
 // the constant clock as in resident.hpp: a workgroup that has waited too long
 // raises ctl->fault, waits no more and goes through the rest of its rows, so
@@ -50,7 +61,7 @@ namespace modap {
 struct RelayArgs {
     SplitArgs s;             // A, b, nu, work, pd, r_out, part, scalars (one per band); ntiles
     int64_t tile;            // columns of a tile (the last may be shorter)
-    uint64_t *words;         // [bands][kRelayRing][ntiles * 4]
+    uint64_t *words;         // [bands][kRelayRing][relay_row_words(ntiles)]
     uint32_t base;           // number of the band's row 0 in this launch
     uint32_t pad;
     int64_t timeout_ticks;
@@ -60,6 +71,9 @@ constexpr int kRelayThreads = 512;              // streaming threads
 constexpr int kRelayRing = 16;
 constexpr int kRelayRows = 4;                   // rows in registers: one in work, the others in flight
 constexpr int kRelayMaxTiles = 32;              // two exchanged words of four per lane
+// Words of a row: of each tile the dots with x and v in two halves each, then
+// the two halves of b.
+__host__ __device__ constexpr int relay_row_words(int ntiles) { return ntiles * 4 + 2; }
 constexpr int relay_chunks(int dt) { return dt == 2 ? 2 : 4; }   // 16-byte vectors per thread and row
 constexpr int relay_depth(int dt) { return dt == 2 ? 8 : 4; }    // D
 constexpr int relay_ahead(int dt) { return dt == 2 ? 3 : 1; }    // F
@@ -106,23 +120,36 @@ __global__ __launch_bounds__(kRelayThreads + 128) void sweep_relay(const RelayAr
     // the last row add nothing: their weights are zero)
     const int iters = (R + D + F - 1) / F * F;
 
-    const int nwords = a.ntiles * 4;
+    const int dots = a.ntiles * 4, nwords = relay_row_words(a.ntiles);
     uint64_t *mine = ra.words + (int64_t)band * kRelayRing * nwords;
     if (wave == NW + 1) {
         // ---- publishing wavefront: word q of this tile is the dot (q < 2) or
-        // the translation's, low or high half
+        // the translation's, low or high half; tile 0's words 4 and 5 are b
+        const bool gives_b = HAS_V && tile == 0;
+        double bnow = 0.0, bnext = 0.0;   // lane i: b of row 64 q + i, of this block of rows and the next
+        if (gives_b && R > 0) bnext = a.b_in[r0 + min(lane, R - 1)];
         __syncthreads();
         for (int t = 0; t < iters; ++t) {
             const int rp = t - 1;
-            if (rp >= 0 && rp < R && lane < 4) {
-                double v = 0.0;
+            if (rp >= 0 && rp < R) {
+                if (gives_b && (rp & 63) == 0) {
+                    bnow = bnext;
+                    if (rp + 64 < R) bnext = a.b_in[r0 + min(rp + 64 + lane, R - 1)];
+                }
+                const double bp = lane_value(bnow, rp & 63);
+                if (lane < (gives_b ? 6 : 4)) {
+                    double v = bp;
+                    if (lane < 4) {
+                        v = 0.0;
 #pragma unroll
-                for (int w = 0; w < NW; ++w) v += (double)red[rp & 1][w][lane >> 1];
-                const uint64_t u = __builtin_bit_cast(uint64_t, v);
-                const uint32_t half = (lane & 1) ? (uint32_t)(u >> 32) : (uint32_t)u;
-                __hip_atomic_store(mine + (int64_t)(rp % kRelayRing) * nwords + tile * 4 + lane,
-                                   ((uint64_t)(ra.base + (uint32_t)rp) << 32) | half, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
+                        for (int w = 0; w < NW; ++w) v += (double)red[rp & 1][w][lane >> 1];
+                    }
+                    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+                    const uint32_t half = (lane & 1) ? (uint32_t)(u >> 32) : (uint32_t)u;
+                    __hip_atomic_store(mine + (int64_t)(rp % kRelayRing) * nwords + (lane < 4 ? tile * 4 : dots - 4) + lane,
+                                       ((uint64_t)(ra.base + (uint32_t)rp) << 32) | half, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+                }
             }
             __syncthreads();
         }
@@ -134,34 +161,39 @@ __global__ __launch_bounds__(kRelayThreads + 128) void sweep_relay(const RelayAr
         int64_t h = 0;
         double dmax = 0.0, binf = 0.0, bkeep = 0.0, rkeep = 0.0, nkeep = 1.0;
         bool waits = true;
-        // a lane's words of a row are lane and lane + 64 (clamped: a lane past
-        // the last looks at that one too)
-        const int l0 = min(lane, nwords - 1), l1 = min(lane + 64, nwords - 1);
-        auto fetch = [&](int r, uint64_t (&w)[2]) {
-            uint64_t *at = mine + (int64_t)(r % kRelayRing) * nwords;
-            w[0] = __hip_atomic_load(at + l0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            w[1] = __hip_atomic_load(at + l1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // a lane's words of a row are lane and lane + 64 of the dots (clamped: a
+        // lane past the last looks at that one too), and a half of b
+        constexpr int NL = HAS_V ? 3 : 2;
+        const int at[3] = {min(lane, dots - 1), min(lane + 64, dots - 1), dots + (lane & 1)};
+        auto fetch = [&](int r, uint64_t (&w)[NL]) {
+            uint64_t *row = mine + (int64_t)(r % kRelayRing) * nwords;
+#pragma unroll
+            for (int l = 0; l < NL; ++l) w[l] = __hip_atomic_load(row + at[l], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         };
-        auto fresh = [&](const uint64_t (&w)[2], int r) {
-            const uint32_t want = ra.base + (uint32_t)r;
-            return __all((uint32_t)(w[0] >> 32) == want && (uint32_t)(w[1] >> 32) == want);
+        auto fresh = [&](const uint64_t (&w)[NL], int r) {
+            bool all = true;
+#pragma unroll
+            for (int l = 0; l < NL; ++l) all &= (uint32_t)(w[l] >> 32) == ra.base + (uint32_t)r;
+            return __all(all);
         };
         // Every iteration issues the same loads whether there is a row for them
         // or not, and a fetch only once the words in its
         // registers have been used: the compiler then counts which loads are
         // outstanding, and a fetch stays in flight over F iterations.  (A branch
         // around them, or a copy, became a wait for all of them.)
-        uint64_t word[F][2] = {};
-        double bi[F] = {}, ni[F] = {};   // b and ||a||^2 of the row, requested with its words
+        uint64_t word[F][NL] = {};
+        double bi[F] = {}, ni[F] = {};   // b (if not among the words) and ||a||^2 of the row, requested with them
         __syncthreads();
         for (int t0 = 0; t0 < iters; t0 += F) {
 #pragma unroll
             for (int k = 0; k < F; ++k) {
                 const int t = t0 + k, rw = t - D + 1, rf = rw + F;
                 const bool have = rw >= 0 && rw < R;
-                double d = 0.0, td = 0.0;
+                double d = 0.0, td = 0.0, bb = HAS_V ? 0.0 : uniform(bi[k]);
                 if (have) {
-                    uint64_t w[2] = {word[k][0], word[k][1]};
+                    uint64_t w[NL];
+#pragma unroll
+                    for (int l = 0; l < NL; ++l) w[l] = word[k][l];
                     if (!fresh(w, rw) && waits) {
                         const long long c0 = wall_clock64();
                         for (;;) {
@@ -180,25 +212,26 @@ __global__ __launch_bounds__(kRelayThreads + 128) void sweep_relay(const RelayAr
                     // each row of 16 lanes by rotations, then across the rows.  (One
                     // tile after another it is a chain of reads and adds that cost
                     // more than the rest of the iteration: n = 32000 took 3.6 ms.)
-                    auto whole = [&](uint64_t v, int first) -> double {
+                    auto whole = [&](uint64_t v) -> double {   // (in even lanes)
                         const int own = (int)(uint32_t)v;
                         const int other = __builtin_amdgcn_update_dpp(0, own, 0xB1, 0xF, 0xF, true);   // lane ^ 1
-                        return first + (lane >> 2) < a.ntiles ? __hiloint2double(other, own) : 0.0;
+                        return __hiloint2double(other, own);
                     };
-                    double v = whole(w[0], 0);
-                    if (nwords > 64) v += whole(w[1], 16);
+                    auto dot_of = [&](uint64_t v, int first) { return first + (lane >> 2) < a.ntiles ? whole(v) : 0.0; };
+                    double v = dot_of(w[0], 0);
+                    if (dots > 64) v += dot_of(w[1], 16);
                     v += dpp_move<0x124>(v);   // the row rotated by 4 lanes
                     v += dpp_move<0x128>(v);   // and by 8
                     v = xor_add<32>(xor_add<16>(v));
                     d = lane_value(v, 0);
                     td = lane_value(v, 2);
+                    if constexpr (HAS_V) bb = lane_value(whole(w[2]), 0);
                 }
-                double bb = uniform(bi[k]);
                 const double nw = uniform(ni[k]);
                 {
                     const int rc = max(0, min(rf, R - 1));
                     fetch(rc, word[k]);
-                    bi[k] = a.b_in[r0 + rc];
+                    if constexpr (!HAS_V) bi[k] = a.b_in[r0 + rc];
                     ni[k] = a.nu[r0 + rc];
                 }
                 double weight = 0.0;
