@@ -14,7 +14,7 @@ enum : int32_t {
     ST_NUMERIC = 3,
     ST_LIMIT = 4,
     ST_BAD_ROW = 5,
-    ST_FAULT = 0xff,      // told to the host only: a resident launch gave up waiting
+    ST_FAULT = 0xff,      // told to the host only: a launch gave up waiting for its other workgroups
     ST_UNCERTIFIED = 6,   // the FP64 certificate cannot confirm eps: eps_abs lies below its rounding bound
 };
 
@@ -461,6 +461,22 @@ __device__ __forceinline__ State decide(const State &p, const Totals &t, double 
 __device__ __forceinline__ void post_progress(uint64_t *p, int64_t check, int32_t status) {
     __hip_atomic_store(p, ((uint64_t)(check + 1) << 8) | (uint64_t)status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
+
+// The clock of one wait for another workgroup: false once it has lasted too long or another
+// workgroup gave up (then ctl->fault is raised).
+struct WaitClock {
+    long long t0;
+    uint32_t turn;
+    __device__ __forceinline__ WaitClock() : t0(wall_clock64()), turn(0) {}
+    __device__ __forceinline__ bool goes_on(Ctrl *ctl, int64_t timeout_ticks) {
+        if (wall_clock64() - t0 > timeout_ticks) {
+            __hip_atomic_store(&ctl->fault, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return false;
+        }
+        return (++turn & 63) != 0 ||
+               __hip_atomic_load(&ctl->fault, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
+    }
+};
 
 // The state that sweep pd.j runs under (see Pending).  Called by whole
 // wavefronts (the norm of y is summed across the wavefront); `writer` commits

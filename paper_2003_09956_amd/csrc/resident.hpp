@@ -98,22 +98,6 @@ __device__ __forceinline__ double value_of(const uint64_t (&u)[W]) {
         return (double)__uint_as_float((uint32_t)u[0]);
 }
 
-// The clock of one wait: false once it has lasted too long or another
-// workgroup gave up (then ctl->fault is raised).
-struct WaitClock {
-    long long t0;
-    uint32_t turn;
-    __device__ __forceinline__ WaitClock() : t0(wall_clock64()), turn(0) {}
-    __device__ __forceinline__ bool goes_on(Ctrl *ctl, int64_t timeout_ticks) {
-        if (wall_clock64() - t0 > timeout_ticks) {
-            __hip_atomic_store(&ctl->fault, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            return false;
-        }
-        return (++turn & 63) != 0 ||
-               __hip_atomic_load(&ctl->fault, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
-    }
-};
-
 // The sum of column c over the workgroups [g0, g1), at most U of them, in
 // order, FP64.  All words are requested together, slots past g1 reading the
 // last one.

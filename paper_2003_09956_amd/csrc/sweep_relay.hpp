@@ -48,8 +48,10 @@
 // The launch is cooperative (every workgroup resident).  A wait is bounded by
 // the constant clock as in resident.hpp: a workgroup that has waited too long
 // raises ctl->fault, waits no more and goes through the rest of its rows, so
-// every workgroup ends and its peers get what they wait for; the results are
-// void.  (The row loop has no way out, so that it has no branch around loads.)
+// every workgroup ends and its peers get what they wait for; they stop waiting
+// too once they see the fault, and the results are void.  (The row loop has no
+// way out, so that it has no branch around loads.)  Launches that find the fault
+// raised do nothing but tell the host, so that a solve ends.
 #pragma once
 
 #include "modap_device.hpp"
@@ -100,6 +102,7 @@ __global__ __launch_bounds__(kRelayThreads + 128) void sweep_relay(const RelayAr
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int tile = (int)(blockIdx.x % (unsigned)a.ntiles), band = (int)(blockIdx.x / (unsigned)a.ntiles);
+    const uint32_t fault = load_global(&a.pd.ctl->fault);   // (arrives with the state)
     const State st = sweep_state(a.pd, lane, blockIdx.x == 0 && tid == 0);
     if (a.check_status && st.status != ST_RUNNING) return;
     const bool apply_v = HAS_V && (st.vpend_valid || st.v_idx >= 0);
@@ -115,7 +118,12 @@ __global__ __launch_bounds__(kRelayThreads + 128) void sweep_relay(const RelayAr
     uint4 *hold = reinterpret_cast<uint4 *>(hold_raw);   // [D][C][NT]
     __shared__ Acc red[2][NW][2];
     __shared__ double wsh[2];
+    __shared__ uint32_t gave_up;   // an earlier launch did; one reading for the whole workgroup
     if (tid < 2) wsh[tid] = 0.0;   // (what the first D iterations add)
+    if (tid == 0) {
+        gave_up = fault;
+        if (fault && blockIdx.x == 0 && a.pd.progress) post_progress(a.pd.progress, a.pd.j - 1, ST_FAULT);
+    }
     // row R-1 is added in iteration R-1+D; a multiple of F (the iterations past
     // the last row add nothing: their weights are zero)
     const int iters = (R + D + F - 1) / F * F;
@@ -129,6 +137,7 @@ __global__ __launch_bounds__(kRelayThreads + 128) void sweep_relay(const RelayAr
         double bnow = 0.0, bnext = 0.0;   // lane i: b of row 64 q + i, of this block of rows and the next
         if (gives_b && R > 0) bnext = a.b_in[r0 + min(lane, R - 1)];
         __syncthreads();
+        if (gave_up) return;
         for (int t = 0; t < iters; ++t) {
             const int rp = t - 1;
             if (rp >= 0 && rp < R) {
@@ -184,6 +193,7 @@ __global__ __launch_bounds__(kRelayThreads + 128) void sweep_relay(const RelayAr
         uint64_t word[F][NL] = {};
         double bi[F] = {}, ni[F] = {};   // b (if not among the words) and ||a||^2 of the row, requested with them
         __syncthreads();
+        if (gave_up) return;
         for (int t0 = 0; t0 < iters; t0 += F) {
 #pragma unroll
             for (int k = 0; k < F; ++k) {
@@ -195,17 +205,11 @@ __global__ __launch_bounds__(kRelayThreads + 128) void sweep_relay(const RelayAr
 #pragma unroll
                     for (int l = 0; l < NL; ++l) w[l] = word[k][l];
                     if (!fresh(w, rw) && waits) {
-                        const long long c0 = wall_clock64();
-                        for (;;) {
+                        WaitClock wait;
+                        do {
+                            waits = __all(wait.goes_on(a.pd.ctl, ra.timeout_ticks));
                             fetch(rw, w);
-                            if (fresh(w, rw)) break;
-                            if (wall_clock64() - c0 > ra.timeout_ticks) {
-                                if (lane == 0)
-                                    __hip_atomic_store(&a.pd.ctl->fault, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                                waits = false;
-                                break;
-                            }
-                        }
+                        } while (!fresh(w, rw) && waits);
                     }
                     // The row's dots over all tiles, in a fixed order: lanes 4q and
                     // 4q+2 put their two halves together, the quads are added inside
@@ -327,6 +331,7 @@ __global__ __launch_bounds__(kRelayThreads + 128) void sweep_relay(const RelayAr
         }
     }
     __syncthreads();
+    if (gave_up) return;
     int place = 0;   // t % D, row t's place among the held rows
     auto add_held = [&](int t) {
         const double wd = uniform(wsh[(t - D) & 1]);
