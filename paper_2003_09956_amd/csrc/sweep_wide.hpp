@@ -48,6 +48,16 @@ __device__ __forceinline__ T group_total(T v) {
     return v;
 }
 
+// The sum of v[0 .. N), neighbours first (v is used up).
+template <int N, typename T>
+__device__ __forceinline__ T pair_sum(T (&v)[N]) {
+#pragma unroll
+    for (int s = 1; s < N; s *= 2)
+#pragma unroll
+        for (int i = 0; i + s < N; i += 2 * s) v[i] += v[i + s];
+    return v[0];
+}
+
 template <int DT>
 __device__ __forceinline__ void unpack(const uint4 &u, typename Store<DT>::Acc (&o)[Store<DT>::VEC]);
 
@@ -264,21 +274,28 @@ __global__ __launch_bounds__(BLOCK) void sweep_wide(const SweepArgs a) {
     };
 
     auto process = [&](const uint4 (&buf)[RS][C], const double (&bi)[RS], const double (&nui)[RS], int64_t t) {
+        // A lane's products are added in chains of two chunks, and the chains
+        // neighbours first: one chain over all chunks rounds more the fewer
+        // lanes share a row (rms error of the dot products of BF16 rows of 4096,
+        // 8 chunks: 1.58e-7 in one chain, 1.08e-7 in four; 6000, 12 chunks:
+        // 1.91e-7 and 1.11e-7; an iteration of BF16 4096 x 16384 is 1% slower).
+        constexpr int NA = (C + 1) / 2;
         Acc dot[RS], tdot[RS];
 #pragma unroll
         for (int q = 0; q < RS; ++q) {
-            dot[q] = (Acc)0;
-            tdot[q] = (Acc)0;
+            Acc ds[NA] = {}, ts[NA] = {};
 #pragma unroll
             for (int c = 0; c < C; ++c) {
                 Acc av[VEC];
                 unpack<DT>(buf[q][c], av);
 #pragma unroll
                 for (int e = 0; e < VEC; ++e) {
-                    dot[q] = fma(xr[c][e], av[e], dot[q]);
-                    if (HAS_V) tdot[q] = fma(vr[c][e], av[e], tdot[q]);
+                    ds[c / 2] = fma(xr[c][e], av[e], ds[c / 2]);
+                    if (HAS_V) ts[c / 2] = fma(vr[c][e], av[e], ts[c / 2]);
                 }
             }
+            dot[q] = pair_sum(ds);
+            tdot[q] = HAS_V ? pair_sum(ts) : (Acc)0;
         }
 #pragma unroll
         for (int q = 0; q < RS; ++q) {
