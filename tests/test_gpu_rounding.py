@@ -54,3 +54,40 @@ def test_dot_products_round_in_short_chains(dtype, n):
     print(f"{dtype} {n}: {got:.3e}, model {model:.3e}", flush=True)
     # 1500 rows: 2% of statistical error; the lanes and wavefronts of a row are added in pairs and fours
     assert got <= 1.15 * model
+
+
+@pytest.mark.parametrize("dtype,n,m", [("f32", 20000, 2097), ("f32", 40000, 6000), ("bf16", 40000, 2097),
+                                       ("bf16", 24000, 16384), ("f64", 9000, 8000)])
+def test_the_one_read_sweep_rounds_no_more_than_the_two_phases(dtype, n, m):
+    """Half as many bands of rows as the two phases have: r and y against 64 bits (FP64 storage: y of
+    64 columns against 80 bits), in both forms."""
+    split = {"f64": (256, 256, 8), "f32": (256, 256, 8), "bf16": (256, 256, 4)}[dtype]
+    A, x, b = system(dtype, n, m)
+    if dtype == "f64":
+        cols = slice(0, 64)
+        a = A.cpu().numpy()
+        xs = x.cpu().numpy().astype(np.longdouble)
+        exact = np.concatenate([(c.astype(np.longdouble) * xs).sum(axis=1) for c in np.array_split(a, 50)])
+        nu = np.concatenate([np.square(c.astype(np.longdouble)).sum(axis=1) for c in np.array_split(a, 50)])
+        y = np.where(exact > 0, exact / nu, 0) @ a[:, cols].astype(np.longdouble)
+        limit = 1.5      # 64 columns: 9% of statistical error a side
+    else:
+        cols = slice(0, n)
+        ex = torch.cat([c.to(torch.float64) @ x for c in A.split(512)])
+        nu = torch.cat([c.to(torch.float64).square().sum(1) for c in A.split(512)])
+        w = torch.where(ex > 0, ex / nu, 0.0)
+        y = sum(p @ c.to(torch.float64) for p, c in zip(w.split(512), A.split(512))).cpu().numpy()
+        exact = ex.cpu().numpy()
+        limit = 1.05
+    err = {}
+    for form in ("one read", "two phases"):
+        with P.Solver(0) as s:
+            s.set_system(A, b, dtype=dtype)
+            assert s.get_tile()["kind"] == 1
+            if form != "one read":
+                s.set_tile(*split, 0, 1, kind=1)
+            e = s.eval_sweep(x.cpu().numpy())
+        err[form] = rms(e.r - exact), rms(e.y[cols] - y)
+    print(dtype, n, m, err, flush=True)
+    (r1, y1), (r2, y2) = err["one read"], err["two phases"]
+    assert r1 <= 1.05 * r2 and y1 <= limit * y2
