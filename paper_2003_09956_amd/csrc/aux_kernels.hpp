@@ -429,6 +429,10 @@ __global__ __launch_bounds__(1024) void sched_to_vpend(Ctrl *c, int sl, double *
     }
 }
 
+__global__ void clear_words(uint64_t *p, int64_t count) {
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x) p[i] = 0;
+}
+
 __device__ __forceinline__ void start_schedule(Ctrl *c, int sl, int64_t T) {
     c->sched_len = T;
     c->st[sl].sched_pos = 0;

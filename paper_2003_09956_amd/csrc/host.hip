@@ -443,18 +443,20 @@ SweepArgs sweep_args(modap_ctx *c) {
     return a;
 }
 
-// The one-read form of long rows serves the built-in choice of the split-row
-// form.  Its launch is cooperative and its rows are numbered by the host, so a
-// stream under capture takes the two phases.
-bool use_relay(const modap_ctx *c) {
-    if (!c->relay_ok || c->tile_forced || !c->skern) return false;
+// What is queued may be run again later (a stream that cannot be asked counts as one under capture).
+bool under_capture(const modap_ctx *c) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) {
         (void)hipGetLastError();
-        return false;
+        return true;
     }
-    return cap == hipStreamCaptureStatusNone;
+    return cap != hipStreamCaptureStatusNone;
 }
+
+// The one-read form of long rows serves the built-in choice of the split-row
+// form.  Its launch is cooperative and its rows are numbered by the host, so a
+// stream under capture takes the two phases.
+bool use_relay(const modap_ctx *c) { return c->relay_ok && !c->tile_forced && c->skern && !under_capture(c); }
 
 // Launch the sweep of the configured form (events: start/end of its kernels).
 modap_status launch_sweep(modap_ctx *c, const SweepArgs &a, bool hv, hipEvent_t e0, hipEvent_t e1) {
@@ -880,6 +882,17 @@ modap_status launch_resident(modap_ctx *c, const modap_params *p, int track, int
     r.j0 = c->jn;
     r.K = K;
     r.dp = decide_params(p, track);
+    // Words are told apart by the numbers of their iterations, which the host
+    // gives out once.  A captured launch gives the same ones again each time it is
+    // replayed, and 32 bits of them come round: such a launch starts with clear
+    // words (cleared by a kernel: memory-set nodes have given wrong results in replays).
+    const bool comes_round = (uint64_t)c->res_base + (uint64_t)K > UINT32_MAX;
+    if (comes_round) c->res_base = 1;
+    if (comes_round || under_capture(c)) {
+        hipLaunchKernelGGL(clear_words, dim3(64), dim3(256), 0, c->stream, c->res_words,
+                           resident_all_words(c->dt, c->res_ldR, kResidentMaxGrid));
+        LAUNCH_TRY(c, "clear_words launch");
+    }
     r.words = c->res_words;
     r.base = c->res_base;
     r.progress = progress;

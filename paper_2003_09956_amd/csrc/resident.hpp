@@ -27,7 +27,9 @@
 // words of 4 bytes were slow to write through.)  A workgroup writes a set
 // again two iterations later: by then it has read every other workgroup's
 // words of the iteration between, and each of those was written after its
-// workgroup had read the set.  The numbers go on from launch to launch.
+// workgroup had read the set.  The numbers go on from launch to launch; where
+// they would be used again (a captured launch that is replayed, 2^32 of them
+// used up) the host has the words cleared before the launch.
 //
 // Every wait is bounded by the device's constant clock: a workgroup that
 // waits longer than timeout_ticks raises ctl->fault and leaves, and so do the
