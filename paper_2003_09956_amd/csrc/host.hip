@@ -1266,6 +1266,7 @@ modap_status modap_set_drift(modap_ctx *c, int64_t T, const double *V, int64_t l
     const char *msg = nullptr;
     if ((st = check_drift(T, V, ldv, c->n, !on_dev, &msg))) return fail(c, st, msg);
     DeviceGuard g(c->device);
+    if (under_capture(c)) return hip_fail(c, hipErrorStreamCaptureUnsupported, "modap_set_drift");
     const int sl = last_slot(c);
     if (c->V) {
         hipLaunchKernelGGL(sched_to_vpend, dim3(1), dim3(1024), 0, c->stream, c->ctl, sl, c->vpend,
@@ -1276,7 +1277,7 @@ modap_status modap_set_drift(modap_ctx *c, int64_t T, const double *V, int64_t l
     c->T = 0;
     const size_t want = T > 0 && V ? (size_t)T * (size_t)c->ldA : 0;
     if (!want || want > c->V_cap || want < c->V_cap / 4) {   // (the kept schedule is at most four times what is needed)
-        if (c->V) HIP_TRY(c, hipStreamSynchronize(c->stream));
+        HIP_TRY(c, hipStreamSynchronize(c->stream));
         free_dev(c->V);
         c->V_cap = 0;
         if (want) HIP_TRY(c, hipMalloc(&c->V, sizeof(double) * want));
@@ -1288,24 +1289,30 @@ modap_status modap_set_drift(modap_ctx *c, int64_t T, const double *V, int64_t l
         return MODAP_OK;
     }
     // rows padded with zeros to ldA, like x
-    if (!on_dev) {
+    auto take_in = [&]() -> modap_status {
+        if (on_dev) {
+            const int64_t work = T * ((c->ldA + kDriftCols - 1) / kDriftCols);
+            hipLaunchKernelGGL(drift_in, dim3((unsigned)std::min<int64_t>(work, kDriftGroups)), dim3(256), 0, c->stream,
+                               V, ldv, c->n, T, c->V, c->ldA, &c->checks->flag, c->ctl, sl, c->rb.dev, c->rb.arrived,
+                               ++c->rb.seq);
+            LAUNCH_TRY(c, "drift_in launch");
+            HIP_TRY(c, c->rb.wait(c->stream));
+            return c->rb.view->fault ? fail(c, MODAP_E_INVAL, "drift has a non-finite entry") : MODAP_OK;
+        }
         if (c->ldA != c->n) HIP_TRY(c, hipMemsetAsync(c->V, 0, sizeof(double) * want, c->stream));
         HIP_TRY(c, hipMemcpy2DAsync(c->V, sizeof(double) * c->ldA, V, sizeof(double) * ldv, sizeof(double) * c->n,
                                     (size_t)T, hipMemcpyHostToDevice, c->stream));
-        c->T = T;
         hipLaunchKernelGGL(ctl_set_drift, dim3(1), dim3(64), 0, c->stream, c->ctl, sl, T);
         LAUNCH_TRY(c, "ctl_set_drift launch");
+        // (a copy from pinned memory waits in the stream, behind whatever is
+        // queued there, and V is the caller's again when the call returns)
+        HIP_TRY(c, hipStreamSynchronize(c->stream));
         return MODAP_OK;
-    }
-    const int64_t work = T * ((c->ldA + kDriftCols - 1) / kDriftCols);
-    hipLaunchKernelGGL(drift_in, dim3((unsigned)std::min<int64_t>(work, kDriftGroups)), dim3(256), 0, c->stream, V,
-                       ldv, c->n, T, c->V, c->ldA, &c->checks->flag, c->ctl, sl, c->rb.dev, c->rb.arrived, ++c->rb.seq);
-    LAUNCH_TRY(c, "drift_in launch");
-    HIP_TRY(c, c->rb.wait(c->stream));
-    if (c->rb.view->fault) {
+    };
+    if ((st = take_in())) {   // no schedule is left behind
         free_dev(c->V);
         c->V_cap = 0;
-        return fail(c, MODAP_E_INVAL, "drift has a non-finite entry");
+        return st;
     }
     c->T = T;
     return MODAP_OK;
