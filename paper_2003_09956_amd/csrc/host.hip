@@ -1730,7 +1730,7 @@ hipError_t aux_rhs_exact(int dt, const void *A, int64_t ldA, int64_t m, int64_t 
     return hipPeekAtLastError();
 }
 
-bool static_sweep_plan(int dt, int64_t ldA, int64_t m, int64_t n, int cu_count, StaticPlan *out) {
+bool static_sweep_plan(int dt, int64_t ldA, int64_t m, int64_t n, int cu_count, int per_cu, StaticPlan *out) {
     modap_tile t{};
     choose_shape(dt, ldA, m, cu_count, &t);
     // (FP64 rows above 4096 elements have a one-pass shape, whose partials do
@@ -1740,7 +1740,7 @@ bool static_sweep_plan(int dt, int64_t ldA, int64_t m, int64_t n, int cu_count, 
     if (!k) return false;
     // the row mapping of configure() for a band of rows per workgroup
     const int per_step = (t.block / t.lanes_per_row) * t.rows_per_step;
-    int grid = t.grid > 0 ? t.grid : std::max(1, cu_count);
+    int grid = std::min(t.grid > 0 ? t.grid : std::max(1, cu_count), per_cu * std::max(1, cu_count));
     int64_t rpb = (m + grid - 1) / grid;
     rpb = ((rpb + per_step - 1) / per_step) * per_step;
     grid = (int)((m + rpb - 1) / rpb);

@@ -39,8 +39,8 @@ struct StaticPlan {
     int64_t rows_per_block, block_stride, step_stride;
 };
 
-// false when no one-pass shape covers rows of padded length ldA.
-bool static_sweep_plan(int dt, int64_t ldA, int64_t m, int64_t n, int cu_count, StaticPlan *out);
+// At most `per_cu` workgroups per CU; false when no one-pass shape covers rows of padded length ldA.
+bool static_sweep_plan(int dt, int64_t ldA, int64_t m, int64_t n, int cu_count, int per_cu, StaticPlan *out);
 
 // Device memory the stateless sweep works in (caller-provided, see noalloc.hip).
 struct SweepScratch {

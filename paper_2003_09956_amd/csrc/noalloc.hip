@@ -67,28 +67,34 @@ extern "C" modap_status modap_eval_sweep_static(int device, void *hip_stream, in
     unsigned char *base = nullptr;
     int cus = 0;
     if (modap_status st = scratch_of(device, &base, &cus)) return st;
+    // The layout of this call inside the scratch array.  Long systems of short
+    // rows would take two workgroups per CU; where their partials do not fit,
+    // one, as every other system.
     StaticPlan plan{};
-    if (!static_sweep_plan(dt, lda, m, n, cus, &plan)) return MODAP_E_INVAL;   // rows too long for one pass
-    // the layout of this call inside the scratch array
-    const size_t acc = dt == 0 ? 8 : 4;
-    size_t off = 0;
-    auto take = [&](size_t bytes) {
-        unsigned char *p = base + off;
-        off += up256(bytes);
-        return p;
-    };
     SweepScratch s{};
-    s.ctl = reinterpret_cast<Ctrl *>(take(sizeof(Ctrl)));
-    s.tot = reinterpret_cast<Totals *>(take(sizeof(Totals)));
-    s.bad = reinterpret_cast<unsigned long long *>(take(sizeof(unsigned long long)));
-    s.h_part = reinterpret_cast<int64_t *>(take(sizeof(int64_t) * (size_t)plan.grid));
-    s.dmax_part = reinterpret_cast<double *>(take(sizeof(double) * (size_t)plan.grid));
-    s.binf_part = reinterpret_cast<double *>(take(sizeof(double) * (size_t)plan.grid));
-    s.ynp = reinterpret_cast<double *>(take(sizeof(double) * (size_t)plan.R));
-    s.nu = reinterpret_cast<double *>(take(sizeof(double) * (size_t)m));
-    s.work = take(3 * acc * (size_t)lda);
-    s.part = take(acc * (size_t)plan.grid * (size_t)plan.cov);
-    if (off > kScratchBytes) return MODAP_E_INVAL;      // beyond the static scratch
+    bool fits = false;
+    for (int most = 2; most >= 1 && !fits; --most) {
+        if (!static_sweep_plan(dt, lda, m, n, cus, most, &plan)) return MODAP_E_INVAL;   // rows too long for one pass
+        const size_t acc = dt == 0 ? 8 : 4;
+        size_t off = 0;
+        auto take = [&](size_t bytes) {
+            unsigned char *p = base + off;
+            off += up256(bytes);
+            return p;
+        };
+        s.ctl = reinterpret_cast<Ctrl *>(take(sizeof(Ctrl)));
+        s.tot = reinterpret_cast<Totals *>(take(sizeof(Totals)));
+        s.bad = reinterpret_cast<unsigned long long *>(take(sizeof(unsigned long long)));
+        s.h_part = reinterpret_cast<int64_t *>(take(sizeof(int64_t) * (size_t)plan.grid));
+        s.dmax_part = reinterpret_cast<double *>(take(sizeof(double) * (size_t)plan.grid));
+        s.binf_part = reinterpret_cast<double *>(take(sizeof(double) * (size_t)plan.grid));
+        s.ynp = reinterpret_cast<double *>(take(sizeof(double) * (size_t)plan.R));
+        s.nu = reinterpret_cast<double *>(take(sizeof(double) * (size_t)m));
+        s.work = take(3 * acc * (size_t)lda);
+        s.part = take(acc * (size_t)plan.grid * (size_t)plan.cov);
+        fits = off <= kScratchBytes;
+    }
+    if (!fits) return MODAP_E_INVAL;      // beyond the static scratch
     const hipError_t e = static_sweep_launch(dt, plan, s, A, lda, m, n, b, x, r, y, h, max_viol,
                                              reinterpret_cast<hipStream_t>(hip_stream));
     if (e != hipSuccess) {
