@@ -1665,18 +1665,18 @@ hipError_t aux_row_norms(int dt, const void *A, int64_t ldA, int64_t m, int64_t 
         case 1: hipLaunchKernelGGL(row_norms<1>, dim3(nb), dim3(256), 0, s, A, ldA, m, n, nu, bad); break;
         default: hipLaunchKernelGGL(row_norms<2>, dim3(nb), dim3(256), 0, s, A, ldA, m, n, nu, bad); break;
     }
-    return hipPeekAtLastError();
+    return hipGetLastError();
 }
 
 hipError_t aux_check_finite(const double *p, int64_t np, const double *q, int64_t nq, unsigned long long *flag,
                             hipStream_t s) {
     hipLaunchKernelGGL(check_finite, dim3(64), dim3(256), 0, s, p, np, q, nq, flag);
-    return hipPeekAtLastError();
+    return hipGetLastError();
 }
 
 hipError_t aux_ctl_init(Ctrl *c, DataChecks *checks, hipStream_t s) {
     hipLaunchKernelGGL(ctl_init, dim3(1), dim3(64), 0, s, c, checks);
-    return hipPeekAtLastError();
+    return hipGetLastError();
 }
 
 hipError_t aux_scatter_rows(int dt, void *A, int64_t ldA, int64_t m, int64_t n, int64_t k, const int64_t *rows,
@@ -1688,34 +1688,34 @@ hipError_t aux_scatter_rows(int dt, void *A, int64_t ldA, int64_t m, int64_t n, 
         case 1: hipLaunchKernelGGL(scatter_rows<1>, dim3(k), dim3(256), 0, s, A, ldA, m, n, rows, new_rows, new_b, b, bref, nu, ctl, sl, vpend, V, ldV, wsum); break;
         default: hipLaunchKernelGGL(scatter_rows<2>, dim3(k), dim3(256), 0, s, A, ldA, m, n, rows, new_rows, new_b, b, bref, nu, ctl, sl, vpend, V, ldV, wsum); break;
     }
-    return hipPeekAtLastError();
+    return hipGetLastError();
 }
 
 hipError_t aux_claim_rows(const int64_t *rows, int64_t k, int64_t m, int *claim, Ctrl *ctl, int sl, hipStream_t s) {
     const int grid = (int)std::min<int64_t>(1024, (k + 255) / 256);
     hipLaunchKernelGGL(claim_rows, dim3(grid), dim3(256), 0, s, rows, k, m, claim, ctl, sl);
-    return hipPeekAtLastError();
+    return hipGetLastError();
 }
 
 hipError_t aux_release_rows(const int64_t *rows, int64_t k, int64_t m, int *claim, hipStream_t s) {
     const int grid = (int)std::min<int64_t>(1024, (k + 255) / 256);
     hipLaunchKernelGGL(release_rows, dim3(grid), dim3(256), 0, s, rows, k, m, claim);
-    return hipPeekAtLastError();
+    return hipGetLastError();
 }
 
 hipError_t aux_vpend_add(Ctrl *c, int sl, double *vpend, const double *v, int64_t n, hipStream_t s) {
     hipLaunchKernelGGL(vpend_add, dim3(1), dim3(1024), 0, s, c, sl, vpend, v, n);
-    return hipPeekAtLastError();
+    return hipGetLastError();
 }
 
 hipError_t aux_sched_to_vpend(Ctrl *c, int sl, double *vpend, const double *V, int64_t ldV, int64_t n, hipStream_t s) {
     hipLaunchKernelGGL(sched_to_vpend, dim3(1), dim3(1024), 0, s, c, sl, vpend, V, ldV, n);
-    return hipPeekAtLastError();
+    return hipGetLastError();
 }
 
 hipError_t aux_ctl_set_drift(Ctrl *c, int sl, int64_t T, hipStream_t s) {
     hipLaunchKernelGGL(ctl_set_drift, dim3(1), dim3(64), 0, s, c, sl, T);
-    return hipPeekAtLastError();
+    return hipGetLastError();
 }
 
 hipError_t aux_rhs_exact(int dt, const void *A, int64_t ldA, int64_t m, int64_t n, const Ctrl *ctl, int sl,
@@ -1727,7 +1727,7 @@ hipError_t aux_rhs_exact(int dt, const void *A, int64_t ldA, int64_t m, int64_t 
         case 1: hipLaunchKernelGGL(rhs_exact<1>, dim3(nb), dim3(256), 0, s, A, ldA, m, n, ctl, sl, bref, wsum, vpend, V, ldV, out); break;
         default: hipLaunchKernelGGL(rhs_exact<2>, dim3(nb), dim3(256), 0, s, A, ldA, m, n, ctl, sl, bref, wsum, vpend, V, ldV, out); break;
     }
-    return hipPeekAtLastError();
+    return hipGetLastError();
 }
 
 bool static_sweep_plan(int dt, int64_t ldA, int64_t m, int64_t n, int cu_count, int per_cu, StaticPlan *out) {
@@ -1763,7 +1763,7 @@ hipError_t static_sweep_launch(int dt, const StaticPlan &plan, const SweepScratc
         case 1: hipLaunchKernelGGL(static_begin<1>, dim3(nb + sg), dim3(256), 0, stream, A, ldA, m, n, s.nu, s.bad, x, s.work, s.ctl, nb); break;
         default: hipLaunchKernelGGL(static_begin<2>, dim3(nb + sg), dim3(256), 0, stream, A, ldA, m, n, s.nu, s.bad, x, s.work, s.ctl, nb); break;
     }
-    hipError_t e = hipPeekAtLastError();
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     SweepArgs a{};
     a.A = A;
@@ -1808,7 +1808,7 @@ hipError_t static_sweep_launch(int dt, const StaticPlan &plan, const SweepScratc
         hipLaunchKernelGGL(reduce_y<double>, dim3(plan.R), dim3(kReduceThreads), 0, stream, ra);
     else
         hipLaunchKernelGGL(reduce_y<float>, dim3(plan.R), dim3(kReduceThreads), 0, stream, ra);
-    return hipPeekAtLastError();
+    return hipGetLastError();
 }
 
 CertPlan cert_plan(int dt, int64_t m, int64_t n, int64_t ldA, int64_t workgroups) {
@@ -1875,7 +1875,7 @@ hipError_t aux_certify(int dt, const CertArgs &a, const CertPlan &p, hipStream_t
         case 1: launch_cert<1>(a, p, s); break;
         default: launch_cert<2>(a, p, s); break;
     }
-    return hipPeekAtLastError();
+    return hipGetLastError();
 }
 
 hipError_t aux_certify_list(int dt, const CertArgs *list, int count, const CertJob *jobs, int ndot, int naxpy,
@@ -1885,7 +1885,7 @@ hipError_t aux_certify_list(int dt, const CertArgs *list, int count, const CertJ
         case 1: launch_cert_list<1>(list, count, jobs, ndot, naxpy, nreduce, s); break;
         default: launch_cert_list<2>(list, count, jobs, ndot, naxpy, nreduce, s); break;
     }
-    return hipPeekAtLastError();
+    return hipGetLastError();
 }
 
 }  // namespace modap

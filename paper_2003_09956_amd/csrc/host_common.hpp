@@ -34,8 +34,11 @@ modap_status fail(Ctx *c, modap_status st, const std::string &msg) {
     return st;
 }
 
+// (The runtime keeps the error for whoever asks next, and the next launch of
+// this thread, ours or another library's, would report it for its own.)
 template <typename Ctx>
 modap_status hip_fail(Ctx *c, hipError_t e, const char *what) {
+    (void)hipGetLastError();
     if (e == hipErrorOutOfMemory) return fail(c, MODAP_E_NOMEM, std::string(what) + ": out of device memory");
     return fail(c, MODAP_E_DEVICE, std::string(what) + ": " + hipGetErrorString(e));
 }
@@ -82,9 +85,6 @@ struct Pieces {
 
 #define LAUNCH_TRY(c, what)                                             \
     do {                                                                \
-        hipError_t e_ = hipPeekAtLastError();                           \
-        if (e_ != hipSuccess) {                                         \
-            (void)hipGetLastError();                                    \
-            return ::modap_host::hip_fail((c), e_, what);               \
-        }                                                               \
+        hipError_t e_ = hipGetLastError();                              \
+        if (e_ != hipSuccess) return ::modap_host::hip_fail((c), e_, what); \
     } while (0)

@@ -153,7 +153,7 @@ struct Readback {
         a.seq = ++seq;
         const int grid = a.count[0] + a.count[1] <= modap::kPublishAlone ? 1 : 32;
         hipLaunchKernelGGL(modap::publish, dim3(grid), dim3(256), 0, s, a);
-        const hipError_t e = hipPeekAtLastError();
+        const hipError_t e = hipGetLastError();
         return e == hipSuccess ? wait(s) : e;
     }
 };

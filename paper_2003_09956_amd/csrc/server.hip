@@ -143,6 +143,7 @@ modap_status take_stage(modap_server *s, size_t bytes, Stage **out) {
     Stage t;
     t.size = (bytes + (1u << 20) - 1) / (1u << 20) * (1u << 20);
     if (hipMalloc(&t.p, t.size) != hipSuccess) {
+        (void)hipGetLastError();
         s->err = "no device memory to stage an update";
         return MODAP_E_NOMEM;
     }
@@ -187,7 +188,10 @@ hipError_t take_stream(modap_server *s, Req &r) {
         return hipSuccess;
     }
     const hipError_t e = hipStreamCreateWithFlags(&r.stream, hipStreamNonBlocking);
-    if (e != hipSuccess) r.stream = nullptr;
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        r.stream = nullptr;
+    }
     return e;
 }
 
@@ -401,6 +405,7 @@ modap_status modap_server_submit(modap_server *s, int64_t m, int64_t n, const vo
                                  sizeof(double) * (size_t)n, (size_t)T, hipMemcpyDeviceToDevice, s->copy_stream);
         if (e == hipSuccess) e = hipStreamSynchronize(s->copy_stream);
         if (e != hipSuccess) {
+            (void)hipGetLastError();
             release_inputs(r);
             return fail(s, e == hipErrorOutOfMemory ? MODAP_E_NOMEM : MODAP_E_DEVICE,
                         std::string("copying the request's inputs: ") + hipGetErrorString(e));
