@@ -161,34 +161,14 @@ int chunks_for(int dt, int64_t ldA) {
 modap_status ensure_stage(modap_batch *c, size_t bytes) {
     if (bytes <= c->stage_bytes) return MODAP_OK;
     HIP_TRY(c, hipStreamSynchronize(c->stream));
-    free_dev(c->stage);
-    HIP_TRY(c, hipMalloc(&c->stage, bytes));
-    c->stage_bytes = bytes;
+    HIP_TRY(c, grow_dev(c->stage, c->stage_bytes, bytes, 1));
     return MODAP_OK;
 }
 
 template <typename P>
 modap_status ensure_buf(modap_batch *c, P *&p, size_t &cap, size_t count) {
     if (count <= cap) return MODAP_OK;
-    free_dev(p);
-    const size_t want = std::max(count, cap * 2);
-    HIP_TRY(c, hipMalloc(&p, sizeof(P) * want));
-    cap = want;
-    return MODAP_OK;
-}
-
-// As ensure_buf for bytes, without room to grow into; nothing is kept on failure.
-modap_status ensure_bytes(modap_batch *c, unsigned char *&p, size_t &cap, size_t bytes) {
-    if (bytes <= cap) return MODAP_OK;
-    free_dev(p);
-    cap = 0;
-    const hipError_t e = hipMalloc(&p, bytes);
-    if (e != hipSuccess) {
-        p = nullptr;
-        (void)hipGetLastError();
-        return hip_fail(c, e, "hipMalloc");
-    }
-    cap = bytes;
+    HIP_TRY(c, grow_dev(p, cap, std::max(count, cap * 2), sizeof(P)));
     return MODAP_OK;
 }
 
@@ -283,23 +263,17 @@ modap_status rebuild(modap_batch *c) {
     }
     modap_status st;
     if ((st = ensure_buf(c, c->d_sys, c->sys_cap, std::max<size_t>(1, c->h_sys.size())))) return st;
-    size_t cap = c->prt_cap;
-    if ((st = ensure_buf(c, c->h_part, cap, std::max<size_t>(1, (size_t)parts)))) return st;
-    if (cap != c->prt_cap) {
-        size_t c3 = 0, c4 = 0;
-        free_dev(c->dmax_part);
-        free_dev(c->binf_part);
-        if ((st = ensure_buf(c, c->dmax_part, c3, cap)) || (st = ensure_buf(c, c->binf_part, c4, cap))) return st;
+    if (const size_t want = std::max<size_t>(1, (size_t)parts); want > c->prt_cap) {
+        size_t cap = std::max(want, 2 * c->prt_cap), c2 = 0, c3 = 0, c4 = 0;
+        c->prt_cap = 0;
+        if ((st = ensure_buf(c, c->h_part, c2, cap)) || (st = ensure_buf(c, c->dmax_part, c3, cap)) ||
+            (st = ensure_buf(c, c->binf_part, c4, cap)))
+            return st;
         c->prt_cap = cap;
     }
     if ((st = ensure_buf(c, c->d_items, c->item_cap, std::max<size_t>(1, items)))) return st;
     if ((st = ensure_buf(c, c->d_cols, c->cols_cap, std::max<size_t>(1, c->h_cols.size())))) return st;
-    const size_t pbytes = std::max<size_t>(16, (size_t)part * acc_size(c->dt));
-    if (pbytes > c->part_bytes) {
-        free_dev(c->part);
-        HIP_TRY(c, hipMalloc(&c->part, pbytes));
-        c->part_bytes = pbytes;
-    }
+    HIP_TRY(c, grow_dev(c->part, c->part_bytes, std::max<size_t>(16, (size_t)part * acc_size(c->dt)), 1));
     if (!c->h_sys.empty()) {
         HIP_TRY(c, hipMemcpyAsync(c->d_sys, c->h_sys.data(), sizeof(BatchSys) * c->h_sys.size(),
                                   hipMemcpyHostToDevice, c->stream));
@@ -500,10 +474,14 @@ modap_status certify_systems(modap_batch *c, const std::vector<int64_t> &ids, co
     }
     const size_t want = std::min(scratch, std::max(kCertScratch, largest));
     modap_status st;
+    auto grow = [&](size_t bytes) -> modap_status {
+        HIP_TRY(c, grow_dev(c->cert, c->cert_cap, bytes, 1));
+        return MODAP_OK;
+    };
     if (want > c->cert_cap) {
         HIP_TRY(c, hipStreamSynchronize(c->stream));
-        st = ensure_bytes(c, c->cert, c->cert_cap, want);
-        if (st == MODAP_E_NOMEM && want > largest) st = ensure_bytes(c, c->cert, c->cert_cap, largest);   // one at a time
+        st = grow(want);
+        if (st == MODAP_E_NOMEM && want > largest) st = grow(largest);   // one at a time
         if (st) return st;
     }
     // any two neighbouring groups together exceed the scratch; each group's list and jobs are aligned

@@ -247,6 +247,7 @@ modap_status ensure_scalar_parts(modap_ctx *c, int count) {
     free_dev(c->h_part);
     free_dev(c->dmax_part);
     free_dev(c->binf_part);
+    c->part_grid = 0;
     HIP_TRY(c, hipMalloc(&c->h_part, sizeof(int64_t) * count));
     HIP_TRY(c, hipMalloc(&c->dmax_part, sizeof(double) * count));
     HIP_TRY(c, hipMalloc(&c->binf_part, sizeof(double) * count));
@@ -255,10 +256,7 @@ modap_status ensure_scalar_parts(modap_ctx *c, int count) {
 }
 
 modap_status ensure_part(modap_ctx *c, size_t need) {
-    if (need <= c->part_bytes) return MODAP_OK;
-    free_dev(c->part);
-    HIP_TRY(c, hipMalloc(&c->part, need));
-    c->part_bytes = need;
+    HIP_TRY(c, grow_dev(c->part, c->part_bytes, need, 1));
     return MODAP_OK;
 }
 
@@ -279,11 +277,7 @@ modap_status configure_split(modap_ctx *c, modap_tile t) {
     modap_status st;
     if ((st = ensure_part(c, (size_t)bands * (size_t)ntiles * (size_t)tw * acc))) return st;
     const size_t pd = 2 * (size_t)ntiles * (size_t)c->m * acc;
-    if (pd > c->pdot_bytes) {
-        free_dev(c->pdot);
-        HIP_TRY(c, hipMalloc(&c->pdot, pd));
-        c->pdot_bytes = pd;
-    }
+    HIP_TRY(c, grow_dev(c->pdot, c->pdot_bytes, pd, 1));
     if (!c->wrow) HIP_TRY(c, hipMalloc(&c->wrow, sizeof(double) * (size_t)c->m));
     c->finish_blocks = (int)((c->m + 255) / 256);
     if ((st = ensure_scalar_parts(c, c->finish_blocks))) return st;
@@ -366,9 +360,7 @@ modap_status check_params(modap_ctx *c, const modap_params *p) {
 modap_status ensure_stage(modap_ctx *c, size_t bytes) {
     if (bytes <= c->stage_bytes) return MODAP_OK;
     HIP_TRY(c, hipStreamSynchronize(c->stream));
-    free_dev(c->stage);
-    HIP_TRY(c, hipMalloc(&c->stage, bytes));
-    c->stage_bytes = bytes;
+    HIP_TRY(c, grow_dev(c->stage, c->stage_bytes, bytes, 1));
     return MODAP_OK;
 }
 

@@ -53,6 +53,22 @@ void free_dev(P *&p) {
     p = nullptr;
 }
 
+// A device buffer of at least `count` elements of `each` bytes, its contents
+// not kept.  A failure leaves no buffer and a capacity of none, so that the next
+// call, which may need less, asks again.
+template <typename P>
+hipError_t grow_dev(P *&p, size_t &cap, size_t count, size_t each) {
+    if (count <= cap) return hipSuccess;
+    free_dev(p);
+    cap = 0;
+    const hipError_t e = hipMalloc(reinterpret_cast<void **>(&p), count * each);
+    if (e == hipSuccess)
+        cap = count;
+    else
+        p = nullptr;
+    return e;
+}
+
 // Several arrays in one device allocation (of each system, the vectors and
 // small results): an allocation and a release each time a system comes and
 // goes, in place of a dozen.
