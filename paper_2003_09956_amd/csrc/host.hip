@@ -1388,31 +1388,36 @@ modap_status modap_solve(modap_ctx *c, const modap_params *p, modap_stats *out) 
         int64_t queued = 0, chunk = 16, settled = 0;
         int64_t prev_end = first - 1, last_end = first - 1;   // last checks of the two newest resident launches
         uint32_t idle = 0;
-        *static_cast<volatile uint64_t *>(&c->rb.view->progress) = 0;   // (nothing that writes it is queued)
-        while (queued < total) {
-            const uint64_t w = *static_cast<volatile uint64_t *>(&c->rb.view->progress);
-            if (w != 0) {
-                if ((w & 0xff) != ST_RUNNING) break;
-                const int64_t now_settled = (int64_t)(w >> 8) - first;
-                if (now_settled != settled) idle = 0;
-                settled = now_settled;
-            }
-            const bool room = resident ? first - 1 + settled >= prev_end : queued - settled < ahead;
-            if (!room) {
+        bool stopped = false;
+        volatile uint64_t *word = &c->rb.view->progress;
+        *word = 0;   // (nothing that writes it is queued)
+        auto look = [&]() {
+            const uint64_t w = *word;
+            if (w == 0) return;
+            stopped = (w & 0xff) != ST_RUNNING;
+            const int64_t now_settled = (int64_t)(w >> 8) - first;
+            if (now_settled != settled) idle = 0;
+            settled = now_settled;
+        };
+        auto room = [&]() { return resident ? first - 1 + settled >= prev_end : queued - settled < ahead; };
+        while (queued < total && !stopped) {
+            // a chunk: what there is room for, and the wait until there is more
+            TraceRange trace_chunk("modap_solve chunk");
+            do {
+                if (resident) {
+                    const int64_t cnt = std::min(chunk, total - queued);
+                    if ((st = launch_resident(c, p, 0, cnt, &c->rb.dev->progress, &bytes))) return st;
+                    queued += cnt;
+                    prev_end = last_end;
+                    last_end = c->jn - 1;
+                    chunk = std::min<int64_t>(chunk * 2, 1024);
+                } else {
+                    if ((st = enqueue_iteration(c, p, 0, queued, &c->rb.dev->progress, &ev, &bytes))) return st;
+                    ++queued;
+                }
+            } while (queued < total && room());
+            for (look(); queued < total && !stopped && !room(); look())
                 if ((st = poll_pause(c, ++idle))) return st;
-                continue;
-            }
-            if (resident) {
-                const int64_t cnt = std::min(chunk, total - queued);
-                if ((st = launch_resident(c, p, 0, cnt, &c->rb.dev->progress, &bytes))) return st;
-                queued += cnt;
-                prev_end = last_end;
-                last_end = c->jn - 1;
-                chunk = std::min<int64_t>(chunk * 2, 1024);
-            } else {
-                if ((st = enqueue_iteration(c, p, 0, queued, &c->rb.dev->progress, &ev, &bytes))) return st;
-                ++queued;
-            }
         }
         if (!resident && (st = enqueue_settle(c, p, 0))) return st;
         if ((st = read_back(c, &kc))) return st;

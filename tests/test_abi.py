@@ -158,3 +158,15 @@ def test_loading_the_library_first_maps_one_hip_runtime():
     r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=600)
     assert r.returncode == 0, r.stderr[-2000:]
     assert r.stdout.strip().splitlines()[-1] == "1", r.stdout
+
+
+def test_tracing_ranges_are_where_the_documents_say():
+    """A range per call, per chunk of iterations that a solve queues (inside the solve's) and per
+    served request."""
+    csrc = os.path.join(ROOT, "paper_2003_09956_amd", "csrc")
+    host = open(os.path.join(csrc, "host.hip")).read()
+    solve = host[host.index("modap_status modap_solve("):]
+    solve = solve[:solve.index("\n}\n")]
+    names = re.findall(r'TraceRange \w+\("([^"]+)"\)', solve)
+    assert names == ["modap_solve", "modap_solve chunk"]
+    assert 'trace_start("modap request")' in open(os.path.join(csrc, "server.hip")).read()
