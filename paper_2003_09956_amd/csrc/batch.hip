@@ -913,7 +913,7 @@ modap_status modap_batch_solve(modap_batch *c, const modap_params *p, modap_batc
     // Passes of queued iterations until no system runs; stops that the FP64
     // certificate does not confirm have taken a step instead, and the next
     // pass goes on from there (the step limits are the devices').
-    const int64_t ahead = 10.0 + c->bytes_per_iter / 6e6 > 100.0 ? 2 : 4;   // as for a single system's solve
+    int64_t ahead = 10.0 + c->bytes_per_iter / 6e6 > 100.0 ? 2 : 4;   // as for a single system's solve
     int64_t running = 0;
     for (;;) {
         // Each reduction tells the host how many systems run on after the
@@ -931,6 +931,7 @@ modap_status modap_batch_solve(modap_batch *c, const modap_params *p, modap_batc
                 const int64_t now_settled = (int64_t)((uint32_t)(w >> 32) - (uint32_t)(first + 1));
                 if (now_settled != settled) idle = 0;
                 settled = now_settled;
+                ahead = solve_ahead_after(ahead, queued - settled, settled);
             }
             if (queued - settled >= ahead) {
                 if ((st = poll_pause(c, ++idle))) return st;

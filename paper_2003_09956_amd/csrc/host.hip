@@ -1378,7 +1378,7 @@ modap_status modap_solve(modap_ctx *c, const modap_params *p, modap_stats *out) 
     // eps-feasibility that the FP64 certificate does not confirm has taken a
     // step instead, and the next pass goes on from there.  The step limit is
     // the device's, so a pass may queue more iterations than remain.
-    const int64_t ahead = resident ? 0 : solve_ahead(c);
+    int64_t ahead = resident ? 0 : solve_ahead(c);
     for (;;) {
         // Each sweep tells the host the decision it takes on the previous
         // check (a resident launch its last one).  The host keeps a few
@@ -1398,6 +1398,7 @@ modap_status modap_solve(modap_ctx *c, const modap_params *p, modap_stats *out) 
             const int64_t now_settled = (int64_t)(w >> 8) - first;
             if (now_settled != settled) idle = 0;
             settled = now_settled;
+            ahead = solve_ahead_after(ahead, queued - settled, settled);
         };
         auto room = [&]() { return resident ? first - 1 + settled >= prev_end : queued - settled < ahead; };
         while (queued < total && !stopped) {
