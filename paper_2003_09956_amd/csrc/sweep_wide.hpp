@@ -58,6 +58,13 @@ __device__ __forceinline__ T pair_sum(T (&v)[N]) {
     return v[0];
 }
 
+// The value of a load that a ring keeps in flight, taken where it is used.
+template <bool AT_USE>
+__device__ __forceinline__ double taken(double v) {
+    if constexpr (AT_USE) asm volatile("" : "+v"(v));
+    return v;
+}
+
 template <int DT>
 __device__ __forceinline__ void unpack(const uint4 &u, typename Store<DT>::Acc (&o)[Store<DT>::VEC]);
 
@@ -273,6 +280,14 @@ __global__ __launch_bounds__(BLOCK) void sweep_wide(const SweepArgs a) {
         __syncthreads();
     };
 
+    // Without a translation b is used as it comes, and in rings of more than two
+    // steps or several rows a step the compiler then forms |b| (and what else needs
+    // only b or ||a||^2) where the value was requested, beside the rows ahead, and
+    // waits for each as it is issued.  Taken at its use, a sweep without a
+    // translation is as fast as one with (us, 400 MB of FP64 256: 73 for 122, FP64
+    // 2048 70 for 85, FP32 256 76 for 132, 768 65 for 95, BF16 512 116 for 204, 1536
+    // 68 for 98, 8192 72 for 110).
+    constexpr bool kTaken = !HAS_V && (RS > 1 || PD > 2);
     auto process = [&](const uint4 (&buf)[RS][C], const double (&bi)[RS], const double (&nui)[RS], int64_t t) {
         // A lane's products are added in chains of two chunks, and the chains
         // neighbours first: one chain over all chunks rounds more the fewer
@@ -335,7 +350,8 @@ __global__ __launch_bounds__(BLOCK) void sweep_wide(const SweepArgs a) {
 #pragma unroll
             for (int q = 0; q < RS; ++q) {
                 const bool ok = row_of(t, q) < r1;
-                double bb = bi[q];
+                const double nu = taken<kTaken>(nui[q]);
+                double bb = taken<kTaken>(bi[q]);
                 if (apply_v) bb += (double)tdot[q];
                 const double r = ok ? (double)dot[q] - bb : -1.0;
                 const int si = (int)(t % KS) * SR + grp * RS + q;
@@ -344,9 +360,9 @@ __global__ __launch_bounds__(BLOCK) void sweep_wide(const SweepArgs a) {
                 if (ok) binf = max_nan(binf, fabs(bb));
                 const bool pos = r > 0.0;
                 h += pos ? 1 : 0;
-                const double d = r / sqrt(nui[q]);
+                const double d = r / sqrt(nu);
                 dmax = pos ? max_nan(dmax, d) : (r != r ? r : dmax);
-                const Acc w = pos ? (Acc)(r / nui[q]) : (Acc)0;
+                const Acc w = pos ? (Acc)(r / nu) : (Acc)0;
 #pragma unroll
                 for (int c = 0; c < C; ++c) {
                     Acc av[VEC];
@@ -361,7 +377,8 @@ __global__ __launch_bounds__(BLOCK) void sweep_wide(const SweepArgs a) {
         for (int q = 0; q < RS; ++q) {
             const int64_t row = row_of(t, q);
             if (row >= r1) continue;
-            double bb = bi[q];
+            const double nu = taken<kTaken>(nui[q]);
+            double bb = taken<kTaken>(bi[q]);
             if (apply_v) bb += (double)tdot[q];
             const double r = (double)dot[q] - bb;
             const int si = (int)(t % KS) * SR + grp * RS + q;
@@ -370,8 +387,8 @@ __global__ __launch_bounds__(BLOCK) void sweep_wide(const SweepArgs a) {
             binf = max_nan(binf, fabs(bb));
             if (r > 0.0) {
                 ++h;
-                dmax = max_nan(dmax, r / sqrt(nui[q]));
-                const Acc w = (Acc)(r / nui[q]);
+                dmax = max_nan(dmax, r / sqrt(nu));
+                const Acc w = (Acc)(r / nu);
 #pragma unroll
                 for (int c = 0; c < C; ++c) {
                     Acc av[VEC];
