@@ -186,27 +186,38 @@ constexpr int64_t kMaxBandRows = 4096;  // rows per band of the split-row form (
 //    it (BF16 12000 x 30000: 119.7 us with three chunks, 122.7 with four).
 //    12-chunk wavefronts still beat 256 lanes on BF16 rows of 8 to 12 KiB
 //    (6000 x 18000: 51.6 against 60.2).
+//  - on systems of fewer rows than `few`, rows of a wavefront with six and more
+//    chunks are spread over two or four wavefronts (the same vectors: 128 lanes
+//    of 3 chunks for 64 of 6, 256 of 2 for 8, 256 of 3 for 12).  There a row's own
+//    time counts, and below four rows a CU a band of four leaves CUs idle: BF16
+//    4000 x 300 14.5 us an iteration with a wavefront a row and 11.0, 6000 x 2000
+//    22.1 and 17.7, x 5000 27.3 and 25.1; FP64 1500 x 600 12.2 and 11.1, x 2500 15.4
+//    and 15.6; FP32 2000 x 600 10.9 and 10.1, x 2000 12.5 and 13.0.
 // Rows longer than the last entry take the split-row form.
 struct ShapeFor {
     int32_t row;    // longest padded row
     int32_t block, lpr, chunks, rs, pd;
+    int32_t few;    // systems of fewer rows spread the row over more lanes (0: none)
 };
 constexpr ShapeFor kShapesF64[] = {
-    {32, 256, 16, 1, 1, 2},    {64, 256, 16, 2, 1, 2},    {128, 256, 16, 4, 1, 2},   {256, 256, 64, 2, 2, 2},
-    {384, 256, 64, 3, 2, 2},   {512, 256, 64, 4, 1, 2},   {768, 256, 64, 6, 1, 3},   {1024, 256, 64, 8, 1, 2},
-    {1536, 256, 64, 12, 1, 2}, {2048, 256, 256, 4, 1, 4}, {3072, 256, 256, 6, 1, 2}, {4096, 256, 256, 8, 1, 2},
-    {6144, 512, 512, 6, 1, 2}, {8192, 512, 512, 8, 1, 2}};
+    {32, 256, 16, 1, 1, 2},      {64, 256, 16, 2, 1, 2},      {128, 256, 16, 4, 1, 2},   {256, 256, 64, 2, 2, 2},
+    {384, 256, 64, 3, 2, 2},     {512, 256, 64, 4, 1, 2},     {768, 256, 64, 6, 1, 3, 1000},
+    {1024, 256, 64, 8, 1, 2, 1000}, {1536, 256, 64, 12, 1, 2, 2000},
+    {2048, 256, 256, 4, 1, 4},   {3072, 256, 256, 6, 1, 2},   {4096, 256, 256, 8, 1, 2}, {6144, 512, 512, 6, 1, 2},
+    {8192, 512, 512, 8, 1, 2}};
 constexpr ShapeFor kShapesF32[] = {
-    {64, 256, 16, 1, 1, 2},    {128, 256, 16, 2, 1, 2},   {256, 512, 64, 1, 1, 4},   {512, 512, 64, 2, 2, 2},
-    {768, 256, 64, 3, 1, 3},   {1024, 256, 64, 4, 1, 2},  {1536, 256, 64, 6, 1, 3},  {2048, 256, 64, 8, 1, 2},
-    {4096, 512, 256, 4, 1, 2}, {6144, 256, 256, 6, 1, 2}, {8192, 256, 256, 8, 1, 2}, {12288, 512, 512, 6, 1, 2},
+    {64, 256, 16, 1, 1, 2},      {128, 256, 16, 2, 1, 2},     {256, 512, 64, 1, 1, 4},   {512, 512, 64, 2, 2, 2},
+    {768, 256, 64, 3, 1, 3},     {1024, 256, 64, 4, 1, 2},    {1536, 256, 64, 6, 1, 3, 1500},
+    {2048, 256, 64, 8, 1, 2, 1500},
+    {4096, 512, 256, 4, 1, 2},   {6144, 256, 256, 6, 1, 2},   {8192, 256, 256, 8, 1, 2}, {12288, 512, 512, 6, 1, 2},
     {16384, 512, 512, 8, 1, 2}};
 constexpr ShapeFor kShapesBF16[] = {
-    {128, 256, 16, 1, 1, 2},   {256, 256, 16, 2, 1, 2},   {512, 256, 64, 1, 2, 2},   {1024, 256, 64, 2, 1, 2},
-    {1536, 256, 64, 3, 1, 3},  {2048, 256, 64, 4, 1, 2},  {3072, 256, 64, 6, 1, 2},  {4096, 256, 64, 8, 1, 3},
-    {6144, 256, 64, 12, 1, 2}, {8192, 512, 512, 2, 2, 2}, {12288, 512, 512, 3, 1, 2}, {16384, 512, 512, 4, 1, 2}};
+    {128, 256, 16, 1, 1, 2},     {256, 256, 16, 2, 1, 2},     {512, 256, 64, 1, 2, 2},   {1024, 256, 64, 2, 1, 2},
+    {1536, 256, 64, 3, 1, 3},    {2048, 256, 64, 4, 1, 2},    {3072, 256, 64, 6, 1, 2, 3500},
+    {4096, 256, 64, 8, 1, 3, 3500}, {6144, 256, 64, 12, 1, 2, 5000},
+    {8192, 512, 512, 2, 2, 2},   {12288, 512, 512, 3, 1, 2},  {16384, 512, 512, 4, 1, 2}};
 
-// Two exceptions by the number of rows.  FP64 rows of 65 to 128 elements: four
+// Two more exceptions by the number of rows.  FP64 rows of 65 to 128 elements: four
 // rows to a wavefront leave compute units idle on short systems (120 x 480:
 // 9.8 us against 8.4 with a wavefront a row, 120 x 4096 12.3 and 11.5, but
 // 120 x 16384 14.9 and 16.1).  And 16-lane rows of long systems take two
@@ -234,7 +245,13 @@ void choose_shape(int dt, int64_t ldA, int64_t m, int cu_count, modap_tile *out)
     out->chunks = t->chunks;
     out->rows_per_step = t->rs;
     out->depth = t->pd;
-    if (dt == 0 && t->row == 128 && m < kFewRowsF64) {
+    if (m < t->few) {
+        out->block = 256;
+        out->lanes_per_row = t->chunks == 6 ? 128 : 256;
+        out->chunks = t->chunks * t->lpr / out->lanes_per_row;
+        out->rows_per_step = 1;
+        out->depth = 2;
+    } else if (dt == 0 && t->row == 128 && m < kFewRowsF64) {
         out->lanes_per_row = 64;
         out->chunks = 1;
     } else if (t->lpr < 64 && m >= kManyRows) {

@@ -16,7 +16,8 @@
     MODAP_SHAPE(512, 512, 4, 1, 3), MODAP_SHAPE(512, 512, 4, 1, 4),                                      \
     MODAP_SHAPE(1024, 1024, 2, 1, 3),  \
     MODAP_SHAPE(512, 64, 1, 1, 4), MODAP_SHAPE(512, 64, 2, 2, 2), MODAP_SHAPE(256, 64, 3, 1, 3), \
-    MODAP_SHAPE(256, 64, 6, 1, 3), MODAP_SHAPE(256, 64, 8, 1, 2), MODAP_SHAPE(256, 256, 6, 1, 2), MODAP_SHAPE(512, 512, 6, 1, 2)
+    MODAP_SHAPE(256, 64, 6, 1, 3), MODAP_SHAPE(256, 64, 8, 1, 2), MODAP_SHAPE(256, 256, 6, 1, 2), MODAP_SHAPE(512, 512, 6, 1, 2), \
+    MODAP_SHAPE(256, 128, 3, 1, 2)
 // split-row form: 256 lanes x 8 chunks per column tile
 #define MODAP_SPLIT_C 8
 #include "sweep_inst.inc"
