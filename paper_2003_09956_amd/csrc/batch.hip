@@ -227,7 +227,7 @@ modap_status rebuild(modap_batch *c) {
         const BatchCut cut = cut_of(c, s, d.RPW, d.C, c->tile);
         const int64_t row_bytes = s.ldA * (int64_t)c->es;
         const int64_t ncells = (s.m + cut.rows_per_cell - 1) / cut.rows_per_cell;
-        const int64_t per_item = plan_cells_per_item(cut, row_bytes, all_bytes, c->grid);
+        const int64_t per_item = plan_cells_per_item(cut, row_bytes, all_bytes, c->grid, c->cu_count);
         d.rows_per_cell = cut.rows_per_cell;
         d.G = cut.cells;
         d.grouped = per_item == cut.cells;
@@ -1113,7 +1113,7 @@ modap_status modap_batch_autotune(modap_batch *c, int reps, modap_batch_tile *be
                 kernel_form(c->dt, s, &rpw, &chunks);
                 const BatchCut cut = cut_of(c, s, rpw, chunks, t);
                 v.insert(v.end(), {cut.rows_per_cell, cut.cells,
-                                   plan_cells_per_item(cut, s.ldA * (int64_t)c->es, total, grid)});
+                                   plan_cells_per_item(cut, s.ldA * (int64_t)c->es, total, grid, c->cu_count)});
             }
         return v;
     };

@@ -46,18 +46,21 @@ inline BatchCut plan_cut(int64_t m, int64_t ldA, int64_t elem_bytes, int32_t ite
     return c;
 }
 
-// Cells of one work item: whole groups in a batch that fills the device with
-// them, fewer cells in a smaller one, so that it has about kItemsPerWorkgroup
-// items for each workgroup of the grid.  Cells that are written one by one
-// spread a small batch over the device (seven BF16 systems of 78 MB in all:
-// 210 us an iteration as 56 groups, 56 as 184 cells), but writing and
-// reading back eight times the partials costs a large one (the 512-system
-// family, 15.8 GB: 2.65 ms a sweep by cells, 2.36 by groups).
+// Cells of one work item: whole groups in a batch that has them for every CU,
+// fewer cells in a smaller one, so that it has about kItemsPerWorkgroup items for
+// each workgroup of the grid.  Cells that are written one by one spread a small
+// batch over the device (seven BF16 systems of 78 MB in all: 210 us an iteration
+// as 56 groups, 56 as 184 cells), but writing and reading back eight times the
+// partials costs a larger one.  The line is at 7/4 groups a CU (us an iteration by
+// groups and by cells: FP32 1400 x 3000, 2.0 a CU 179 and 223, 4.0 351 and 423;
+// FP64 700 x 3000, 1.5 160 and 154, 2.0 181 and 207; BF16 2000 x 4000, 1.5 179 and
+// 172, 1.75 183 and 200; FP64 1000 x 10000, 1.25 516 and 448, 1.9 611 and 654).
 constexpr int64_t kItemsPerWorkgroup = 4;
-inline int64_t plan_cells_per_item(const BatchCut &cut, int64_t row_bytes, int64_t batch_bytes, int64_t grid) {
-    const int64_t want = batch_bytes / std::max<int64_t>(1, grid * kItemsPerWorkgroup);
-    const int64_t cells = std::max<int64_t>(1, want / (cut.rows_per_cell * row_bytes));
-    return 2 * cells > cut.cells ? cut.cells : cells;
+inline int64_t plan_cells_per_item(const BatchCut &cut, int64_t row_bytes, int64_t batch_bytes, int64_t grid, int64_t cus) {
+    const int64_t cell = cut.rows_per_cell * row_bytes;
+    if (4 * batch_bytes >= 7 * cus * cell * cut.cells) return cut.cells;
+    const int64_t cells = std::max<int64_t>(1, batch_bytes / std::max<int64_t>(1, grid * kItemsPerWorkgroup) / cell);
+    return std::min<int64_t>(cells, cut.cells);
 }
 
 // Row form of a system: rows of at most 64 16-byte vectors (C == 1) run four
