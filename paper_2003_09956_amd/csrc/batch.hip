@@ -179,6 +179,20 @@ BatchCut cut_of(const modap_batch *c, const BSys &s, int32_t rpw, int32_t chunks
                     batch_depth(rpw, chunks) * kBatchWaves * rpw, kGroupCells);
 }
 
+// Bytes of A in the batch, and in the largest group that a tile cuts it into.
+void batch_sizes(const modap_batch *c, const modap_batch_tile &t, int64_t *total, int64_t *largest_group) {
+    *total = *largest_group = 0;
+    for (const BSys &s : c->sys) {
+        if (!s.alive) continue;
+        int32_t rpw = 1, chunks = 1;
+        kernel_form(c->dt, s, &rpw, &chunks);
+        const BatchCut cut = cut_of(c, s, rpw, chunks, t);
+        const int64_t row_bytes = s.ldA * (int64_t)c->es;
+        *total += s.m * row_bytes;
+        *largest_group = std::max(*largest_group, std::min(s.m, cut.cells * cut.rows_per_cell) * row_bytes);
+    }
+}
+
 const void *sweep_fn(int dt);
 
 modap_status rebuild(modap_batch *c) {
@@ -197,9 +211,8 @@ modap_status rebuild(modap_batch *c) {
          c->per_cu < 1))
         c->per_cu = 1;
     c->grid = c->tile.grid > 0 ? c->tile.grid : c->cu_count * c->per_cu;
-    int64_t all_bytes = 0;
-    for (const BSys &s : c->sys)
-        if (s.alive) all_bytes += s.m * s.ldA * (int64_t)c->es;
+    int64_t all_bytes = 0, largest_group = 0;
+    batch_sizes(c, c->tile, &all_bytes, &largest_group);
     std::vector<int64_t> item_bytes;
     int64_t parts = 0, part = 0;
     double bytes = 0.0;
@@ -227,7 +240,7 @@ modap_status rebuild(modap_batch *c) {
         const BatchCut cut = cut_of(c, s, d.RPW, d.C, c->tile);
         const int64_t row_bytes = s.ldA * (int64_t)c->es;
         const int64_t ncells = (s.m + cut.rows_per_cell - 1) / cut.rows_per_cell;
-        const int64_t per_item = plan_cells_per_item(cut, row_bytes, all_bytes, c->grid, c->cu_count);
+        const int64_t per_item = plan_cells_per_item(cut, row_bytes, all_bytes, c->grid, c->cu_count, largest_group);
         d.rows_per_cell = cut.rows_per_cell;
         d.G = cut.cells;
         d.grouped = per_item == cut.cells;
@@ -1101,19 +1114,18 @@ modap_status modap_batch_autotune(modap_batch *c, int reps, modap_batch_tile *be
     // the cut of every live system under a tile: a candidate that cuts them
     // all as the incumbent does is the same work, and is not timed (its
     // timing could only differ by noise)
-    int64_t total = 0;
-    for (const BSys &s : c->sys)
-        if (s.alive) total += s.m * s.ldA * (int64_t)c->es;
     auto all_cuts = [&](const modap_batch_tile &t) {
         std::vector<int64_t> v;
         const int64_t grid = t.grid > 0 ? t.grid : c->cu_count * std::max(1, c->per_cu);
+        int64_t total = 0, largest_group = 0;
+        batch_sizes(c, t, &total, &largest_group);
         for (const BSys &s : c->sys)
             if (s.alive) {
                 int32_t rpw = 1, chunks = 1;
                 kernel_form(c->dt, s, &rpw, &chunks);
                 const BatchCut cut = cut_of(c, s, rpw, chunks, t);
                 v.insert(v.end(), {cut.rows_per_cell, cut.cells,
-                                   plan_cells_per_item(cut, s.ldA * (int64_t)c->es, total, grid, c->cu_count)});
+                                   plan_cells_per_item(cut, s.ldA * (int64_t)c->es, total, grid, c->cu_count, largest_group)});
             }
         return v;
     };

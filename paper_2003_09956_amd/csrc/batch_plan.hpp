@@ -51,16 +51,21 @@ inline BatchCut plan_cut(int64_t m, int64_t ldA, int64_t elem_bytes, int32_t ite
 // each workgroup of the grid.  Cells that are written one by one spread a small
 // batch over the device (seven BF16 systems of 78 MB in all: 210 us an iteration
 // as 56 groups, 56 as 184 cells), but writing and reading back eight times the
-// partials costs a larger one.  The line is at 7/4 groups a CU (us an iteration by
-// groups and by cells: FP32 1400 x 3000, 2.0 a CU 179 and 223, 4.0 351 and 423;
-// FP64 700 x 3000, 1.5 160 and 154, 2.0 181 and 207; BF16 2000 x 4000, 1.5 179 and
-// 172, 1.75 183 and 200; FP64 1000 x 10000, 1.25 516 and 448, 1.9 611 and 654).
+// partials costs a larger one.  The line is at 7/4 groups of the largest size a CU
+// (us an iteration by groups and by cells: FP32 1400 x 3000, 2.0 a CU 179 and 223,
+// 4.0 351 and 423; FP64 700 x 3000, 1.5 160 and 154, 2.0 181 and 207; BF16
+// 2000 x 4000, 1.5 179 and 172, 1.75 183 and 200; FP64 1000 x 10000, 1.25 516 and
+// 448, 1.9 611 and 654).  A batch with larger groups is cut up anyway, and the
+// systems between make better items as cells: only those are left whole whose
+// groups are less than half the share of a workgroup (64 FP32 systems of 64 to
+// 2048 columns: 125 us a sweep, 138 with the line of the even batches).
 constexpr int64_t kItemsPerWorkgroup = 4;
-inline int64_t plan_cells_per_item(const BatchCut &cut, int64_t row_bytes, int64_t batch_bytes, int64_t grid, int64_t cus) {
-    const int64_t cell = cut.rows_per_cell * row_bytes;
-    if (4 * batch_bytes >= 7 * cus * cell * cut.cells) return cut.cells;
-    const int64_t cells = std::max<int64_t>(1, batch_bytes / std::max<int64_t>(1, grid * kItemsPerWorkgroup) / cell);
-    return std::min<int64_t>(cells, cut.cells);
+inline int64_t plan_cells_per_item(const BatchCut &cut, int64_t row_bytes, int64_t batch_bytes, int64_t grid, int64_t cus,
+                                   int64_t largest_group) {
+    if (4 * batch_bytes >= 7 * cus * largest_group) return cut.cells;
+    const int64_t want = batch_bytes / std::max<int64_t>(1, grid * kItemsPerWorkgroup);
+    const int64_t cells = std::max<int64_t>(1, want / (cut.rows_per_cell * row_bytes));
+    return 2 * cells > cut.cells ? cut.cells : cells;
 }
 
 // Row form of a system: rows of at most 64 16-byte vectors (C == 1) run four

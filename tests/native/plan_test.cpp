@@ -16,10 +16,13 @@ static int failures = 0;
 using namespace modap_host;
 
 // Whether `count` systems of m rows of ldA elements are swept by groups.
-static bool by_groups(int64_t count, int64_t m, int64_t ldA, int64_t es, int32_t item_kib, int64_t per_cu) {
+// other_group: bytes of the largest group of another system.
+static bool by_groups(int64_t count, int64_t m, int64_t ldA, int64_t es, int32_t item_kib, int64_t per_cu,
+                      int64_t other_group = 0) {
     const BatchCut cut = plan_cut(m, ldA, es, item_kib, 0, 16, 8);
-    const int64_t bytes = m * ldA * es;
-    return cut.cells > 1 && plan_cells_per_item(cut, ldA * es, count * bytes, 256 * per_cu, 256) == cut.cells;
+    const int64_t bytes = m * ldA * es, group = cut.cells * cut.rows_per_cell * ldA * es;
+    return cut.cells > 1 &&
+           plan_cells_per_item(cut, ldA * es, count * bytes, 256 * per_cu, 256, std::max(group, other_group)) == cut.cells;
 }
 
 int main() {
@@ -30,8 +33,11 @@ int main() {
                 for (int64_t total : {int64_t(1), m * ldA * es, 100 * m * ldA * es, int64_t(1) << 40}) {
                     const BatchCut cut = plan_cut(m, ldA, es, 4096, 0, 16, 8);
                     EXPECT(cut.cells >= 1 && cut.cells <= 8 && cut.rows_per_cell % 16 == 0);
-                    const int64_t c = plan_cells_per_item(cut, ldA * es, total, 512, 256);
-                    EXPECT(c >= 1 && c <= cut.cells);
+                    const int64_t group = cut.cells * cut.rows_per_cell * ldA * es;
+                    for (int64_t largest : {group, 100 * group}) {
+                        const int64_t c = plan_cells_per_item(cut, ldA * es, total, 512, 256, largest);
+                        EXPECT(c >= 1 && c <= cut.cells);
+                    }
                 }
     // 7/4 groups a CU and more: eight groups a system here
     EXPECT(by_groups(64, 3000, 1400, 4, 8192, 2));     // 2.0 groups a CU
@@ -39,6 +45,9 @@ int main() {
     EXPECT(by_groups(64, 3000, 700, 8, 8192, 2));
     EXPECT(by_groups(128, 3000, 600, 4, 4096, 2));
     EXPECT(by_groups(64, 4000, 2000, 2, 4096, 1));
+    // beside larger groups: less than half the share of a workgroup
+    EXPECT(!by_groups(64, 3000, 1400, 4, 8192, 2, int64_t(8) << 20));
+    EXPECT(by_groups(300, 3000, 1400, 4, 8192, 2, int64_t(32) << 20));
     EXPECT(!by_groups(48, 3000, 1400, 4, 8192, 2));    // 1.5
     EXPECT(!by_groups(32, 4000, 2000, 2, 4096, 1));    // 1.0
     EXPECT(!by_groups(7, 4000, 2000, 2, 4096, 1));
