@@ -21,9 +21,11 @@ inline int bucket_of(int C) { return C == 1 ? 0 : C == 2 ? 1 : C == 4 ? 2 : 3; }
 // are added in order -- by the sweep, where an item is a whole group, or by
 // the reduction, where it is less: the same sums either way.  `unit` rows are
 // the step that cells are a multiple of.  A cell's end costs the sweep ten rows
-// of LDS traffic, so its size goes with the element: 256 KiB in 2 and 4 bytes
-// (in 512 KiB a BF16 system of 6.7 MB takes 48 us an iteration for 25), 512
-// KiB in 8 (in 256, 200 systems of 8 MB take 280 us for 271).
+// of LDS traffic, so a cell has 256 KiB at least in 2 and 4 bytes an element (in
+// 512 KiB a BF16 system of 6.7 MB takes 48 us an iteration for 25), 512 KiB in 8
+// (in 256, 200 systems of 8 MB take 280 us for 271), and 128 rows of BF16 or 64 of
+// FP32 (128 BF16 systems of 2000 x 4000 in cells of 64 rows 372 us, of 128 350; of
+// 4000 x 1100 in 32 rows 242, in 128 220).
 constexpr int64_t kMinItems = 8;
 constexpr int64_t kMinItemKib = 32;
 constexpr int32_t kMaxMinItems = 64;
@@ -31,7 +33,9 @@ struct BatchCut {
     int64_t rows_per_cell;
     int32_t cells;          // cells per group
 };
-inline int64_t cell_kib(int64_t elem_bytes) { return std::max<int64_t>(256, 64 * elem_bytes); }
+inline int64_t cell_kib(int64_t elem_bytes, int64_t row_bytes) {
+    return std::max({int64_t(256), 64 * elem_bytes, 256 / elem_bytes * row_bytes / 1024});
+}
 inline BatchCut plan_cut(int64_t m, int64_t ldA, int64_t elem_bytes, int32_t item_kib, int32_t min_items, int64_t unit,
                          int32_t max_cells) {
     const int64_t row_bytes = ldA * elem_bytes;
@@ -39,7 +43,7 @@ inline BatchCut plan_cut(int64_t m, int64_t ldA, int64_t elem_bytes, int32_t ite
     const int64_t least = min_items > 0 ? min_items : kMinItems;
     const int64_t kib = std::min(cap, std::max(kMinItemKib, sys_kib / least));
     BatchCut c{0, 1};
-    if (min_items <= 0) c.cells = (int32_t)std::clamp<int64_t>(kib / cell_kib(elem_bytes), 1, max_cells);
+    if (min_items <= 0) c.cells = (int32_t)std::clamp<int64_t>(kib / cell_kib(elem_bytes, row_bytes), 1, max_cells);
     int64_t r = kib * 1024 / (row_bytes * c.cells);
     r = std::max(unit, (r + unit - 1) / unit * unit);
     c.rows_per_cell = std::min(r, (m + unit - 1) / unit * unit);
