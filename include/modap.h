@@ -217,7 +217,10 @@ modap_status modap_update_coeffs(modap_ctx *ctx, int64_t k, const int64_t *rows,
  * [T x ldv] FP64 array, ldv >= n), i.e. b <- b + A V[s], fused into the next
  * sweep.  This is the non-stationary workload of section 5 (a polytope moved
  * by a translation between iterations).  T = 0 or V = NULL removes it.
- * Errors: E_STATE, E_INVAL, E_NOMEM. */
+ * A schedule in host memory has been read when the call returns, pinned memory
+ * too; one in device memory is read in stream order.  A context whose stream
+ * is being captured refuses the call.
+ * Errors: E_STATE, E_INVAL, E_NOMEM, E_DEVICE. */
 modap_status modap_set_drift(modap_ctx *ctx, int64_t T, const double *V, int64_t ldv,
                              int ptrs_on_device);
 
@@ -232,8 +235,10 @@ modap_status modap_iterate(modap_ctx *ctx, const modap_params *params, int64_t k
 
 /* Iterate until x is eps-feasible (OK), max_iters steps were taken
  * (E_NOT_CONVERGED), no step direction exists (E_INFEASIBLE) or a NaN/Inf
- * appears (E_NUMERIC).  The host reads the device's stop flag once per batch
- * of queued iterations; no per-iteration synchronisation.  out may be NULL. */
+ * appears (E_NUMERIC).  The device tells the host each check it settles, and the
+ * host keeps a few iterations queued beyond it (small systems: chunks of
+ * iterations in one launch); no per-iteration synchronisation.  out may be
+ * NULL. */
 modap_status modap_solve(modap_ctx *ctx, const modap_params *params, modap_stats *out);
 
 /* One sweep at the caller's point x ([n]) on the current data (including any
@@ -260,7 +265,9 @@ modap_status modap_query(modap_ctx *ctx, double *x, double *b, modap_stats *out,
  * for a shape the library does not provide for the loaded system. */
 modap_status modap_set_tile(modap_ctx *ctx, const modap_tile *tile);
 
-/* The kernel shape in use for the loaded system.  Errors: E_STATE, E_INVAL. */
+/* The kernel shape in use for the loaded system.  For kind 1 it is the shape of
+ * the two phases, also where A is read once instead; setting it forces the two
+ * phases.  Errors: E_STATE, E_INVAL. */
 modap_status modap_get_tile(modap_ctx *ctx, modap_tile *tile);
 
 /* Autotuner: time every compiled sweep shape that covers the loaded rows, at
@@ -314,7 +321,8 @@ typedef struct {
  * results depend on its cut (the order in which item partials are added). */
 typedef struct {
     int32_t item_kib[4];    /* largest KiB of A per work item, buckets C = 1, 2, 4, 8 (>= 1) */
-    int32_t grid;           /* workgroups of the batch sweep (0: every workgroup that can be resident) */
+    int32_t grid;           /* workgroups of the batch sweep (0: every workgroup that can be resident, one per CU where
+                               that leaves fewer than two work items each) */
     int32_t min_items;      /* items per system at least, 1 .. 64 (0: the library's choice: 8, and items of
                                a part of that size where the batch is small, with the same results) */
 } modap_batch_tile;

@@ -1104,7 +1104,7 @@ modap_status set_system(modap_ctx *c, int64_t m, int64_t n, modap_dtype storage,
         c->tile_forced = false;
         if ((st = configure(c, t))) {
             if (owned) c->A = nullptr;
-        release_system(c);
+            release_system(c);
             return st;
         }
     }
