@@ -322,7 +322,7 @@ typedef struct {
 typedef struct {
     int32_t item_kib[4];    /* largest KiB of A per work item, buckets C = 1, 2, 4, 8 (>= 1) */
     int32_t grid;           /* workgroups of the batch sweep (0: every workgroup that can be resident, one per CU where
-                               that leaves fewer than two work items each) */
+                               that leaves fewer than two work items each and min_items is 0) */
     int32_t min_items;      /* items per system at least, 1 .. 64 (0: the library's choice: 8, and items of
                                a part of that size where the batch is small, with the same results) */
 } modap_batch_tile;

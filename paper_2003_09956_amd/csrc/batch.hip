@@ -295,13 +295,7 @@ modap_status rebuild(modap_batch *c) {
         HIP_TRY(c, hipMemcpyAsync(c->d_cols, c->h_cols.data(), sizeof(BatchCol) * c->h_cols.size(),
                                   hipMemcpyHostToDevice, c->stream));
     }
-    // Fewer than two items for each workgroup: one workgroup per CU instead
-    // (a second one on some CUs slows the first, and the kernel waits for those;
-    // us an iteration, 16 FP64 systems of 17 MB 77 and 58, 16 FP32 of 7 MB 53 and
-    // 41, 64 FP64 of 2 MB 54 and 38; from two items on two are better, 128 FP64 of
-    // 2 MB 60 and 64).
-    if (c->tile.grid == 0 && c->nitems < 2 * c->grid) c->grid = c->cu_count;
-    c->grid = std::max(1, std::min(c->grid, std::max(1, c->nitems)));
+    c->grid = (int)plan_grid(c->tile.grid, c->per_cu, c->cu_count, c->nitems, c->tile.min_items);
     c->dirty = false;
     return MODAP_OK;
 }

@@ -72,6 +72,21 @@ inline int64_t plan_cells_per_item(const BatchCut &cut, int64_t row_bytes, int64
     return 2 * cells > cut.cells ? cut.cells : cells;
 }
 
+// Workgroups of the batch sweep: `tuned` if positive, else every one that can be
+// resident (per_cu a CU).  Fewer than two items for each of those: one workgroup
+// per CU instead (a second one on some CUs slows the first, and the kernel waits
+// for those; us an iteration, 16 FP64 systems of 17 MB 77 and 58, 16 FP32 of 7 MB
+// 53 and 41, 64 FP64 of 2 MB 54 and 38; from two items on two are better, 128 FP64
+// of 2 MB 60 and 64).  Not where min_items sets the cut: the autotuner, which sets
+// it, compares cuts by sweeps without a translation, where one long item a system
+// on one workgroup per CU looked best (512 FP32 systems of 256 x 2048: 165 us,
+// two items 169) that lost with one (205, two items 195); grids it tries by itself.
+inline int64_t plan_grid(int64_t tuned, int64_t per_cu, int64_t cus, int64_t items, int32_t min_items) {
+    int64_t grid = tuned > 0 ? tuned : cus * per_cu;
+    if (tuned <= 0 && min_items <= 0 && items < 2 * grid) grid = cus;
+    return std::max<int64_t>(1, std::min(grid, std::max<int64_t>(1, items)));
+}
+
 // Row form of a system: rows of at most 64 16-byte vectors (C == 1) run four
 // to a wavefront, 16 lanes each, with 1, 2 or 4 chunks per lane; longer rows
 // (or with the short form switched off) one to a wavefront with C chunks.

@@ -51,6 +51,18 @@ int main() {
     EXPECT(!by_groups(48, 3000, 1400, 4, 8192, 2));    // 1.5
     EXPECT(!by_groups(32, 4000, 2000, 2, 4096, 1));    // 1.0
     EXPECT(!by_groups(7, 4000, 2000, 2, 4096, 1));
+    // the grid: two workgroups a CU from two items each on, one below, where the
+    // count of items is not set; a tuned grid as it is; never more than items
+    EXPECT(plan_grid(0, 2, 256, 1024, 0) == 512);
+    EXPECT(plan_grid(0, 2, 256, 1023, 0) == 256);
+    EXPECT(plan_grid(0, 2, 256, 1023, 1) == 512);
+    EXPECT(plan_grid(0, 2, 256, 512, 1) == 512);
+    EXPECT(plan_grid(0, 2, 256, 100, 1) == 100);
+    EXPECT(plan_grid(0, 1, 256, 300, 0) == 256);
+    EXPECT(plan_grid(0, 2, 256, 100, 0) == 100);
+    EXPECT(plan_grid(0, 2, 256, 0, 0) == 1);
+    EXPECT(plan_grid(512, 2, 256, 600, 0) == 512);
+    EXPECT(plan_grid(300, 2, 256, 200, 4) == 200);
     if (failures) return 1;
     std::puts("all plan checks passed");
     return 0;
