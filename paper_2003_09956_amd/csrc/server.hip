@@ -25,6 +25,7 @@
 #include "trace.hpp"
 #include "internal.hpp"
 #include "modap.h"
+#include "stage_pool.hpp"
 
 using namespace modap_host;
 
@@ -71,15 +72,6 @@ void end_trace(Req &r) {
     r.trace = 0;
 }
 
-// Device memory for the inputs of one update, reusable once the update that
-// read it has run (its event has completed).
-struct Stage {
-    void *p = nullptr;
-    size_t size = 0;
-    hipEvent_t used = nullptr;
-    bool busy = false;
-};
-
 }  // namespace
 
 struct modap_server {
@@ -98,7 +90,7 @@ struct modap_server {
     hipStream_t batch_stream = nullptr;
     hipStream_t copy_stream = nullptr;    // staging of device-side update inputs
     hipStream_t spare = nullptr;          // the stream of the last request with a context of its own, for the next
-    std::vector<Stage> stages;
+    StagePool stages;                     // device-side update inputs
     int batch_live = 0;
     std::vector<Req> reqs;              // every request, indexed by ticket
     std::deque<int64_t> pending;
@@ -122,39 +114,17 @@ int64_t batch_row_limit(int dt) { return 64 * (int64_t)vec_elems(dt) * 8; }
 // gets a context of its own.
 bool batched(const modap_server *s, const Req &r) { return r.ldA <= batch_row_limit(s->dt); }
 
-// A staging buffer of at least `bytes` whose last update has run, from the
-// server's pool (grown when none is free).
+// A staging buffer of at least `bytes` whose last update has run.
 modap_status take_stage(modap_server *s, size_t bytes, Stage **out) {
-    for (Stage &t : s->stages) {
-        if (t.busy) {
-            const hipError_t e = hipEventQuery(t.used);
-            if (e == hipSuccess) {
-                t.busy = false;
-            } else if (e != hipErrorNotReady) {
-                s->err = std::string("hipEventQuery: ") + hipGetErrorString(e);
-                return MODAP_E_DEVICE;
-            }
-        }
-        if (!t.busy && t.size >= bytes) {
-            *out = &t;
-            return MODAP_OK;
-        }
-    }
-    Stage t;
-    t.size = (bytes + (1u << 20) - 1) / (1u << 20) * (1u << 20);
-    if (hipMalloc(&t.p, t.size) != hipSuccess) {
-        (void)hipGetLastError();
+    const char *what = "";
+    const hipError_t e = s->stages.take(bytes, out, &what);
+    if (e == hipSuccess) return MODAP_OK;
+    if (std::string(what) == "hipMalloc") {
         s->err = "no device memory to stage an update";
         return MODAP_E_NOMEM;
     }
-    if (hipEventCreateWithFlags(&t.used, hipEventDisableTiming) != hipSuccess) {
-        (void)hipFree(t.p);
-        s->err = "hipEventCreateWithFlags failed";
-        return MODAP_E_DEVICE;
-    }
-    s->stages.push_back(t);
-    *out = &s->stages.back();
-    return MODAP_OK;
+    s->err = std::string(what) + ": " + hipGetErrorString(e);
+    return MODAP_E_DEVICE;
 }
 
 double elapsed_since(std::chrono::steady_clock::time_point t0) {
@@ -196,10 +166,12 @@ hipError_t take_stream(modap_server *s, Req &r) {
 }
 
 void give_stream(modap_server *s, Req &r) {
-    if (r.stream && !s->spare)
+    if (r.stream && !s->spare) {
         s->spare = r.stream;
-    else if (r.stream)
+    } else if (r.stream) {
+        s->stages.end_stream(r.stream);
         (void)hipStreamDestroy(r.stream);
+    }
     r.stream = nullptr;
 }
 
@@ -335,11 +307,7 @@ void modap_server_destroy(modap_server *s) {
         end_trace(r);
     }
     modap_batch_destroy(s->batch);
-    for (Stage &t : s->stages) {
-        (void)hipEventSynchronize(t.used);
-        (void)hipFree(t.p);
-        (void)hipEventDestroy(t.used);
-    }
+    s->stages.destroy();
     if (s->spare) (void)hipStreamDestroy(s->spare);
     if (s->copy_stream) (void)hipStreamDestroy(s->copy_stream);
     if (s->batch_stream) (void)hipStreamDestroy(s->batch_stream);
@@ -465,8 +433,7 @@ modap_status modap_server_update(modap_server *s, int64_t ticket, int64_t k, con
                                  : modap_update_coeffs(r.ctx, k, rp, np, bp, vp, ptrs_on_device);
     if (stage) {
         // reusable once whatever the update queued on the request's stream has run
-        HIP_TRY(s, hipEventRecord(stage->used, gs));
-        stage->busy = true;
+        HIP_TRY(s, s->stages.used(stage, gs));
     }
     if (st) return fail(s, st, r.in_batch ? modap_batch_last_error(s->batch) : modap_last_error(r.ctx));
     return MODAP_OK;
