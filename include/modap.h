@@ -28,7 +28,9 @@
  *    of the context's GPU (e.g. torch.Tensor.data_ptr() of a tensor on it).
  *  - Ordering: work is queued on the context's stream in call order.
  *    set_system, set_x, set_drift, update_coeffs and iterate (without stats)
- *    are asynchronous with respect to the host once host inputs are copied;
+ *    are asynchronous with respect to the host once host inputs are copied
+ *    (inputs in pinned memory are copied in stream order, so the calls wait
+ *    for what is queued before them, except under stream capture);
  *    solve, eval_sweep, query and any call given a stats pointer synchronise.
  *  - Layout: A is dense row-major, row i at A + i*lda elements, lda >= n, in
  *    the storage type; b is m doubles; x, v are n doubles.  BF16 elements are

@@ -803,6 +803,7 @@ modap_status modap_batch_set_drift(modap_batch *c, int64_t id, int64_t T, const 
     }
     HIP_TRY(c, aux_ctl_set_drift(s->ctl, sl, s->T, c->stream));
     c->dirty = true;
+    if (!on_dev && s->T > 0) HIP_TRY(c, inputs_read(c->stream, {V}));
     return MODAP_OK;
 }
 

@@ -1219,6 +1219,7 @@ modap_status modap_set_x(modap_ctx *c, const double *x, int on_dev) {
     }
     hipLaunchKernelGGL(ctl_restart, dim3(1), dim3(64), 0, c->stream, c->ctl, last_slot(c));
     LAUNCH_TRY(c, "ctl_restart launch");
+    if (!on_dev) HIP_TRY(c, inputs_read(c->stream, {x}));
     return MODAP_OK;
 }
 
@@ -1265,6 +1266,8 @@ modap_status modap_update_coeffs(modap_ctx *c, int64_t k, const int64_t *rows, c
         LAUNCH_TRY(c, "vpend_add launch");
         c->vpend_maybe = true;
     }
+    if (!on_dev && k > 0) HIP_TRY(c, inputs_read(c->stream, {rows, new_rows, new_b}));
+    if (!on_dev) HIP_TRY(c, inputs_read(c->stream, {v}));
     return MODAP_OK;
 }
 

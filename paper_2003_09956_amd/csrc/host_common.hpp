@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <initializer_list>
 #include <string>
 
 #include "modap.h"
@@ -41,6 +42,31 @@ modap_status hip_fail(Ctx *c, hipError_t e, const char *what) {
     (void)hipGetLastError();
     if (e == hipErrorOutOfMemory) return fail(c, MODAP_E_NOMEM, std::string(what) + ": out of device memory");
     return fail(c, MODAP_E_DEVICE, std::string(what) + ": " + hipGetErrorString(e));
+}
+
+// Whether an asynchronous copy from host memory `p` reads it only when the
+// stream comes to it: from pinned memory it does, from pageable memory the
+// runtime has read it when the call returns.
+inline bool read_later(const void *p) {
+    hipPointerAttribute_t at{};
+    if (!p || hipPointerGetAttributes(&at, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return at.type == hipMemoryTypeHost || at.type == hipMemoryTypeManaged;
+}
+
+// The caller's host inputs of a call are the caller's again when it returns: wait
+// for the copies out of them, if there are any that the stream has still to come
+// to.  (Nothing can be waited for under capture; a replay reads them again.)
+inline hipError_t inputs_read(hipStream_t s, std::initializer_list<const void *> inputs) {
+    for (const void *p : inputs)
+        if (read_later(p)) {
+            hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+            if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+            return cap == hipStreamCaptureStatusNone ? hipStreamSynchronize(s) : hipSuccess;
+        }
+    return hipSuccess;
 }
 
 inline size_t elem_size(int dt) { return dt == 0 ? 8 : dt == 1 ? 4 : 2; }
